@@ -344,7 +344,7 @@ typedef struct {
 int agile_clients_create(agile_clients** out, agile_rt* const* tables, uint32_t n, int device);
 int agile_clients_destroy(agile_clients* cs);
 
-/* Run `nreq` requests (host array) in one persistent launch on `stream`. d_ptrs holds the
+/* Run `nreq` requests (host array) in one launch on `stream`. d_ptrs holds the
  * pointer arguments of all requests (device, 16-byte aligned); d_ptr_verdict / d_ptr_owner
  * (device, one entry per pointer) receive each pointer's verdict and owner; d_result (device
  * memory, or pinned host memory from hipHostMalloc; nreq entries) receives each request's

@@ -108,17 +108,12 @@ static_assert(sizeof(BatchReq) == 96, "BatchReq mirrors agile_request");
 
 struct BatchScratch {
     unsigned int minfail;      // lowest failing pointer index of the request (or ~0)
-    unsigned int remaining;    // tiles of the request not finished yet
+    unsigned int remaining;    // pieces (workgroups) of the request not finished yet
     unsigned long long gcount; // gather denials
     unsigned long long gminkey;
     unsigned long long pad;
 };
 static_assert(sizeof(BatchScratch) == 32, "BatchScratch is 32 bytes");
-
-struct BatchCtl {
-    unsigned int next;  // next tile to hand out
-    unsigned int pad[15];
-};
 
 struct agile_req_result_dev {
     uint32_t verdict;
@@ -140,7 +135,6 @@ struct BatchGuard {
 };
 
 struct BatchArgs {
-    BatchCtl* ctl;
     const uint64_t* tstart;  // nreq + 1 entries: first tile of each request, then the total
     const uint32_t* tile_req;  // ntiles entries: the request each tile belongs to
     const BatchGuard* guards;  // nreq entries
@@ -152,17 +146,20 @@ struct BatchArgs {
     int32_t* po;
     agile_req_result_dev* result;
     uint64_t ntiles;
+    uint64_t tile0;      // first tile of this launch
     uint64_t tile_copy;  // bytes per copy tile of this launch
     uint64_t tile_rows;  // rows per gather tile of this launch
     uint32_t nreq;
     uint32_t pad;
 };
 
-// Tile sizes of one launch: small launches get small tiles, so that even one request spreads
-// over the whole chip; large launches get the largest tiles (fewer claims, longer streams).
-void batch_tile_sizes(uint64_t copy_bytes, uint64_t gather_rows, const DevInfo& d,
-                      uint64_t& tile_copy, uint64_t& tile_rows);
+// Tile sizes of one launch, a request's tiles, and how many workgroups work on `tiles` of them.
+void batch_tile_sizes(uint64_t copy_bytes, uint64_t gather_rows, uint64_t& tile_copy,
+                      uint64_t& tile_rows);
 uint64_t batch_tiles(const BatchReq& q, uint64_t tile_copy, uint64_t tile_rows);
-hipError_t launch_batch(const BatchArgs& a, const DevInfo& d, hipStream_t s);
+uint64_t batch_limit_tiles(const BatchReq& q);
+uint32_t batch_pieces(uint64_t tiles);
+hipError_t launch_batch(BatchArgs a, hipStream_t s);
+hipError_t launch_batch_pull(void* dst, const void* src, uint64_t bytes, hipStream_t s);
 
 }  // namespace agile

@@ -1031,10 +1031,12 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
         total_rows = q.gather_n > U64MAX - total_rows ? U64MAX : total_rows + q.gather_n;
     }
     uint64_t tile_copy, tile_rows;
-    batch_tile_sizes(total_copy, total_rows, cs->tables[0]->info, tile_copy, tile_rows);
-    uint64_t ntiles = 0;
-    for (uint32_t r = 0; r < nreq; ++r)
+    batch_tile_sizes(total_copy, total_rows, tile_copy, tile_rows);
+    uint64_t ntiles = 0, limit = 0;
+    for (uint32_t r = 0; r < nreq; ++r) {
         ntiles += batch_tiles(reinterpret_cast<const BatchReq&>(reqs[r]), tile_copy, tile_rows);
+        limit += batch_limit_tiles(reinterpret_cast<const BatchReq&>(reqs[r]));
+    }
     DeviceGuard dg(cs->device);
     if (!dg.ok) return AGILE_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -1042,9 +1044,9 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
         const int rc = prepare(rt, s);
         if (rc != AGILE_OK) return rc;
     }
-    // layout: ctl | tstart[nreq+1] | reqs | scratch | tables | guards[nreq] | tile_req[ntiles]
-    if (ntiles > 0xFFFFFFFFull) return AGILE_EINVAL;
-    const size_t o_ts = align64(sizeof(BatchCtl));
+    // layout: tstart[nreq+1] | reqs | scratch | tables | guards[nreq] | tile_req[ntiles]
+    if (ntiles > 0xFFFFFFFFull || limit > 0xFFFFFFFFull) return AGILE_EINVAL;
+    const size_t o_ts = 0;
     const size_t o_rq = o_ts + align64((size_t)(nreq + 1) * 8);
     const size_t o_sc = o_rq + align64((size_t)nreq * sizeof(BatchReq));
     const size_t o_tb = o_sc + align64((size_t)nreq * sizeof(BatchScratch));
@@ -1091,7 +1093,6 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
         sl.dcap = sl.hcap = cap;
     }
     uint8_t* h = static_cast<uint8_t*>(sl.hstage);
-    std::memset(h, 0, o_ts);
     uint64_t* ts = reinterpret_cast<uint64_t*>(h + o_ts);
     BatchReq* rq = reinterpret_cast<BatchReq*>(h + o_rq);
     BatchScratch* sc = reinterpret_cast<BatchScratch*>(h + o_sc);
@@ -1116,18 +1117,16 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
                                         q.gather_table, q.gather_n, q.gather_row_bytes, 4)
                            : rows_open(0, 4, 4);
         sc[r].minfail = 0xFFFFFFFFu;
-        sc[r].remaining = (unsigned int)k;
+        sc[r].remaining = batch_pieces(k);
         sc[r].gcount = 0;
         sc[r].gminkey = ~0ull;
         sc[r].pad = 0;
     }
     ts[nreq] = acc;
     for (uint32_t c = 0; c < ncl; ++c) tb[c] = cs->tables[c]->tab;
-    if (hipMemcpyAsync(sl.dmem, h, bytes, hipMemcpyHostToDevice, s) != hipSuccess)
-        return AGILE_EDEVICE;
+    if (launch_batch_pull(sl.dmem, h, bytes, s) != hipSuccess) return AGILE_EDEVICE;
     uint8_t* d = static_cast<uint8_t*>(sl.dmem);
     BatchArgs A{};
-    A.ctl = reinterpret_cast<BatchCtl*>(d);
     A.tstart = reinterpret_cast<const uint64_t*>(d + o_ts);
     A.reqs = reinterpret_cast<const BatchReq*>(d + o_rq);
     A.scratch = reinterpret_cast<BatchScratch*>(d + o_sc);
@@ -1142,7 +1141,7 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
     A.tile_copy = tile_copy;
     A.tile_rows = tile_rows;
     A.nreq = nreq;
-    if (launch_batch(A, cs->tables[0]->info, s) != hipSuccess) return AGILE_EDEVICE;
+    if (launch_batch(A, s) != hipSuccess) return AGILE_EDEVICE;
     if (hipEventRecord(sl.done, s) != hipSuccess) return AGILE_EDEVICE;
     sl.used = true;
     return AGILE_OK;

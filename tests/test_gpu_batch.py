@@ -183,3 +183,74 @@ def test_batch_against_oracle_and_alone_identity(seed, n_ranges):
     for c, cl in enumerate(cls):
         assert np.array_equal(cl.dev.cpu().numpy(), cl.mem.buffer(cl.base))
     g.agile_clients_destroy(cs)
+
+
+@pytest.mark.parametrize("src_off,dst_off", [(0, 0), (5, 0), (0, 3), (4, 9), (15, 1)])
+def test_batch_copies_at_the_edges_of_tiles(src_off, dst_off):
+    """Copies around a workgroup's pass (32 KiB) and a tile (128 KiB), with the source and the
+    destination at any place in a 16-byte vector, whole and with either end denied, against the
+    oracle byte for byte and in their fault records."""
+    need_gpu()
+    g = guard_mod()
+    sizes = [1, 15, 16, 17, 32767, 32768, 32784, 131071, 131072, 131073, 300001]
+    cap = max(sizes) + 64
+    n = len(sizes) * 3
+    gen = torch.Generator().manual_seed(src_off * 16 + dst_off)
+    host = torch.randint(0, 256, (cap * (n + 1) + 4096,), dtype=torch.uint8, generator=gen)
+    dev = host.cuda()
+    mem, ot, rt = Memory(), OracleTable(), g.RangeTable(n * 2 + 8)
+    mem.add(dev.data_ptr(), host.numpy())
+    base = dev.data_ptr() + (-dev.data_ptr()) % 16
+    reqs = np.zeros(n, dtype=g.REQUEST_DTYPE)
+    src_end = base + src_off + 200_000      # the source's range ends inside the largest copies
+    ranges = [(base, src_end - base)]
+    for r in range(n):
+        size, cut = sizes[r // 3], (r % 3) * 9      # destination: whole, 9 or 18 bytes short
+        lo = base + cap * (r + 1)
+        lo += -lo % 16 + dst_off
+        if size > cut:
+            ranges.append((lo, size - cut))
+        reqs[r]["copy_src"], reqs[r]["copy_dst"], reqs[r]["copy_bytes"] = base + src_off, lo, size
+    for b, s in ranges:
+        rt.insert(b, s, 0)
+        ot.insert(b, s, 0)
+    cs = g.agile_clients_create([rt])
+    _, _, res = run_batch(g, cs, reqs, torch.zeros((1, 2), dtype=torch.int64, device="cuda"), 0)
+    assert (res["done"] == 1).all()
+    for r, q in enumerate(reqs):
+        log = G.FaultLog()
+        G.copy_vec(ot, mem, log, r, int(q["copy_dst"]), int(q["copy_src"]), int(q["copy_bytes"]))
+        check_fault(res[r], log, r, r)
+    assert np.array_equal(dev.cpu().numpy(), mem.buffer(dev.data_ptr()))
+    g.agile_clients_destroy(cs)
+
+
+@pytest.mark.parametrize("n_ranges,align", [(4096, 4096), (4100, 1), (8192, 4096), (8196, 4096),
+                                            (16400, 1)])
+def test_batch_pointers_with_keys_of_either_width(n_ranges, align):
+    """Tables whose bucket keys fit 32 bits (page-aligned bases) and tables whose keys do not
+    (byte-granular bases over a wide span), with the most buckets that are staged whole and a few
+    more, against the oracle at and around every range's ends."""
+    need_gpu()
+    g = guard_mod()
+    rng = random.Random(n_ranges + align)
+    ot, rt = OracleTable(), g.RangeTable(n_ranges)
+    pos, q = (1 << 41) + (0 if align > 1 else 3), []
+    for k in range(n_ranges):
+        pos += rng.randrange(0, 4) * align + (rng.randrange(1 << 24) if align == 1 else 0)
+        size = rng.choice([1, 7, align, 3 * align])
+        kind = rng.choice([0, 0, 1, 2])
+        rt.insert(pos, size, kind)
+        ot.insert(pos, size, kind)
+        q += [[pos - 1, 2], [pos, size], [pos + size - 1, 1], [pos + size, 1]]
+        pos += size + (-size) % align
+    q += [[0, 1], [(1 << 64) - 1, 1], [1 << 41, 0]]
+    qn = np.array(q, dtype=np.uint64)
+    cs = g.agile_clients_create([rt])
+    reqs = np.zeros(1, dtype=g.REQUEST_DTYPE)
+    reqs[0]["nptr"] = len(q)
+    pv, po, res = run_batch(g, cs, reqs, torch.from_numpy(qn.view(np.int64)).cuda(), len(q))
+    ev, eo = ot.verdict_many(qn[:, 0], qn[:, 1])
+    assert np.array_equal(pv, ev) and np.array_equal(po, eo)
+    assert res[0]["arg"] == int(np.flatnonzero(ev)[0]) and res[0]["done"] == 1
+    g.agile_clients_destroy(cs)
