@@ -264,8 +264,8 @@ int agile_guarded_gather(agile_rt* rt, void* d_out, const void* d_table, uint64_
  * destination whose rows are all +0.0 before the call (a fresh gradient, for instance): the
  * result is the same bit for bit, and large calls then write each row's sum without reading
  * the row; on any other destination the result is unspecified. Other values: AGILE_EINVAL.
- * With accumulate, calls of at least 32,768
- * rows sort the destination rows (scratch owned by the handle, grown on demand with
+ * With accumulate, calls of more than 2^18 rows (or of at least 32,768 rows and 96 MiB of them)
+ * sort the destination rows (scratch owned by the handle, grown on demand with
  * hipMalloc, freed by agile_rt_destroy; ENOMEM never results: without scratch the call takes
  * the chunk path) and sum each run of equal rows in index order; the order in which partial
  * sums of one row from different parts of the call are added is unspecified, as is the
@@ -283,7 +283,7 @@ int agile_fault_log_read(agile_rt* rt, agile_fault* out, int clear, void* stream
 
 /* ---- unguarded twins (same kernels with the guard compiled out; measurement only) ----
  * Every access is performed as addressed: the caller guarantees the arguments are valid.
- * agile_unguarded_scatter with accumulate (1 or 2, as above) and n >= 32,768 sorts 32-bit
+ * agile_unguarded_scatter with accumulate (1 or 2, as above) sorts, like the guarded call, by 32-bit
  * keys idx + 2^31, so its indices must lie in [-2^31, 2^31 - 1); its sort scratch is one buffer per device
  * (grown on demand), so such calls on one device must be ordered. */
 int agile_unguarded_copy(void* d_dst, const void* d_src, uint64_t nbytes, void* stream);
@@ -298,7 +298,7 @@ int agile_unguarded_scatter(void* d_dst, uint64_t row_bytes, const int64_t* d_id
 /* ---- batched multi-client requests (Section IV-B: a scheduler assigns each client to a worker;
  * Section IV-C/IV-F: every pointer argument of a mediated request is checked against the
  * calling client's own allocations before the real call). Many requests of many clients run in
- * one persistent launch; each request is judged only against its own client's table. -------- */
+ * one launch; each request is judged only against its own client's table. -------- */
 
 typedef struct agile_clients agile_clients; /* opaque: a fixed set of client tables */
 
@@ -401,7 +401,7 @@ int agile_tokens_check(agile_tokens* ts, const uint64_t* d_tokens, const uint32_
  * first; Section IV-D: revocation when a client's assignment ends) -----------------------
  * Open-loop continuous batching over agile_batch_run: requests arrive at given times, wait in
  * a FIFO, are admitted while their output fits the client's output ring and the in-flight HBM
- * budget, and run as persistent batches on up to max_inflight streams, so new batches overlap
+ * budget, and run as batches on up to max_inflight streams, so new batches overlap
  * the ones still on the device. */
 typedef struct agile_server agile_server; /* opaque */
 

@@ -9,29 +9,41 @@
 // exclusive scan, a stable scatter that ranks a tile's keys with wave ballots and regroups them
 // by digit in LDS, so that each digit's keys leave the tile as one contiguous run; a pass whose
 // digit is the same for every key is skipped on the device) orders (key, position) pairs by
-// destination row, position ascending. Each wave then walks a tile of 256 sorted entries and sums the source rows
-// of each run of equal keys in position order; a run that lies wholly inside the tile owns its
-// destination row and adds with a plain read-modify-write, a run that crosses a tile boundary
-// adds with one atomic per element. When the caller promises a destination of +0.0 rows (scatter-
-// add into zeros), an owned run stores (+0.0 + its sum) without reading the row. Rows that failed the fast test follow in a separate kernel
-// that checks every element exactly (denied loads read zero, denied stores are dropped) and
-// counts denials as the other data-dependent guarded kernels do; a one-thread kernel after the
-// launch records the smallest key.
+// destination row, position ascending. Groups of lanes (a wave for wide rows) then walk tiles of
+// sorted entries and sum the source rows of each run of equal keys in position order. A run that
+// lies inside one workgroup's tiles owns its destination row and adds with a plain
+// read-modify-write, a run that crosses workgroups adds with one atomic per element. When the caller
+// promises a destination of +0.0 rows (scatter-add into zeros), an owned run stores (+0.0 + its sum)
+// without reading the row. Rows that failed the fast test follow in a separate kernel that checks
+// every element exactly (denied loads read zero, denied stores are dropped) and counts denials as
+// the other data-dependent guarded kernels do; a one-thread kernel after the launch records the
+// smallest key.
 //
-// Chunk path (small calls, or destination intervals too large for 32-bit keys): each workgroup
-// takes 2048 consecutive indices, sorts (key, position) pairs in LDS with a bitonic network,
-// cuts the sorted chunk into pieces of at most 32 equal keys, sums each piece in position order
-// and adds the sum with one atomic per element; rows outside the interval are checked per element.
+// Chunk path (smaller calls, or destination intervals too large for 32-bit keys): one kernel, whose
+// workgroups sort 64 to 1,024 consecutive indices each in LDS and add each row of the chunk once, with
+// one atomic per element; rows outside the interval are checked per element.
+//
+// Measured against an earlier chunk path of 2,048 indices a workgroup (one CU in use for every 2,048
+// rows) and a reduce with a wave per row of any width (Zipf indices, 4,096-2^20 destination rows):
+//   rows x columns       before     now
+//     5,000 x 64         318 us     17 us   (chunks)
+//    50,000 x 32          82 us     34 us   (chunks)
+//   131,072 x 64         128 us     46 us   (chunks)
+//   1,048,576 x 32       204 us    132 us   (sorted)
+//   1,048,576 x 256      375 us    335 us   (sorted; the reduce alone 297 -> 265)
 #include <type_traits>
 
 #include "launch.h"
 
 namespace agile {
 
-constexpr int SABLOCK = 256;
-constexpr int SACHUNK = 2048;
-constexpr int SAPIECE = 32;
-constexpr uint64_t SA_SLOW = ~0ull;  // key of rows outside the destination's row interval
+constexpr int SAU = 8;               // source rows in flight per lane group
+// Rows per chunk: the least power of two from 64 to 1024 that makes at most 32 chunks. Small chunks
+// spread over more CUs, but add a hot row's sum in more steps, each of them rounded: relative
+// error of the sum for 16,384 x 32 Zipf indices 5.4e-8 with 32 chunks, 6.5e-8 with 64 (6.1e-8 for
+// chunks of 2,048 added in pieces of 32). Time 21 us against 23 us with 64 chunks of 256.
+constexpr uint64_t SA_CHUNKS = 32;
+constexpr uint64_t SA_SLOW = ~0ull;  // key of rows that fail the guard's fast test
 
 template <int W>
 struct FloatOf;
@@ -46,160 +58,203 @@ struct FloatOf<8> {
     using E = uint64_t;
 };
 
-// Exclusive block-wide prefix sum of one value per thread (SABLOCK threads); returns the total.
-__device__ inline uint32_t block_exscan(uint32_t v, uint32_t& excl, uint32_t* wsum) {
-    const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
-    uint32_t inc = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o, 64);
-        if (lane >= (uint32_t)o) inc += y;
+// One row that failed the fast test: every element checked exactly, atomics for the allowed ones
+// (a wave per row).
+template <bool GUARD, int W>
+__device__ inline void add_row_exact(uint8_t* dst, uint64_t rb, const int64_t* idx,
+                                     const uint8_t* src, uint64_t r, const RowsGuard& rg,
+                                     FaultAcc& acc) {
+    using F = typename FloatOf<W>::F;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint64_t D = rb / W;
+    const bool iok = !GUARD || r < rg.ki;
+    if (!iok && lane == 0) acc.note((r * D) << 2);
+    const int64_t iv = iok ? idx[r] : 0;
+    uint8_t* drow = dst + (uint64_t)iv * rb;
+    for (uint64_t col = lane; col < D; col += 64) {
+        const uint64_t es = r * D + col;
+        const bool sok = !GUARD || es < rg.kc;
+        if (!sok) acc.note((es << 2) | 1u);
+        // the source element is read only where its sum may be stored
+        if (!GUARD || elem_ok(rg.g, iv, rb, col, W))
+            unsafeAtomicAdd(reinterpret_cast<F*>(drow + col * W),
+                            sok ? reinterpret_cast<const F*>(src)[es] : (F)0.0);
+        else
+            acc.note((es << 2) | 2u);
     }
-    if (lane == 63) wsum[wv] = inc;
-    __syncthreads();
-    uint32_t before = 0, total = 0;
-    for (int k = 0; k < SABLOCK / 64; ++k) {
-        const uint32_t s = wsum[k];
-        if ((uint32_t)k < wv) before += s;
-        total += s;
-    }
-    excl = before + inc - v;
-    __syncthreads();
-    return total;
 }
 
+// Adds a run's sum to its destination row: columns col, col + G, ... of the row with key `key`.
 template <bool GUARD, int W, int EPL>
-__global__ __launch_bounds__(SABLOCK) void k_scatter_add(DevTable t, DevLog* log, uint8_t* dst,
+__device__ __forceinline__ void add_sum(uint8_t* dst, uint64_t rb, int64_t rlo, uint64_t key,
+                                        uint64_t col, uint32_t G, uint64_t D,
+                                        const typename FloatOf<W>::F (&sum)[EPL]) {
+    using F = typename FloatOf<W>::F;
+    if (GUARD && key == SA_SLOW) return;
+    const int64_t r = GUARD ? (int64_t)(key + (uint64_t)rlo) : (int64_t)(key ^ 0x8000000000000000ull);
+    F* d = reinterpret_cast<F*>(dst + (uint64_t)r * rb) + col;
+#pragma unroll
+    for (int q = 0; q < EPL; ++q)
+        if (col + q * G < D) unsafeAtomicAdd(d + q * G, sum[q]);
+}
+
+// CH consecutive indices per workgroup, sorted by destination row in LDS: each wave sorts 64 of them
+// (a key counts the keys before it), then each key finds its place among the other sorted blocks by
+// binary search (CH = 1024 takes two barriers and about 160 LDS reads a thread). Groups of 2^glog2 lanes walk segments of
+// `seg` sorted entries side by side: SAU source rows are loaded at once and summed in position order
+// while the destination stays the same. A run that spans segments is put together in LDS by the
+// group in whose segment it ends, so that each row of the chunk gets one atomic add per element: a
+// row's atomics are served one after another (about 25 ns for 64 bytes), and a hot row of a Zipf
+// batch has a run in every chunk. A lane holds EPL columns a group's width apart, so that each
+// atomic instruction covers whole lines.
+template <bool GUARD, int W, int EPL, int CH, int TB>
+__global__ __launch_bounds__(TB) void k_scatter_add(DevTable t, DevLog* log, uint8_t* dst,
                                                          uint64_t rb, const int64_t* idx,
                                                          const uint8_t* src, uint64_t n,
-                                                         RowsGuard rg, unsigned long long seq,
-                                                         int logon) {
+                                                         RowsGuard rg, int logon, uint32_t glog2) {
     using F = typename FloatOf<W>::F;
-    __shared__ uint64_t skey[SACHUNK];
-    __shared__ uint16_t spos[SACHUNK];
-    __shared__ uint16_t sstart[SACHUNK + 1];
-    __shared__ uint32_t wsum[SABLOCK / 64];
-    __shared__ uint32_t snp;
-
+    constexpr uint32_t NB = CH / 64;
+    __shared__ __align__(16) uint64_t kin[CH], kblk[CH];  // keys as they came, and each 64 sorted
+    __shared__ uint64_t skey[CH];
+    __shared__ uint16_t spos[CH];
+    __shared__ F part[EPL][TB];  // sum of each segment's last run, if the next one goes on with it
     const uint64_t D = rb / W;
-    const uint64_t Ki = rg.ki, Ks = rg.kc;
     const RowGuard g = rg.g;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
-    constexpr uint32_t NWV = SABLOCK / 64;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t G = 1u << glog2, lir = tid & (G - 1), grp = tid >> glog2;
+    const uint32_t ng = TB >> glog2;
+    const uint32_t seg = CH / ng > (uint32_t)SAU ? CH / ng : (uint32_t)SAU;  // ng * seg >= CH
     FaultAcc acc;
-
-    for (uint64_t c0 = (uint64_t)blockIdx.x * SACHUNK; c0 < n; c0 += (uint64_t)gridDim.x * SACHUNK) {
-        const uint32_t cnt = (uint32_t)(n - c0 < SACHUNK ? n - c0 : SACHUNK);
-        // 1. destination keys: offset of the row inside the binding's row interval, or SA_SLOW
-        for (uint32_t k = tid; k < SACHUNK; k += SABLOCK) {
-            uint64_t key = SA_SLOW;
-            if (k < cnt) {
-                const uint64_t i = c0 + k;
-                const bool iok = !GUARD || i < Ki;
-                const int64_t iv = iok ? idx[i] : 0;
-                if (!iok) acc.note((i * D) << 2);
-                if (GUARD && g.rlo <= iv && iv <= g.rhi) key = (uint64_t)iv - (uint64_t)g.rlo;
-                if (!GUARD) key = (uint64_t)iv ^ 0x8000000000000000ull;  // order-preserving
+    for (uint64_t c0 = (uint64_t)blockIdx.x * CH; c0 < n; c0 += (uint64_t)gridDim.x * CH) {
+        const uint32_t cnt = (uint32_t)(n - c0 < CH ? n - c0 : CH);
+        // destination keys: offset of the row inside the binding's row interval, or SA_SLOW
+        uint64_t key = SA_SLOW;
+        if (tid < CH) {
+            const uint64_t i = c0 + tid;
+            if (tid < cnt) {
+                if (GUARD) {
+                    const int64_t iv = i < rg.nfast ? idx[i] : 0;
+                    if (i < rg.nfast && g.rlo <= iv && iv <= g.rhi) key = (uint64_t)iv - (uint64_t)g.rlo;
+                } else {
+                    key = (uint64_t)idx[i] ^ 0x8000000000000000ull;  // order-preserving
+                }
             }
-            skey[k] = key;
-            spos[k] = (uint16_t)k;
+            kin[tid] = key;
         }
         __syncthreads();
-        // 2. bitonic sort of (key, position), ascending; padding (position >= cnt) sorts last
-        for (uint32_t size = 2; size <= SACHUNK; size <<= 1) {
-            for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
-                for (uint32_t x = tid; x < SACHUNK / 2; x += SABLOCK) {
-                    const uint32_t a = 2 * x - (x & (stride - 1));
-                    const uint32_t b = a + stride;
-                    const bool asc = (a & size) == 0;
-                    const uint64_t ka = skey[a], kb = skey[b];
-                    const uint16_t pa = spos[a], pb = spos[b];
-                    const bool gt = ka > kb || (ka == kb && pa > pb);
-                    if (gt == asc) {
-                        skey[a] = kb;
-                        skey[b] = ka;
-                        spos[a] = pb;
-                        spos[b] = pa;
+        const uint32_t blk = tid >> 6, lane = tid & 63u;
+        uint32_t rank = 0;
+        if (tid < CH) {
+#pragma unroll 4
+            for (uint32_t j = 0; j < 64; j += 2) {
+                const ulonglong2 k2 = *reinterpret_cast<const ulonglong2*>(&kin[blk * 64 + j]);
+                rank += (k2.x < key || (k2.x == key && j < lane)) ? 1u : 0u;
+                rank += (k2.y < key || (k2.y == key && j + 1 < lane)) ? 1u : 0u;
+            }
+            if (NB > 1) kblk[blk * 64 + rank] = key;
+        }
+        if (NB > 1) {
+            __syncthreads();
+            if (tid < CH) {
+#pragma unroll 4
+                for (uint32_t o = 0; o < NB; ++o) {
+                    if (o == blk) continue;
+                    // keys of block o that come before: less, or equal in an earlier block
+                    uint32_t p = 0;
+#pragma unroll
+                    for (uint32_t step = 32; step; step >>= 1) {
+                        const uint64_t k = kblk[o * 64 + p + step - 1];
+                        p += (k < key || (k == key && o < blk)) ? step : 0u;
+                    }
+                    const uint64_t k = kblk[o * 64 + p];
+                    rank += p + ((k < key || (k == key && o < blk)) ? 1u : 0u);
+                }
+            }
+        }
+        if (tid < CH) {
+            skey[rank] = key;
+            spos[rank] = (uint16_t)tid;
+        }
+        __syncthreads();
+        const uint32_t e0 = grp * seg, e1 = e0 + seg < cnt ? e0 + seg : cnt;
+        const bool some = e0 < cnt;
+        const uint64_t k0 = some ? skey[e0] : SA_SLOW, klast = some ? skey[e1 - 1] : SA_SLOW;
+        const bool from_prev = some && e0 > 0 && skey[e0 - 1] == k0;
+        const bool to_next = some && e1 < cnt && skey[e1] == klast;
+        for (uint64_t cb = 0; cb < D; cb += (uint64_t)G * EPL) {
+            F sum[EPL], head[EPL];  // head: the end of a run that earlier segments began
+            bool ends_here = false, first = true;
+            uint64_t cur = k0;
+#pragma unroll
+            for (int q = 0; q < EPL; ++q) sum[q] = (F)-0.0;
+            for (uint32_t b = e0; b < e1; b += SAU) {
+                F v[SAU][EPL];
+#pragma unroll
+                for (int u = 0; u < SAU; ++u) {
+                    const uint32_t e = b + u;
+                    if (e < e1 && skey[e] != SA_SLOW) {
+                        const F* sp = reinterpret_cast<const F*>(src + (c0 + spos[e]) * rb) + cb + lir;
+#pragma unroll
+                        for (int q = 0; q < EPL; ++q)
+                            if (cb + lir + q * G < D) v[u][q] = sp[q * G];
                     }
                 }
-                __syncthreads();
-            }
-        }
-        // 3. pieces: runs of equal keys, cut every SAPIECE positions
-        constexpr uint32_t PER = SACHUNK / SABLOCK;
-        uint32_t flags = 0, c = 0;
 #pragma unroll
-        for (uint32_t q = 0; q < PER; ++q) {
-            const uint32_t k = tid * PER + q;
-            const bool f = k < cnt && (k == 0 || k % SAPIECE == 0 || skey[k] != skey[k - 1]);
-            flags |= (uint32_t)f << q;
-            c += f;
-        }
-        uint32_t excl;
-        const uint32_t np = block_exscan(c, excl, wsum);
+                for (int u = 0; u < SAU; ++u) {
+                    const uint32_t e = b + u;
+                    if (e >= e1) break;
+                    const uint64_t k = skey[e];
+                    if (k != cur) {
+                        if (first && from_prev) {
+                            ends_here = true;
 #pragma unroll
-        for (uint32_t q = 0; q < PER; ++q)
-            if ((flags >> q) & 1u) sstart[excl++] = (uint16_t)(tid * PER + q);
-        if (tid == 0) {
-            sstart[np] = (uint16_t)cnt;
-            snp = np;
-        }
-        __syncthreads();
-        // 4. one wave per piece: sum the piece's source rows, add once to the destination row
-        const uint32_t npieces = snp;
-        for (uint32_t p = wv; p < npieces; p += NWV) {
-            const uint32_t s = sstart[p], e = sstart[p + 1];
-            const uint64_t key = skey[s];
-            if (key != SA_SLOW) {
-                const int64_t r = GUARD ? (int64_t)(key + (uint64_t)g.rlo)
-                                        : (int64_t)(key ^ 0x8000000000000000ull);
-                uint8_t* drow = dst + (uint64_t)r * rb;
-                for (uint64_t col0 = (uint64_t)lane * EPL; col0 < D; col0 += 64u * EPL) {
-                    F sum[EPL];
-#pragma unroll
-                    for (int q = 0; q < EPL; ++q) sum[q] = (F)-0.0;
-                    for (uint32_t k = s; k < e; ++k) {
-                        const uint64_t pos = c0 + spos[k];
-                        const uint64_t es = pos * D + col0;
-                        if (!GUARD || es + EPL <= Ks) {
-                            const F* sp = reinterpret_cast<const F*>(src) + es;
-#pragma unroll
-                            for (int q = 0; q < EPL; ++q) sum[q] += sp[q];
+                            for (int q = 0; q < EPL; ++q) head[q] = sum[q];
                         } else {
-#pragma unroll
-                            for (int q = 0; q < EPL; ++q) {
-                                if (es + q < Ks) sum[q] += reinterpret_cast<const F*>(src)[es + q];
-                                else {
-                                    sum[q] += (F)0.0;
-                                    acc.note(((es + q) << 2) | 1u);
-                                }
-                            }
+                            add_sum<GUARD, W, EPL>(dst, rb, g.rlo, cur, cb + lir, G, D, sum);
                         }
+                        first = false;
+                        cur = k;
+#pragma unroll
+                        for (int q = 0; q < EPL; ++q) sum[q] = (F)-0.0;
                     }
 #pragma unroll
-                    for (int q = 0; q < EPL; ++q)
-                        unsafeAtomicAdd(reinterpret_cast<F*>(drow) + col0 + q, sum[q]);
-                }
-            } else {
-                // rows outside the destination's row interval: exact per-element checks
-                for (uint32_t k = s; k < e; ++k) {
-                    const uint64_t pos = c0 + spos[k];
-                    const bool iok = !GUARD || pos < Ki;
-                    const int64_t iv = iok ? idx[pos] : 0;
-                    uint8_t* drow = dst + (uint64_t)iv * rb;
-                    for (uint64_t col = lane; col < D; col += 64) {
-                        const uint64_t es = pos * D + col;
-                        F v = (F)0.0;
-                        if (!GUARD || es < Ks) v = reinterpret_cast<const F*>(src)[es];
-                        else acc.note((es << 2) | 1u);
-                        if (!GUARD || elem_ok(g, iv, rb, col, W))
-                            unsafeAtomicAdd(reinterpret_cast<F*>(drow + col * W), v);
-                        else
-                            acc.note((es << 2) | 2u);
-                    }
+                    for (int q = 0; q < EPL; ++q) sum[q] += v[u][q];
                 }
             }
+            if (some) {
+                if (to_next) {
+#pragma unroll
+                    for (int q = 0; q < EPL; ++q) part[q][tid] = sum[q];
+                } else if (first && from_prev) {
+                    ends_here = true;
+#pragma unroll
+                    for (int q = 0; q < EPL; ++q) head[q] = sum[q];
+                } else {
+                    add_sum<GUARD, W, EPL>(dst, rb, g.rlo, cur, cb + lir, G, D, sum);
+                }
+            }
+            __syncthreads();
+            if (ends_here) {
+                uint32_t p = grp - 1;  // the segment in which the run begins
+                while (p > 0 && skey[p * seg] == k0 && skey[p * seg - 1] == k0) --p;
+                F run[EPL];
+#pragma unroll
+                for (int q = 0; q < EPL; ++q) run[q] = (F)-0.0;
+                for (; p < grp; ++p)
+#pragma unroll
+                    for (int q = 0; q < EPL; ++q) run[q] += part[q][(p << glog2) + lir];
+#pragma unroll
+                for (int q = 0; q < EPL; ++q) run[q] += head[q];
+                add_sum<GUARD, W, EPL>(dst, rb, g.rlo, k0, cb + lir, G, D, run);
+            }
+            __syncthreads();
         }
-        __syncthreads();
+        // rows that failed the fast test sort last, before the unused slots of a last chunk
+        if (GUARD) {
+            for (uint32_t e = tid >> 6; e < cnt; e += TB / 64)
+                if (skey[e] == SA_SLOW) add_row_exact<GUARD, W>(dst, rb, idx, src, c0 + spos[e], rg, acc);
+            __syncthreads();
+        }
     }
     if (GUARD && logon) fold_faults(acc, log);
 }
@@ -209,7 +264,7 @@ constexpr int SRT_BLOCK = 256;
 constexpr uint32_t SRT_TILE = 4096;   // keys per histogram / scatter tile (16 per thread)
 constexpr uint32_t SRT_TB = 1024;      // threads of the histogram and scatter workgroups
 constexpr uint32_t SRT_SENT = 0xFFFFFFFFu;
-constexpr uint32_t RED_TILE = 256;    // sorted entries per reduce wave
+constexpr uint32_t RED_TILE = 128;    // most sorted entries per tile of the reduce
 // ctl[p] (p < 4): pass p was skipped (one digit value only); ctl[4 + p]: the buffer pass p reads
 // (ctl[4 + npasses]: the buffer holding the sorted result, which the reduce reads)
 constexpr int CTL_WORDS = 16;
@@ -217,17 +272,16 @@ constexpr int CTL_WORDS = 16;
 struct SortBufs {
     uint32_t* keys[2];
     uint32_t* vals[2];
-    uint32_t* hist;  // [256 * ntiles], scanned in place
+    uint32_t* hist;  // [257 * ntiles], scanned in place (row 256, first pass: guard-failing rows)
     uint32_t* ctl;   // [CTL_WORDS]
-    uint32_t* dstart;  // [256]: the current pass's digit totals
-    uint64_t* slow;  // [ceil(n / 64)]: bit l of word w marks row 64 w + l as failing the fast test
+    uint32_t* dstart;  // [256]: the current pass's digit totals; [256]: all guard-failing rows
 };
 
 static inline uint64_t srt_ntiles(uint64_t n) { return (n + SRT_TILE - 1) / SRT_TILE; }
 
 size_t scatter_add_scratch_bytes(uint64_t n) {
     const uint64_t a = ((n * 4 + 255) / 256) * 256;
-    return 4 * a + srt_ntiles(n) * 256 * 4 + 256 + 1024 + ((n + 63) / 64) * 8;
+    return 4 * a + srt_ntiles(n) * 257 * 4 + 256 + 1280;
 }
 
 static SortBufs sort_bufs(void* scratch, uint64_t n) {
@@ -239,9 +293,8 @@ static SortBufs sort_bufs(void* scratch, uint64_t n) {
     b.vals[0] = reinterpret_cast<uint32_t*>(p + 2 * a);
     b.vals[1] = reinterpret_cast<uint32_t*>(p + 3 * a);
     b.hist = reinterpret_cast<uint32_t*>(p + 4 * a);
-    b.ctl = reinterpret_cast<uint32_t*>(p + 4 * a + srt_ntiles(n) * 256 * 4);
-    b.dstart = reinterpret_cast<uint32_t*>(p + 4 * a + srt_ntiles(n) * 256 * 4 + 256);
-    b.slow = reinterpret_cast<uint64_t*>(p + 4 * a + srt_ntiles(n) * 256 * 4 + 256 + 1024);
+    b.ctl = reinterpret_cast<uint32_t*>(p + 4 * a + srt_ntiles(n) * 257 * 4);
+    b.dstart = reinterpret_cast<uint32_t*>(p + 4 * a + srt_ntiles(n) * 257 * 4 + 256);
     return b;
 }
 
@@ -252,25 +305,22 @@ static SortBufs sort_bufs(void* scratch, uint64_t n) {
 template <bool GUARD>
 __global__ __launch_bounds__(SRT_TB) void k_srt_keys(const int64_t* __restrict__ idx, uint64_t n,
                                                      RowsGuard rg, SortBufs b) {
-    __shared__ uint32_t h[256];
+    __shared__ uint32_t h[257];
     const uint32_t tid = threadIdx.x;
     if (blockIdx.x == 0 && tid < CTL_WORDS) b.ctl[tid] = 0;  // every pass starts from buffer 0
-    if (tid < 256) h[tid] = 0;
+    if (tid < 257) h[tid] = 0;
     __syncthreads();
     const uint64_t t0 = (uint64_t)blockIdx.x * SRT_TILE;
 #pragma unroll
     for (uint32_t r = 0; r < SRT_TILE / SRT_TB; ++r) {
-        // a wave covers 64 consecutive rows (i0 is its first), so its ballot is one bitmask word
-        const uint64_t i0 = t0 + r * SRT_TB + (tid & ~63u);
-        const uint64_t i = i0 + (tid & 63u);
-        uint32_t key = SRT_SENT;
-        bool slow = false;
+        const uint64_t i = t0 + r * SRT_TB + tid;
         if (i < n) {
+            uint32_t key = SRT_SENT;
             if (GUARD) {
                 const int64_t x = i < rg.nfast ? idx[i] : 0;
                 const bool fast = i < rg.nfast && rg.g.rlo <= x && x <= rg.g.rhi;
-                key = fast ? (uint32_t)((uint64_t)x - (uint64_t)rg.g.rlo) : SRT_SENT;
-                slow = !fast;
+                if (fast) key = (uint32_t)((uint64_t)x - (uint64_t)rg.g.rlo);
+                else atomicAdd(&h[256], 1u);
             } else {
                 key = (uint32_t)((uint64_t)idx[i] + 0x80000000ull);
             }
@@ -278,13 +328,9 @@ __global__ __launch_bounds__(SRT_TB) void k_srt_keys(const int64_t* __restrict__
             b.vals[0][i] = (uint32_t)i;
             atomicAdd(&h[key & 255u], 1u);
         }
-        if (GUARD) {
-            const uint64_t m = __ballot(slow);
-            if ((tid & 63u) == 0 && i0 < n) b.slow[i0 >> 6] = m;
-        }
     }
     __syncthreads();
-    if (tid < 256) b.hist[(uint64_t)tid * gridDim.x + blockIdx.x] = h[tid];
+    if (tid < 257) b.hist[(uint64_t)tid * gridDim.x + blockIdx.x] = h[tid];
 }
 
 // Digit histogram of one pass per tile of SRT_TILE keys, stored digit-major (hist[d * ntiles + t]).
@@ -455,20 +501,13 @@ template <int W, int EPL, bool NT = false>
 __device__ __forceinline__ RowVec<W, EPL> load_row(const uint8_t* src, uint64_t rb, uint32_t row,
                                                    uint64_t col0) {
     using F = typename FloatOf<W>::F;
+    typedef F fv __attribute__((ext_vector_type(EPL)));
     RowVec<W, EPL> r;
     const F* sp = reinterpret_cast<const F*>(src + (uint64_t)row * rb) + col0;
-    if (EPL == 4) {
-        typedef F f4 __attribute__((ext_vector_type(4)));
-        const f4* vp = reinterpret_cast<const f4*>(sp);
-        const f4 v = NT ? __builtin_nontemporal_load(vp) : *vp;
-        r.v[0] = v.x;
-        r.v[EPL > 1 ? 1 : 0] = v.y;
-        r.v[EPL > 2 ? 2 : 0] = v.z;
-        r.v[EPL > 3 ? 3 : 0] = v.w;
-    } else {
+    const fv* vp = reinterpret_cast<const fv*>(sp);
+    const fv v = NT ? __builtin_nontemporal_load(vp) : *vp;
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) r.v[q] = NT ? __builtin_nontemporal_load(sp + q) : sp[q];
-    }
+    for (int q = 0; q < EPL; ++q) r.v[q] = v[q];
     return r;
 }
 
@@ -479,171 +518,231 @@ __device__ __forceinline__ void srt_flush(uint8_t* dst, uint64_t rb, int64_t row
                                           bool owned, const RowVec<W, EPL>& old,
                                           const typename FloatOf<W>::F (&acc)[EPL]) {
     using F = typename FloatOf<W>::F;
+    typedef F fv __attribute__((ext_vector_type(EPL)));
     F* d = reinterpret_cast<F*>(dst + (uint64_t)row * rb) + col0;
     if (owned) {
-        if (EPL == 4) {
-            typedef F f4 __attribute__((ext_vector_type(4)));
-            f4 v;
-            v.x = old.v[0] + acc[0];
-            v.y = old.v[EPL > 1 ? 1 : 0] + acc[EPL > 1 ? 1 : 0];
-            v.z = old.v[EPL > 2 ? 2 : 0] + acc[EPL > 2 ? 2 : 0];
-            v.w = old.v[EPL > 3 ? 3 : 0] + acc[EPL > 3 ? 3 : 0];
-            *reinterpret_cast<f4*>(d) = v;
-        } else {
+        fv v;
 #pragma unroll
-            for (int q = 0; q < EPL; ++q) d[q] = old.v[q] + acc[q];
-        }
+        for (int q = 0; q < EPL; ++q) v[q] = old.v[q] + acc[q];
+        *reinterpret_cast<fv*>(d) = v;
     } else {
 #pragma unroll
         for (int q = 0; q < EPL; ++q) unsafeAtomicAdd(d + q, acc[q]);
     }
 }
 
-// Each wave walks RED_TILE sorted entries (their keys and positions held one per lane, read out
-// wave-uniformly) with RED_U rows in flight: the source rows of the next RED_U entries are loaded
-// together with the destination row of every run that starts among them, then the rows are
-// summed in order. A run the tile owns ends with a plain store of (destination + sum); a run
-// shared with a neighbouring tile ends with one atomic add per element.
+// A group of 2^glog2 lanes walks a tile of `tile` sorted entries with RED_U rows in flight: the source
+// rows of the next RED_U entries are loaded together with the destination row of every run that
+// starts among them, then the rows are summed in order. A run that the tile owns ends with a plain
+// store of (destination + sum). A run that spans tiles of the workgroup is put together in LDS by
+// the group in whose tile it ends, and ends there the same way; a run shared with a neighbouring
+// workgroup ends with one atomic add per element and workgroup. ROW_WAVE: rows of at least 64 chunks,
+// a wave per row, whose keys and positions are held one per lane and read out wave-uniformly.
+// Bound by the random row reads; with one atomic add per tile instead of per workgroup the atomics
+// on the hottest rows, about 100 ns each one after another, set the time instead (1 KiB rows, 2^20 of
+// them: 298 us with tiles of 256, more with shorter ones; now 265 us with 128, 270 with 64, 280 with 256).
 constexpr int RED_U = 8;
 // zero_dst: the destination rows are +0.0 before the call (the caller's promise), so the rows are
 // not read: an owned run stores (+0.0 + sum), exactly what the read-modify-write would.
-template <bool GUARD, int W, int EPL>
-__global__ __launch_bounds__(256) void k_srt_reduce(uint8_t* dst, uint64_t rb,
-                                                    const uint8_t* __restrict__ src, uint64_t n,
-                                                    SortBufs b, uint32_t npasses, int64_t rlo,
-                                                    uint32_t zero_dst) {
+template <bool GUARD, int W, int EPL, bool ROW_WAVE>
+__global__ __launch_bounds__(256, ROW_WAVE ? 4 : 3) void k_srt_reduce(uint8_t* dst, uint64_t rb,
+                                                       const uint8_t* __restrict__ src, uint64_t n,
+                                                       SortBufs b, uint32_t npasses, int64_t rlo,
+                                                       uint32_t zero_dst, uint32_t tile,
+                                                       uint32_t glog2) {
     using F = typename FloatOf<W>::F;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t wave = ((uint64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-    const uint64_t nwaves = ((uint64_t)gridDim.x * 256) >> 6;
+    __shared__ F part[EPL][256];  // sum of each tile's last run, if the next tile goes on with it
+    __shared__ uint32_t whole[32];  // the tile is one run that goes on from the previous tile
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t gl = ROW_WAVE ? 6u : glog2;
+    const uint32_t lir = tid & ((1u << gl) - 1), grp = tid >> gl, ng = 256u >> gl;
     const uint32_t buf = b.ctl[4 + npasses];
     const uint32_t* __restrict__ keys = b.keys[buf];
     const uint32_t* __restrict__ vals = b.vals[buf];
     const uint64_t D = rb / W;
     const int64_t base = GUARD ? rlo : -(int64_t)0x80000000ll;
-    const uint64_t ncb = (D + 64 * EPL - 1) / (64 * EPL);
-    for (uint64_t e0 = wave * RED_TILE; e0 < n; e0 += nwaves * RED_TILE) {
-        const uint64_t e1 = e0 + RED_TILE < n ? e0 + RED_TILE : n;
-        const uint32_t k0 = keys[e0];
-        if (k0 == SRT_SENT) continue;
-        // does the tile's first run continue a run of the previous tile, its last run the next?
-        const bool head_shared = e0 > 0 && keys[e0 - 1] == k0;
-        const uint32_t klast = keys[e1 - 1];
-        const bool tail_shared = e1 < n && klast != SRT_SENT && keys[e1] == klast;
-        // the tile's keys and positions, one per lane per group of 64 (sentinel past the tile)
-        uint32_t tk[RED_TILE / 64], tv[RED_TILE / 64];
-#pragma unroll
-        for (int j = 0; j < RED_TILE / 64; ++j) {
-            const uint64_t e = e0 + (uint64_t)j * 64 + lane;
-            tk[j] = e < e1 ? keys[e] : SRT_SENT;
-            tv[j] = e < e1 ? vals[e] : 0u;
-        }
-        for (uint64_t cb = 0; cb < ncb; ++cb) {
-            const uint64_t col0 = cb * 64 * EPL + (uint64_t)lane * EPL;
-            const bool on = col0 < D;
-            F acc[EPL];
+    const uint64_t span = (uint64_t)tile * ng;  // entries per workgroup
+    for (uint64_t b0 = (uint64_t)blockIdx.x * span; b0 < n; b0 += (uint64_t)gridDim.x * span) {
+        if (keys[b0] == SRT_SENT) break;
+        uint64_t e0 = b0 + (uint64_t)grp * tile;
+        if (ROW_WAVE) e0 = uniform_u64(e0);
+        const uint64_t e1 = e0 + tile < n ? e0 + tile : n;
+        uint32_t k0 = e0 < n ? keys[e0] : SRT_SENT;
+        if (ROW_WAVE) k0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)k0);
+        const bool some = k0 != SRT_SENT;
+        const uint32_t klast = some ? keys[e1 - 1] : SRT_SENT;
+        // does the tile's first run go on from the previous tile, its last run into the next?
+        const bool head_on = some && e0 > 0 && keys[e0 - 1] == k0;
+        const bool tail_on = some && e1 < n && klast != SRT_SENT && keys[e1] == klast;
+        const bool from_prev = head_on && grp > 0, to_next = tail_on && grp + 1 < ng;
+        if (lir == 0) whole[grp] = head_on && k0 == klast;
+        for (uint64_t cb = 0; cb < D; cb += (uint64_t)EPL << gl) {
+            const uint64_t col0 = cb + (uint64_t)lir * EPL;
+            const bool on = some && col0 < D;
+            F acc[EPL], head[EPL];  // head: the end of a run that earlier tiles began
 #pragma unroll
             for (int q = 0; q < EPL; ++q) acc[q] = (F)-0.0;
             uint32_t cur = k0;
-            bool first = true, stop = false;
+            bool first = true, ends_here = false;
             RowVec<W, EPL> dcur;
 #pragma unroll
             for (int q = 0; q < EPL; ++q) dcur.v[q] = (F)0.0;
-            if (on && !head_shared && !zero_dst)
+            if (on && !head_on && !zero_dst)
                 dcur = load_row<W, EPL>(dst + (uint64_t)(base + (int64_t)k0) * rb, rb, 0, col0);
-#pragma unroll
-            for (int j = 0; j < RED_TILE / 64; ++j) {
-                for (uint32_t l = 0; l < 64 && !stop; l += RED_U) {
+            uint32_t tk = 0, tv = 0;
+            if (ROW_WAVE ? some : on) {
+                for (uint64_t e = e0; e < e1; e += RED_U) {
                     uint32_t kk[RED_U], vv[RED_U];
                     RowVec<W, EPL> rv[RED_U], dv[RED_U];
+                    if (ROW_WAVE) {
+                        const uint32_t l = (uint32_t)(e - e0) & 63u;
+                        if (l == 0) {
+                            tk = e + lane < e1 ? keys[e + lane] : SRT_SENT;
+                            tv = e + lane < e1 ? vals[e + lane] : 0u;
+                        }
 #pragma unroll
-                    for (int u = 0; u < RED_U; ++u) {
-                        kk[u] = (uint32_t)__builtin_amdgcn_readlane((int)tk[j], (int)(l + u));
-                        vv[u] = (uint32_t)__builtin_amdgcn_readlane((int)tv[j], (int)(l + u));
+                        for (int u = 0; u < RED_U; ++u) {
+                            kk[u] = (uint32_t)__builtin_amdgcn_readlane((int)tk, (int)(l + u));
+                            vv[u] = (uint32_t)__builtin_amdgcn_readlane((int)tv, (int)(l + u));
+                        }
+                        if (kk[0] == SRT_SENT) break;
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < RED_U; ++u) {
+                            const uint64_t x = e + u < e1 ? e + u : e1 - 1;
+                            kk[u] = e + u < e1 ? keys[x] : SRT_SENT;
+                            vv[u] = vals[x];
+                        }
                     }
 #pragma unroll
                     for (int u = 0; u < RED_U; ++u) {
                         if (kk[u] != SRT_SENT && on) {
                             rv[u] = load_row<W, EPL, true>(src, rb, vv[u], col0);
-                            const uint32_t prev = u == 0 ? cur : kk[u - 1];
-                            if (kk[u] != prev) {
+                            if (kk[u] != (u == 0 ? cur : kk[u - 1])) {
                                 if (zero_dst) {
 #pragma unroll
                                     for (int q = 0; q < EPL; ++q) dv[u].v[q] = (F)0.0;
                                 } else {
-                                    dv[u] = load_row<W, EPL>(
-                                        dst + (uint64_t)(base + (int64_t)kk[u]) * rb, rb, 0, col0);
+                                    dv[u] = load_row<W, EPL>(dst + (uint64_t)(base + (int64_t)kk[u]) * rb,
+                                                             rb, 0, col0);
                                 }
                             }
                         }
                     }
 #pragma unroll
                     for (int u = 0; u < RED_U; ++u) {
-                        if (kk[u] == SRT_SENT) {
-                            stop = true;
-                            break;
-                        }
-                        if (kk[u] != cur) {
-                            if (on) srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0,
-                                                      !(first && head_shared), dcur, acc);
+                        if (kk[u] != SRT_SENT) {
+                            if (kk[u] != cur) {
+                                if (first && from_prev) {
+                                    ends_here = true;
 #pragma unroll
-                            for (int q = 0; q < EPL; ++q) acc[q] = (F)-0.0;
-                            cur = kk[u];
-                            dcur = dv[u];
-                            first = false;
-                        }
-                        if (on) {
+                                    for (int q = 0; q < EPL; ++q) head[q] = acc[q];
+                                } else if (on) {
+                                    srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0,
+                                                      !(first && head_on), dcur, acc);
+                                }
 #pragma unroll
-                            for (int q = 0; q < EPL; ++q) acc[q] += rv[u].v[q];
+                                for (int q = 0; q < EPL; ++q) acc[q] = (F)-0.0;
+                                cur = kk[u];
+                                dcur = dv[u];
+                                first = false;
+                            }
+                            if (on) {
+#pragma unroll
+                                for (int q = 0; q < EPL; ++q) acc[q] += rv[u].v[q];
+                            }
                         }
                     }
                 }
             }
-            // the last run of the tile: shared with the next tile only if it reaches the tile end
-            const bool last_shared = tail_shared && cur == klast;
-            if (on) srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0,
-                                      !((first && head_shared) || last_shared), dcur, acc);
+            // the last run: its sum goes to the next tile's group, joins an earlier tile's, or is flushed
+            const bool last_on = tail_on && cur == klast;
+            bool tail_out = false;  // the run put together here goes on in the next workgroup
+            if (on) {
+                if (last_on && to_next) {
+#pragma unroll
+                    for (int q = 0; q < EPL; ++q) part[q][tid] = acc[q];
+                } else if (first && from_prev) {
+                    ends_here = true;
+                    tail_out = last_on;
+#pragma unroll
+                    for (int q = 0; q < EPL; ++q) head[q] = acc[q];
+                } else {
+                    srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0,
+                                      !((first && head_on) || last_on), dcur, acc);
+                }
+            }
+            __syncthreads();
+            if (on && ends_here) {
+                uint32_t p = grp - 1;  // the tile in which the run begins, or the workgroup's first
+                while (p > 0 && whole[p]) --p;
+                const bool owned = !tail_out && !whole[p];  // whole[0]: an earlier workgroup's run
+                RowVec<W, EPL> old;
+#pragma unroll
+                for (int q = 0; q < EPL; ++q) old.v[q] = (F)0.0;
+                if (owned && !zero_dst)
+                    old = load_row<W, EPL>(dst + (uint64_t)(base + (int64_t)k0) * rb, rb, 0, col0);
+                F run[EPL];
+#pragma unroll
+                for (int q = 0; q < EPL; ++q) run[q] = (F)-0.0;
+                for (; p < grp; ++p)
+#pragma unroll
+                    for (int q = 0; q < EPL; ++q) run[q] += part[q][(p << gl) + lir];
+#pragma unroll
+                for (int q = 0; q < EPL; ++q) run[q] += head[q];
+                srt_flush<W, EPL>(dst, rb, base + (int64_t)k0, col0, owned, old, run);
+            }
+            __syncthreads();
         }
     }
 }
 
-// Rows that failed the fast test: every element checked exactly, atomics for the allowed ones.
+// Rows that failed the fast test: every element checked exactly, atomics for the allowed ones. They
+// sorted last (largest key), and the first scan counted them. In a kernel of their own behind the
+// reduce, whose owned rows take plain stores. All of the sorted path's denials come from these rows,
+// so the last workgroup to finish also records them.
 template <int W>
 __global__ __launch_bounds__(256) void k_srt_slow(DevTable t, DevLog* log, uint8_t* dst, uint64_t rb,
                                                   const int64_t* idx, const uint8_t* src,
                                                   uint64_t n, RowsGuard rg, SortBufs b,
-                                                  unsigned long long seq, int logon) {
-    using F = typename FloatOf<W>::F;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t wave = ((uint64_t)blockIdx.x * 256 + threadIdx.x) >> 6;
-    const uint64_t nwaves = ((uint64_t)gridDim.x * 256) >> 6;
-    const uint64_t D = rb / W;
-    const uint64_t Ki = rg.ki, Ks = rg.kc;
-    const RowGuard g = rg.g;
+                                                  uint32_t npasses, int logon) {
+    const uint32_t slow = b.dstart[256];
+    if (slow == 0) return;
+    const uint32_t* vals = b.vals[b.ctl[4 + npasses]];
     FaultAcc acc;
-    for (uint64_t r0 = wave * 64; r0 < n; r0 += nwaves * 64) {
-        uint64_t m = uniform_u64(b.slow[r0 >> 6]);
-        while (m) {
-            const uint32_t l = (uint32_t)__builtin_ctzll(m);
-            m &= m - 1;
-            const uint64_t r = r0 + l;
-            const bool iok = r < Ki;
-            if (!iok && lane == 0) acc.note((r * D) << 2);
-            const int64_t iv = iok ? idx[r] : 0;
-            uint8_t* drow = dst + (uint64_t)iv * rb;
-            for (uint64_t col = lane; col < D; col += 64) {
-                const uint64_t es = r * D + col;
-                F v = (F)0.0;
-                if (es < Ks) v = reinterpret_cast<const F*>(src)[es];
-                else acc.note((es << 2) | 1u);
-                if (elem_ok(g, iv, rb, col, W))
-                    unsafeAtomicAdd(reinterpret_cast<F*>(drow + col * W), v);
-                else
-                    acc.note((es << 2) | 2u);
-            }
-        }
-    }
+    // four rows at a time, so that fewer waves fold their denials into the log's one cache line
+    const uint64_t wave = blockIdx.x * 4u + (threadIdx.x >> 6), step = (uint64_t)gridDim.x * 16;
+    for (uint64_t e0 = n - slow + wave * 4; e0 < n; e0 += step)
+        for (uint64_t e = e0; e < n && e < e0 + 4; ++e)
+            add_row_exact<true, W>(dst, rb, idx, src, vals[e], rg, acc);
     if (logon) fold_faults(acc, log);
+}
+
+// Lanes per row: enough to cover its chunks, at most a wave.
+static uint32_t row_lanes_log2(uint64_t nch) {
+    uint32_t l = 0;
+    while (l < 6 && (1ull << l) < nch) ++l;
+    return l;
+}
+
+template <bool G, int W, int EPL>
+static void reduce_sorted(void* dst, uint64_t rb, const void* src, uint64_t n, const RowsGuard& rg,
+                          uint32_t npasses, const SortBufs& b, const DevInfo& d, hipStream_t s,
+                          bool zero_dst) {
+    // at least 8 lanes a group: at most 32 tiles of a workgroup are put together one after another
+    const uint32_t rl = row_lanes_log2((rb / W + EPL - 1) / EPL), gl = rl < 3 ? 3 : rl;
+    // short tiles until four waves for every SIMD of the chip remain, then longer ones
+    uint32_t tile = gl == 6 ? 64 : 32;
+    while (tile < RED_TILE && (n >> (6 - gl)) / (2 * tile) >= (uint64_t)d.num_cu * 16) tile *= 2;
+    const uint64_t span = (uint64_t)tile * (256 >> gl);
+    const uint64_t blocks = (n + span - 1) / span, cap = 1ull << 22;
+    const dim3 grid((uint32_t)(blocks < cap ? blocks : cap)), block(256);
+    if (gl == 6)
+        hipLaunchKernelGGL((k_srt_reduce<G, W, EPL, true>), grid, block, 0, s, (uint8_t*)dst, rb,
+                           (const uint8_t*)src, n, b, npasses, rg.g.rlo, (uint32_t)zero_dst, tile, gl);
+    else
+        hipLaunchKernelGGL((k_srt_reduce<G, W, EPL, false>), grid, block, 0, s, (uint8_t*)dst, rb,
+                           (const uint8_t*)src, n, b, npasses, rg.g.rlo, (uint32_t)zero_dst, tile, gl);
 }
 
 template <bool G, int W>
@@ -658,42 +757,45 @@ static void scatter_add_sorted(const DevTable& t, DevLog* log, void* dst, uint64
     hipLaunchKernelGGL((k_srt_keys<G>), dim3(ntiles), dim3(SRT_TB), 0, s, idx, n, rg, b);
     for (uint32_t p = 0; p < npasses; ++p) {
         if (p > 0) hipLaunchKernelGGL(k_srt_hist, dim3(ntiles), dim3(SRT_TB), 0, s, b, n, p);
-        hipLaunchKernelGGL(k_srt_scan_rows, dim3(256), dim3(SRT_BLOCK), 0, s, b, ntiles);
+        hipLaunchKernelGGL(k_srt_scan_rows, dim3(p == 0 ? 257 : 256), dim3(SRT_BLOCK), 0, s, b, ntiles);
         hipLaunchKernelGGL(k_srt_scatter, dim3(ntiles), dim3(SRT_TB), 0, s, b, n, p);
     }
-    const uint64_t waves = (n + RED_TILE - 1) / RED_TILE;
-    const uint64_t rg_blocks = (waves + 3) / 4;
-    const uint32_t rgrid = (uint32_t)(rg_blocks < (uint64_t)d.num_cu * 8 ? rg_blocks : (uint64_t)d.num_cu * 8);
-    const bool v4 = W == 4 && (rb / W) % 4 == 0 && (((uint64_t)src | (uint64_t)dst | rb) & 15) == 0;
-    if (v4)
-        hipLaunchKernelGGL((k_srt_reduce<G, W, 4>), dim3(rgrid), dim3(256), 0, s, (uint8_t*)dst, rb,
-                           (const uint8_t*)src, n, b, npasses, rg.g.rlo, (uint32_t)zero_dst);
+    if ((((uint64_t)src | (uint64_t)dst | rb) & 15) == 0)
+        reduce_sorted<G, W, 16 / W>(dst, rb, src, n, rg, npasses, b, d, s, zero_dst);
     else
-        hipLaunchKernelGGL((k_srt_reduce<G, W, 1>), dim3(rgrid), dim3(256), 0, s, (uint8_t*)dst, rb,
-                           (const uint8_t*)src, n, b, npasses, rg.g.rlo, (uint32_t)zero_dst);
+        reduce_sorted<G, W, 1>(dst, rb, src, n, rg, npasses, b, d, s, zero_dst);
     if (G) {
-        const uint64_t sw = (n + 63) / 64;
-        const uint64_t sb = (sw + 3) / 4;
-        const uint32_t sgrid = (uint32_t)(sb < (uint64_t)d.num_cu * 4 ? sb : (uint64_t)d.num_cu * 4);
-        hipLaunchKernelGGL((k_srt_slow<W>), dim3(sgrid), dim3(256), 0, s, t, log, (uint8_t*)dst, rb,
-                           idx, (const uint8_t*)src, n, rg, b, seq, logon);
+        const uint64_t sb = (n + 255) / 256, cap = (uint64_t)d.num_cu * 4;
+        hipLaunchKernelGGL((k_srt_slow<W>), dim3((uint32_t)(sb < cap ? sb : cap)), dim3(256), 0, s, t, log,
+                           (uint8_t*)dst, rb, idx, (const uint8_t*)src, n, rg, b, npasses, logon);
     }
+}
+
+template <bool G, int W, int EPL, int CH, int TB>
+static void launch_chunks(dim3 grid, const DevTable& t, DevLog* log, void* dst, uint64_t rb,
+                          const int64_t* idx, const void* src, uint64_t n, const RowsGuard& rg,
+                          int logon, uint32_t gl, hipStream_t s) {
+    hipLaunchKernelGGL((k_scatter_add<G, W, EPL, CH, TB>), grid, dim3(TB), 0, s, t, log, (uint8_t*)dst, rb,
+                       idx, (const uint8_t*)src, n, rg, logon, gl);
 }
 
 template <bool G, int W>
 static void scatter_add_w(const DevTable& t, DevLog* log, void* dst, uint64_t rb,
                           const int64_t* idx, const void* src, uint64_t n, const RowsGuard& rg,
                           unsigned long long seq, int logon, const DevInfo& d, hipStream_t s) {
-    uint64_t grid = (n + SACHUNK - 1) / SACHUNK;
-    const uint64_t cap = (uint64_t)d.num_cu * 4;
-    if (grid > cap) grid = cap;
-    const bool v4 = W == 4 && (rb / W) % 4 == 0 && ((uint64_t)src & 15) == 0;
-    if (v4)
-        hipLaunchKernelGGL((k_scatter_add<G, W, 4>), dim3((uint32_t)grid), dim3(SABLOCK), 0, s, t, log,
-                           (uint8_t*)dst, rb, idx, (const uint8_t*)src, n, rg, seq, logon);
-    else
-        hipLaunchKernelGGL((k_scatter_add<G, W, 1>), dim3((uint32_t)grid), dim3(SABLOCK), 0, s, t, log,
-                           (uint8_t*)dst, rb, idx, (const uint8_t*)src, n, rg, seq, logon);
+    constexpr int EPL = W == 4 ? 4 : 2;
+    const uint32_t gl = row_lanes_log2((rb / W + EPL - 1) / EPL);
+    uint64_t ch = 64;
+    while (ch < 1024 && n > SA_CHUNKS * ch) ch *= 2;
+    const uint64_t chunks = (n + ch - 1) / ch, cap = (uint64_t)d.num_cu * 8;
+    const dim3 grid((uint32_t)(chunks < cap ? chunks : cap));
+    switch (ch) {
+        case 64: return launch_chunks<G, W, EPL, 64, 256>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
+        case 128: return launch_chunks<G, W, EPL, 128, 256>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
+        case 256: return launch_chunks<G, W, EPL, 256, 1024>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
+        case 512: return launch_chunks<G, W, EPL, 512, 1024>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
+        default: return launch_chunks<G, W, EPL, 1024, 1024>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
+    }
 }
 
 hipError_t launch_scatter_add(bool guard, const DevTable& t, DevLog* log, const Bind* binds,
@@ -708,7 +810,7 @@ hipError_t launch_scatter_add(bool guard, const DevTable& t, DevLog* log, const 
     // sorted path: 32-bit keys (guarded: the destination's row interval minus the sentinel;
     // unguarded: idx + 2^31), positions below 2^32
     uint32_t npasses = 0;
-    bool sorted = scratch != nullptr && n >= SORT_MIN_N && n < (1ull << 32);
+    bool sorted = scratch != nullptr && scatter_add_sorts(n, rb) && n < (1ull << 32);
     if (sorted && guard) {
         if (!rg.g.bound || rg.g.rhi < rg.g.rlo) {
             npasses = 1;  // no fast rows: every key is the sentinel, the sort is trivial

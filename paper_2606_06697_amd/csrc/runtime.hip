@@ -884,7 +884,7 @@ static int scatter_impl(agile_rt* rt, void* d_dst, uint64_t row_bytes, const int
     DeviceGuard dg(rt->device);
     if (!dg.ok) return AGILE_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool sort = accumulate && n >= SORT_MIN_N;
+    const bool sort = accumulate && scatter_add_sorts(n, row_bytes);
     void* fixed = nullptr;
     if (noalloc && sort) {
         if (scatter_add_scratch_bytes(n) > AGILE_NOALLOC_SCRATCH_BYTES) return AGILE_E2BIG;
@@ -1206,7 +1206,7 @@ int agile_unguarded_scatter(void* d_dst, uint64_t row_bytes, const int64_t* d_id
     if (rc != AGILE_OK) return rc;
     if (n && (!d_dst || !d_src || !d_idx)) return AGILE_EINVAL;
     void* scr = nullptr;
-    if (accumulate && n >= SORT_MIN_N) {
+    if (accumulate && scatter_add_sorts(n, row_bytes)) {
         // one scratch buffer per device for the unguarded twin, kept until the process ends
         static std::mutex mu;
         static std::vector<StreamScratch> per_dev;

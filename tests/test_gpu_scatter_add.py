@@ -10,6 +10,7 @@ takes the sorted path), destinations of exactly 2^8 and 2^16 rows (the last row'
 sorted bit set, as the hostile rows' key has), and the unguarded twin on valid indices.
 """
 import random
+import sys
 
 import numpy as np
 import pytest
@@ -217,4 +218,66 @@ def test_sorted_scatter_add_suppress_only_leaves_log_empty():
                   ar.addr(off["src"][0]), n, w, True)
     ar.check("sorted scatter-add, logged after suppress only")
     log_matches(tw, ol, "sorted scatter-add, logged after suppress only")
+    tw.close()
+
+
+def _pattern(rng, kind, n, rows):
+    """Indices that make runs of one row as long as the call, of a few rows, and of a Zipf-like mix
+    with hostile values."""
+    if kind == "one":
+        return np.full(n, rows - 1, dtype=np.int64)
+    if kind == "few":
+        return rng.choice(np.array([0, 1, rows // 2, rows - 1]), n).astype(np.int64)
+    v = np.minimum(rng.geometric(0.02, n), rows) - 1
+    bad = np.array([rows, rows + 3, -1, 1 << 40, -(1 << 62)], dtype=np.int64)
+    u = rng.random(n)
+    v[u < 0.05] = bad[rng.integers(0, bad.size, int((u < 0.05).sum()))]
+    return v.astype(np.int64)
+
+
+def _add_and_compare(ar, tw, off, w, rb, idx, accumulate, what):
+    n = idx.size
+    ar.write(off["idx"][0], idx)
+    ol = G.FaultLog()
+    a = [ar.addr(off[k][0]) for k in ("dst", "idx", "src")]
+    tw.g.agile_guarded_scatter(tw.h, a[0], rb, a[1], a[2], n, 0 if w == 4 else 1, accumulate)
+    G.scatter_vec(tw.ot, ar.mem, ol, tw.next_seq(), a[0], rb, a[1], a[2], n, w, True)
+    ar.check(what)
+    log_matches(tw, ol, what)
+
+
+@pytest.mark.parametrize("w,D", [(4, 1), (4, 3), (4, 5), (4, 64), (4, 257), (8, 1), (8, 3), (8, 130)])
+def test_scatter_add_chunks(w, D):
+    """The chunk path: calls of part of a chunk and around the row counts (32 chunks) from which chunks
+    of 128, 256, 512 and 1,024 rows are taken, with runs of one row inside a segment, over several segments of a chunk and over
+    every chunk. Integer values: every sum is exact in any order."""
+    ar, tw, off = setup(w, D, 700 + D + w)
+    rng = np.random.default_rng(700 + D + w)
+    for n in (1, 63, 64, 65, 2048, 2049, 4097, 8193, 16385, 32000):
+        for kind in ("one", "few", "mix") if n in (65, 2049, 8193, 16385) else ("mix",):
+            _add_and_compare(ar, tw, off, w, w * D, _pattern(rng, kind, n, DST_ROWS), 1,
+                             f"chunks w={w} D={D} n={n} {kind}")
+    tw.close()
+
+
+@pytest.mark.parametrize("w,D,rows,n", [(4, 4, 256, 262145), (4, 1, 65536, 262145),
+                                        (4, 20, 3000, 270000), (4, 64, 3000, 262145),
+                                        (4, 65, 3000, 262145), (4, 256, 3000, 98305),
+                                        (8, 2, 256, 262145), (8, 33, 3000, 262145),
+                                        (8, 130, 3000, 98304)])
+def test_sorted_scatter_add_runs(w, D, rows, n, monkeypatch):
+    """The sorted path (more than 2^18 rows, or 96 MiB of them) over every width of a lane group:
+    runs that span tiles of a workgroup and workgroups (each put together once), tables of 2^8 and
+    2^16 rows, hostile rows behind them, added to and into zeros. Integer values: every sum is
+    exact in any order."""
+    monkeypatch.setattr(sys.modules[__name__], "NMAX", n)
+    ar, tw, off = setup(w, D, 800 + D + w, rows=rows)
+    rng = np.random.default_rng(800 + D + w)
+    dt = np.float32 if w == 4 else np.float64
+    for kind, accumulate in (("one", 1), ("mix", 1), ("few", tw.g.SCATTER_ADD_INTO_ZEROS),
+                             ("mix", tw.g.SCATTER_ADD_INTO_ZEROS)):
+        if accumulate == tw.g.SCATTER_ADD_INTO_ZEROS:
+            ar.write(off["dst"][0], np.zeros(rows * D, dtype=dt))
+        _add_and_compare(ar, tw, off, w, w * D, _pattern(rng, kind, n, rows), accumulate,
+                         f"sorted w={w} D={D} n={n} {kind} accumulate={accumulate}")
     tw.close()
