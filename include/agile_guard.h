@@ -23,8 +23,8 @@
  *    stream; the library never frees caller memory.
  *  - Streams: `stream` is a hipStream_t (NULL = the legacy default stream). Device work is
  *    queued asynchronously on it. Table mutations take effect for work queued after them
- *    (the device image is refreshed lazily, in stream order, by the next launch; the handle
- *    keeps two images, so a change does not wait for launches, on any stream, that still
+ *    (the device image is refreshed lazily, in stream order, by the next launch that reads it;
+ *    the handle keeps two images, so a change does not wait for launches, on any stream, that still
  *    read the previous table).
  *  - Threading: one handle must not be used from two host threads at once, and guarded
  *    calls on one handle that run concurrently on different streams race on its fault
@@ -213,7 +213,7 @@ int agile_rt_clear(agile_rt* rt);
 /* Number of live ranges. */
 int agile_rt_count(const agile_rt* rt, uint32_t* out_n);
 
-/* Upload pending table changes now on `stream` (optional: every launch does it lazily). */
+/* Upload pending table changes now on `stream` (optional: a launch that reads the image does it lazily). */
 int agile_rt_sync(agile_rt* rt, void* stream);
 
 /* ---- batched API-time pointer validation (Section IV-E, V-C) ----------------------- */

@@ -6,13 +6,14 @@ namespace agile {
 
 struct DeviceGuard {
     int prev = -1;
-    bool ok = false;
+    bool ok = false, changed = false;
     explicit DeviceGuard(int dev) {
         if (hipGetDevice(&prev) != hipSuccess) return;
-        ok = prev == dev || hipSetDevice(dev) == hipSuccess;
+        changed = prev != dev;
+        ok = !changed || hipSetDevice(dev) == hipSuccess;
     }
     ~DeviceGuard() {
-        if (prev >= 0) (void)hipSetDevice(prev);
+        if (changed) (void)hipSetDevice(prev);
     }
     DeviceGuard(const DeviceGuard&) = delete;
     DeviceGuard& operator=(const DeviceGuard&) = delete;

@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "guard_arith.h"
 
 namespace agile {
@@ -82,9 +84,24 @@ struct DevLog {
     uint32_t first_verdict;
     int32_t first_owner;
     uint32_t reserved;
-    // scratch of one guarded launch, returned to its idle state by the launch's finishing kernel
+    // scratch of one guarded launch, returned to its idle state by the launch's finishing step
     unsigned long long s_minkey;   // min over (elem << 2 | operand) of this launch's denials
     unsigned long long s_count;    // denials of this launch
+    // workgroups of the launch that are done, counted in TICKETS places a memory channel apart (one
+    // place takes about 20 ns a workgroup, one after another), and the places that are full
+    uint32_t pad[12];
+    uint32_t ticket[(32 + 1) * 64];
+};
+constexpr uint32_t TICKETS = 32, TICKET_STRIDE = 64;
+
+// A table of at most INLINE_RANGES ranges in a launch's own arguments (entries in address order), for
+// the reason of its first denial.
+constexpr uint32_t INLINE_RANGES = 64;
+struct InlineTab {
+    uint32_t n;
+    uint32_t pad;
+    uint64_t base[INLINE_RANGES], end[INLINE_RANGES];
+    uint32_t meta[INLINE_RANGES];  // id << 2 | kind
 };
 
 // Classification of `a` inside bucket b (split64[b] <= a is known): verdict + owner for a
@@ -212,16 +229,6 @@ __device__ inline void fold_faults(FaultAcc acc, DevLog* log) {
     }
 }
 
-__device__ inline void record_at(const DevTable& t, DevLog* log, unsigned long long seq,
-                                 unsigned long long elem, uint32_t operand, __int128 A, uint32_t w,
-                                 uint32_t op) {
-    uint32_t v = V_UNMAPPED;
-    int32_t o = -1;
-    const bool in_space = A >= 0 && A <= (__int128)U64MAX;
-    if (in_space) reason_lane(t, (uint64_t)A, w, v, o);
-    log_record(log, seq, elem, operand, (uint64_t)A, w, op, v, o);
-}
-
 // Where the denials of a row kernel (gather, scatter, scatter-add) live: a key's element e is
 // row i = e / D, column e % D; operand 0 is the index load at idx + 8 i, the contiguous operand is
 // at cont + e * w and the row-addressed one at rowp + idx[i] * rb + column * w.
@@ -233,5 +240,108 @@ struct FaultSite {
     uint64_t D, rb, ki;    // elements per row, row bytes, readable index prefix
     uint64_t idx, cont, rowp;
 };
+
+// What a launch of a row kernel needs to record its denials itself (fused != 0); otherwise a kernel
+// after it does.
+struct FinishArgs {
+    InlineTab tab;
+    FaultSite site;
+    unsigned long long seq;
+    uint32_t fused;
+    uint32_t pad;
+};
+struct NoFinish {};  // the unguarded twins' place for it
+template <bool GUARD>
+using FinishOf = std::conditional_t<GUARD, FinishArgs, NoFinish>;
+
+struct InlineLook {
+    const InlineTab& t;
+    // one range per lane of a wave
+    __device__ __forceinline__ void operator()(uint64_t a, uint32_t w, uint32_t& v, int32_t& owner) const {
+        static_assert(INLINE_RANGES == 64, "one range per lane");
+        const uint32_t lane = threadIdx.x & 63u;
+        const bool in = lane < t.n;
+        const uint64_t base = in ? t.base[lane] : 0, end = in ? t.end[lane] : 0;
+        const uint64_t m = __ballot(in && base <= a && a < end);
+        v = V_UNMAPPED;
+        owner = -1;
+        if (!m) return;
+        const uint32_t meta = __shfl(in ? t.meta[lane] : 0u, __builtin_ctzll(m), 64);
+        const uint64_t room = __shfl(end, __builtin_ctzll(m), 64) - a;
+        owner = (int32_t)(meta >> 2);
+        v = (meta & 3u) != KIND_USER ? V_PROTECTED : (w <= room ? V_CROSS_ALLOC : V_STRADDLE);
+    }
+};
+struct ImageLook {
+    const DevTable& t;
+    __device__ __forceinline__ void operator()(uint64_t a, uint32_t w, uint32_t& v, int32_t& owner) const {
+        reason_lane(t, a, w, v, owner);
+    }
+};
+
+// Finishing step of a row kernel's launch (one wave): adds the launch's denial count to the log and,
+// if the log holds no record yet, records the smallest key (its address and reason).
+template <class Look>
+__device__ inline void finish_faults(const Look& look, DevLog* log, const FaultSite& f,
+                                     unsigned long long seq) {
+    // the launch's waves folded into these from every XCD
+    const unsigned long long total =
+        __hip_atomic_load(&log->s_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (total == 0) return;
+    const unsigned long long key =
+        __hip_atomic_load(&log->s_minkey, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long elem = key >> 2;
+    const uint32_t operand = (uint32_t)(key & 3u);
+    const uint64_t i = elem / f.D, col = elem % f.D;
+    const int64_t* idx = reinterpret_cast<const int64_t*>(f.idx);
+    __int128 A;
+    uint32_t w = f.w;
+    if (operand == 0) {
+        A = (__int128)f.idx + (__int128)(8 * i);
+        w = 8;
+    } else if (operand == f.row_operand) {
+        const int64_t v = i < f.ki ? idx[i] : 0;
+        A = (__int128)f.rowp + (__int128)v * (__int128)f.rb + (__int128)(col * f.w);
+    } else {
+        A = (__int128)f.cont + (__int128)elem * f.w;
+    }
+    uint32_t v = V_UNMAPPED;
+    int32_t o = -1;
+    if (A >= 0 && A <= (__int128)U64MAX) look((uint64_t)A, w, v, o);
+    if ((threadIdx.x & 63u) == 0) {
+        atomicAdd(&log->count, total);
+        log_record(log, seq, elem, operand, (uint64_t)A, w, f.op, v, o);
+        atomicExch(&log->s_count, 0ull);
+        atomicExch(&log->s_minkey, ~0ull);
+    }
+}
+
+// End of a guarded row kernel, called by every thread of every workgroup of the launch: folds the
+// denials, and in a fused launch the last workgroup to get here finishes them.
+__device__ inline void end_faults(const FaultAcc& acc, DevLog* log, const FinishArgs& fin) {
+    fold_faults(acc, log);
+    if (!fin.fused) return;
+    __shared__ uint32_t s_last;
+    // every wave waits for its own atomics, then the workgroup is counted
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t last = 1;
+        const uint32_t nb = gridDim.x;
+        if (nb > 1) {
+            const uint32_t s = blockIdx.x % TICKETS, full = (nb - s + TICKETS - 1) / TICKETS;
+            uint32_t* mine = log->ticket + s * TICKET_STRIDE;
+            uint32_t* top = log->ticket + TICKETS * TICKET_STRIDE;
+            const uint32_t places = nb < TICKETS ? nb : TICKETS;
+            // atomicInc goes back to 0 after its bound: the counts are ready for the next launch
+            last = atomicInc(mine, full - 1) == full - 1;
+            if (last) last = atomicInc(top, places - 1) == places - 1;
+        }
+        s_last = last;
+    }
+    __syncthreads();
+    if (s_last && threadIdx.x < 64) finish_faults(InlineLook{fin.tab}, log, fin.site, fin.seq);
+}
+__device__ inline void end_faults(const FaultAcc&, DevLog*, const NoFinish&) {}
 
 }  // namespace agile

@@ -8,7 +8,7 @@
 // two signed compares of the loaded index against scalars. Rows outside it (hostile indices, or a table pointer that is not
 // row-aligned with its allocation's ends) take an exact 128-bit per-element path. Denials are
 // counted per lane, reduced per wave and folded into the handle's log (count and smallest
-// (element, operand) key); a one-thread kernel after the launch writes that denial's record.
+// (element, operand) key); the last workgroup, or a kernel after the launch, writes that denial's record.
 // GUARD=false compiles the same loops with no binding and no compare (the unguarded twin).
 #include "launch.h"
 
@@ -70,11 +70,10 @@ __device__ __forceinline__ void load_rows(const RowLanes& L, uint64_t r0, uint64
 }
 
 template <bool GUARD, int CW, int W, int R, bool WIDE>
-__global__ __launch_bounds__(GBLOCK) void k_gather(DevTable t, DevLog* log, uint8_t* out,
-                                                    const uint8_t* T, uint64_t rb,
-                                                    const int64_t* idx, uint64_t n, RowsGuard rg,
-                                                    unsigned long long seq, int logon,
-                                                    uint32_t glog2) {
+__global__ __launch_bounds__(GBLOCK) void k_gather(DevLog* log, uint8_t* out, const uint8_t* T,
+                                                    uint64_t rb, const int64_t* idx, uint64_t n,
+                                                    RowsGuard rg, int logon, uint32_t glog2,
+                                                    FinishOf<GUARD> fin) {
     using V = typename Word<CW>::T;
     using E = typename Word<W>::T;
     constexpr uint32_t EPC = CW / W;  // elements per chunk
@@ -132,16 +131,15 @@ __global__ __launch_bounds__(GBLOCK) void k_gather(DevTable t, DevLog* log, uint
             }
         }
     }
-    if (GUARD && logon) fold_faults(acc, log);
+    if (GUARD && logon) end_faults(acc, log, fin);
 }
 
 // Plain scatter (no accumulation): with duplicate indices one of the writers wins.
 template <bool GUARD, int CW, int W, int R, bool WIDE>
-__global__ __launch_bounds__(GBLOCK) void k_scatter(DevTable t, DevLog* log, uint8_t* dst,
-                                                     uint64_t rb, const int64_t* idx,
-                                                     const uint8_t* src, uint64_t n, RowsGuard rg,
-                                                     unsigned long long seq, int logon,
-                                                     uint32_t glog2) {
+__global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, uint64_t rb,
+                                                     const int64_t* idx, const uint8_t* src,
+                                                     uint64_t n, RowsGuard rg, int logon,
+                                                     uint32_t glog2, FinishOf<GUARD> fin) {
     using V = typename Word<CW>::T;
     using E = typename Word<W>::T;
     constexpr uint32_t EPC = CW / W;
@@ -199,7 +197,7 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevTable t, DevLog* log, uin
             }
         }
     }
-    if (GUARD && logon) fold_faults(acc, log);
+    if (GUARD && logon) end_faults(acc, log, fin);
 }
 
 __global__ void k_log_reset(DevLog* log) {
@@ -215,6 +213,7 @@ __global__ void k_log_reset(DevLog* log) {
     log->reserved = 0;
     log->s_minkey = ~0ull;
     log->s_count = 0;
+    for (uint32_t k = 0; k <= TICKETS; ++k) log->ticket[k * TICKET_STRIDE] = 0;
 }
 
 hipError_t launch_log_reset(DevLog* log, hipStream_t s) {
@@ -222,38 +221,36 @@ hipError_t launch_log_reset(DevLog* log, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Finishing step of a row kernel's launch: adds the launch's denial count to the log and, if
-// the log holds no record yet, records the smallest key (its address and reason).
+// The finishing step as a kernel of its own (one wave), for launches that are not fused.
 __global__ void k_fault_finish(DevTable t, DevLog* log, FaultSite f, unsigned long long seq) {
-    // device-scope atomics: the launch's waves folded into these from every XCD
-    const unsigned long long total = atomicAdd(&log->s_count, 0ull);
-    if (total == 0) return;
-    const unsigned long long key = atomicMin(&log->s_minkey, ~0ull);
-    atomicAdd(&log->count, total);
-    const unsigned long long elem = key >> 2;
-    const uint32_t operand = (uint32_t)(key & 3u);
-    const uint64_t i = elem / f.D, col = elem % f.D;
-    const int64_t* idx = reinterpret_cast<const int64_t*>(f.idx);
-    __int128 A;
-    uint32_t w = f.w;
-    if (operand == 0) {
-        A = (__int128)f.idx + (__int128)(8 * i);
-        w = 8;
-    } else if (operand == f.row_operand) {
-        const int64_t v = i < f.ki ? idx[i] : 0;
-        A = (__int128)f.rowp + (__int128)v * (__int128)f.rb + (__int128)(col * f.w);
-    } else {
-        A = (__int128)f.cont + (__int128)elem * f.w;
-    }
-    record_at(t, log, seq, elem, operand, A, w, f.op);
-    atomicExch(&log->s_count, 0ull);
-    atomicExch(&log->s_minkey, ~0ull);
+    finish_faults(ImageLook{t}, log, f, seq);
+}
+__global__ void k_fault_finish_inline(InlineTab t, DevLog* log, FaultSite f, unsigned long long seq) {
+    finish_faults(InlineLook{t}, log, f, seq);
 }
 
-hipError_t launch_fault_finish(const DevTable& t, DevLog* log, const FaultSite& f,
+hipError_t launch_fault_finish(const GuardTab& t, DevLog* log, const FaultSite& f,
                                unsigned long long seq, hipStream_t s) {
-    hipLaunchKernelGGL(k_fault_finish, dim3(1), dim3(1), 0, s, t, log, f, seq);
+    if (t.inl) hipLaunchKernelGGL(k_fault_finish_inline, dim3(1), dim3(64), 0, s, *t.inl, log, f, seq);
+    else hipLaunchKernelGGL(k_fault_finish, dim3(1), dim3(64), 0, s, *t.dev, log, f, seq);
     return hipGetLastError();
+}
+
+// The workgroups count themselves up to this grid: 64 rows of 4 bytes 7.9 us a call against 10.9 with a
+// finishing kernel, 2^21 rows (1,024 workgroups) 33.9 / 34.5, 2^23 (4,096) 126 / 127 without denials and
+// 161 / 157 with 0.1%, 2^25 (16,384) 517 / 509.
+constexpr uint64_t FUSE_GRID = 2048;
+
+FinishArgs finish_args(const GuardTab& t, const FaultSite& f, unsigned long long seq, uint64_t grid,
+                       bool wanted) {
+    FinishArgs a;
+    a.fused = wanted && t.inl && grid <= FUSE_GRID;
+    a.seq = seq;
+    if (a.fused) {
+        a.tab = *t.inl;
+        a.site = f;
+    }
+    return a;
 }
 
 FaultSite rows_fault_site(uint32_t op, uint32_t w, uint32_t row_operand, uint64_t rb, uint64_t ki,
@@ -295,88 +292,94 @@ static uint32_t rows_grid(uint64_t n, uint32_t glog2, int R, const DevInfo& d,
     return (uint32_t)(want < cap ? want : cap);
 }
 
-template <bool G, int CW, int W>
-static void gather_cw(const DevTable& t, DevLog* log, void* out, const void* tab, uint64_t rb,
-                      const int64_t* idx, uint64_t n, const RowsGuard& rg, unsigned long long seq,
-                      int logon, const DevInfo& d, hipStream_t s) {
-    const uint32_t gl = lanes_log2(rb / CW);
-    const dim3 block(GBLOCK);
-    if (gl == 6)
-        hipLaunchKernelGGL((k_gather<G, CW, W, R_ROWWAVE, true>), dim3(rows_grid(n, gl, R_ROWWAVE, d)),
-                           block, 0, s, t, log, (uint8_t*)out, (const uint8_t*)tab, rb, idx, n, rg, seq,
-                           logon, gl);
-    else if (rb <= 16)
-        hipLaunchKernelGGL((k_gather<G, CW, W, R_NARROW, false>), dim3(rows_grid(n, gl, R_NARROW, d, true)),
-                           block, 0, s, t, log, (uint8_t*)out, (const uint8_t*)tab, rb, idx, n, rg, seq,
-                           logon, gl);
-    else
-        hipLaunchKernelGGL((k_gather<G, CW, W, R_WIDE, false>), dim3(rows_grid(n, gl, R_WIDE, d)),
-                           block, 0, s, t, log, (uint8_t*)out, (const uint8_t*)tab, rb, idx, n, rg, seq,
-                           logon, gl);
-}
+struct RowCall {  // a row kernel's launch, and what its denials need
+    GuardTab t;
+    DevLog* log;
+    uint64_t rb;
+    const int64_t* idx;
+    uint64_t n;
+    RowsGuard rg;
+    FaultSite site;
+    unsigned long long seq;
+    int logon;
+    bool finish;
+    DevInfo d;
+    hipStream_t s;
+};
 
-template <bool G, int W>
-static void gather_w(const DevTable& t, DevLog* log, void* out, const void* tab, uint64_t rb,
-                     const int64_t* idx, uint64_t n, const RowsGuard& rg, unsigned long long seq,
-                     int logon, const DevInfo& d, hipStream_t s) {
-    if (rb % 16 == 0 && (((uint64_t)out | (uint64_t)tab) & 15) == 0)
-        gather_cw<G, 16, W>(t, log, out, tab, rb, idx, n, rg, seq, logon, d, s);
-    else
-        gather_cw<G, W, W>(t, log, out, tab, rb, idx, n, rg, seq, logon, d, s);
-}
-
-hipError_t launch_gather(bool guard, const DevTable& t, DevLog* log, const Bind* binds, void* out,
-                         const void* tab, uint64_t rb, const int64_t* idx, uint64_t n, uint32_t w,
-                         unsigned long long seq, int logon, const DevInfo& d, hipStream_t s,
-                         bool finish) {
-    if (n == 0) return hipSuccess;
-    if (guard) {
-        const RowsGuard rg = rows_guard(binds[0], binds[2], binds[1], (uint64_t)idx, (uint64_t)out,
-                                        (uint64_t)tab, n, rb, w);
-        if (w == 4) gather_w<true, 4>(t, log, out, tab, rb, idx, n, rg, seq, logon, d, s);
-        else gather_w<true, 8>(t, log, out, tab, rb, idx, n, rg, seq, logon, d, s);
-        if (logon && finish)
-            return launch_fault_finish(t, log, rows_fault_site(3 /*OP_GATHER*/, w, 1, rb, rg.ki, idx,
-                                                                 out, tab), seq, s);
+// Launches the kernel, and the finishing kernel behind it where that is wanted and not fused.
+template <bool G, class K, class L>
+static hipError_t row_launch(const RowCall& c, K kernel, uint32_t grid, const L& launch) {
+    const bool wanted = G && c.logon && c.finish;
+    if constexpr (G) {
+        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted);
+        launch(kernel, grid, fin);
+        if (wanted && !fin.fused) return launch_fault_finish(c.t, c.log, c.site, c.seq, c.s);
     } else {
-        const RowsGuard rg = rows_open(n, rb, w);
-        if (w == 4) gather_w<false, 4>(t, log, out, tab, rb, idx, n, rg, seq, logon, d, s);
-        else gather_w<false, 8>(t, log, out, tab, rb, idx, n, rg, seq, logon, d, s);
+        launch(kernel, grid, NoFinish{});
     }
     return hipGetLastError();
 }
 
 template <bool G, int CW, int W>
-static void scatter_cw(const DevTable& t, DevLog* log, void* dst, uint64_t rb, const int64_t* idx,
-                       const void* src, uint64_t n, const RowsGuard& rg, unsigned long long seq,
-                       int logon, const DevInfo& d, hipStream_t s) {
-    const uint32_t gl = lanes_log2(rb / CW);
-    const dim3 block(GBLOCK);
+static hipError_t gather_cw(const RowCall& c, void* out, const void* tab) {
+    const uint32_t gl = lanes_log2(c.rb / CW);
+    const auto launch = [&](auto k, uint32_t grid, const auto& fin) {
+        hipLaunchKernelGGL(k, dim3(grid), dim3(GBLOCK), 0, c.s, c.log, (uint8_t*)out, (const uint8_t*)tab,
+                           c.rb, c.idx, c.n, c.rg, c.logon, gl, fin);
+    };
     if (gl == 6)
-        hipLaunchKernelGGL((k_scatter<G, CW, W, R_ROWWAVE, true>), dim3(rows_grid(n, gl, R_ROWWAVE, d)),
-                           block, 0, s, t, log, (uint8_t*)dst, rb, idx, (const uint8_t*)src, n, rg, seq,
-                           logon, gl);
-    else if (rb <= 16)
-        hipLaunchKernelGGL((k_scatter<G, CW, W, R_NARROW, false>), dim3(rows_grid(n, gl, R_NARROW, d)),
-                           block, 0, s, t, log, (uint8_t*)dst, rb, idx, (const uint8_t*)src, n, rg, seq,
-                           logon, gl);
-    else
-        hipLaunchKernelGGL((k_scatter<G, CW, W, R_WIDE, false>), dim3(rows_grid(n, gl, R_WIDE, d)),
-                           block, 0, s, t, log, (uint8_t*)dst, rb, idx, (const uint8_t*)src, n, rg, seq,
-                           logon, gl);
+        return row_launch<G>(c, k_gather<G, CW, W, R_ROWWAVE, true>, rows_grid(c.n, gl, R_ROWWAVE, c.d),
+                             launch);
+    if (c.rb <= 16)
+        return row_launch<G>(c, k_gather<G, CW, W, R_NARROW, false>,
+                             rows_grid(c.n, gl, R_NARROW, c.d, true), launch);
+    return row_launch<G>(c, k_gather<G, CW, W, R_WIDE, false>, rows_grid(c.n, gl, R_WIDE, c.d), launch);
 }
 
 template <bool G, int W>
-static void scatter_w(const DevTable& t, DevLog* log, void* dst, uint64_t rb, const int64_t* idx,
-                      const void* src, uint64_t n, const RowsGuard& rg, unsigned long long seq,
-                      int logon, const DevInfo& d, hipStream_t s) {
-    if (rb % 16 == 0 && (((uint64_t)dst | (uint64_t)src) & 15) == 0)
-        scatter_cw<G, 16, W>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-    else
-        scatter_cw<G, W, W>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
+static hipError_t gather_w(const RowCall& c, void* out, const void* tab) {
+    if (c.rb % 16 == 0 && (((uint64_t)out | (uint64_t)tab) & 15) == 0)
+        return gather_cw<G, 16, W>(c, out, tab);
+    return gather_cw<G, W, W>(c, out, tab);
 }
 
-hipError_t launch_scatter(bool guard, const DevTable& t, DevLog* log, const Bind* binds, void* dst,
+hipError_t launch_gather(bool guard, const GuardTab& t, DevLog* log, const Bind* binds, void* out,
+                         const void* tab, uint64_t rb, const int64_t* idx, uint64_t n, uint32_t w,
+                         unsigned long long seq, int logon, const DevInfo& d, hipStream_t s,
+                         bool finish) {
+    if (n == 0) return hipSuccess;
+    RowCall c{t, log, rb, idx, n, rows_open(n, rb, w), FaultSite{}, seq, logon, finish, d, s};
+    if (!guard) return w == 4 ? gather_w<false, 4>(c, out, tab) : gather_w<false, 8>(c, out, tab);
+    c.rg = rows_guard(binds[0], binds[2], binds[1], (uint64_t)idx, (uint64_t)out, (uint64_t)tab, n, rb, w);
+    c.site = rows_fault_site(3 /*OP_GATHER*/, w, 1, rb, c.rg.ki, idx, out, tab);
+    return w == 4 ? gather_w<true, 4>(c, out, tab) : gather_w<true, 8>(c, out, tab);
+}
+
+template <bool G, int CW, int W>
+static hipError_t scatter_cw(const RowCall& c, void* dst, const void* src) {
+    const uint32_t gl = lanes_log2(c.rb / CW);
+    const auto launch = [&](auto k, uint32_t grid, const auto& fin) {
+        hipLaunchKernelGGL(k, dim3(grid), dim3(GBLOCK), 0, c.s, c.log, (uint8_t*)dst, c.rb, c.idx,
+                           (const uint8_t*)src, c.n, c.rg, c.logon, gl, fin);
+    };
+    if (gl == 6)
+        return row_launch<G>(c, k_scatter<G, CW, W, R_ROWWAVE, true>, rows_grid(c.n, gl, R_ROWWAVE, c.d),
+                             launch);
+    if (c.rb <= 16)
+        return row_launch<G>(c, k_scatter<G, CW, W, R_NARROW, false>, rows_grid(c.n, gl, R_NARROW, c.d),
+                             launch);
+    return row_launch<G>(c, k_scatter<G, CW, W, R_WIDE, false>, rows_grid(c.n, gl, R_WIDE, c.d), launch);
+}
+
+template <bool G, int W>
+static hipError_t scatter_w(const RowCall& c, void* dst, const void* src) {
+    if (c.rb % 16 == 0 && (((uint64_t)dst | (uint64_t)src) & 15) == 0)
+        return scatter_cw<G, 16, W>(c, dst, src);
+    return scatter_cw<G, W, W>(c, dst, src);
+}
+
+hipError_t launch_scatter(bool guard, const GuardTab& t, DevLog* log, const Bind* binds, void* dst,
                           uint64_t rb, const int64_t* idx, const void* src, uint64_t n, uint32_t w,
                           int accumulate, unsigned long long seq, int logon, void* scratch,
                           const DevInfo& d, hipStream_t s, bool finish) {
@@ -384,20 +387,11 @@ hipError_t launch_scatter(bool guard, const DevTable& t, DevLog* log, const Bind
     if (accumulate)
         return launch_scatter_add(guard, t, log, binds, dst, rb, idx, src, n, w, seq, logon,
                                   scratch, d, s, finish, accumulate == 2);
-    if (guard) {
-        const RowsGuard rg = rows_guard(binds[0], binds[1], binds[2], (uint64_t)idx, (uint64_t)src,
-                                        (uint64_t)dst, n, rb, w);
-        if (w == 4) scatter_w<true, 4>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-        else scatter_w<true, 8>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-        if (logon && finish)
-            return launch_fault_finish(t, log, rows_fault_site(4 /*OP_SCATTER*/, w, 2, rb, rg.ki, idx,
-                                                                 src, dst), seq, s);
-    } else {
-        const RowsGuard rg = rows_open(n, rb, w);
-        if (w == 4) scatter_w<false, 4>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-        else scatter_w<false, 8>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-    }
-    return hipGetLastError();
+    RowCall c{t, log, rb, idx, n, rows_open(n, rb, w), FaultSite{}, seq, logon, finish, d, s};
+    if (!guard) return w == 4 ? scatter_w<false, 4>(c, dst, src) : scatter_w<false, 8>(c, dst, src);
+    c.rg = rows_guard(binds[0], binds[1], binds[2], (uint64_t)idx, (uint64_t)src, (uint64_t)dst, n, rb, w);
+    c.site = rows_fault_site(4 /*OP_SCATTER*/, w, 2, rb, c.rg.ki, idx, src, dst);
+    return w == 4 ? scatter_w<true, 4>(c, dst, src) : scatter_w<true, 8>(c, dst, src);
 }
 
 }  // namespace agile

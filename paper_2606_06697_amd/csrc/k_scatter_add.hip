@@ -16,8 +16,7 @@
 // promises a destination of +0.0 rows (scatter-add into zeros), an owned run stores (+0.0 + its sum)
 // without reading the row. Rows that failed the fast test follow in a separate kernel that checks
 // every element exactly (denied loads read zero, denied stores are dropped) and counts denials as
-// the other data-dependent guarded kernels do; a one-thread kernel after the launch records the
-// smallest key.
+// the other data-dependent guarded kernels do.
 //
 // Chunk path (smaller calls, or destination intervals too large for 32-bit keys): one kernel, whose
 // workgroups sort 64 to 1,024 consecutive indices each in LDS and add each row of the chunk once, with
@@ -31,8 +30,6 @@
 //   131,072 x 64         128 us     46 us   (chunks)
 //   1,048,576 x 32       204 us    132 us   (sorted)
 //   1,048,576 x 256      375 us    335 us   (sorted; the reduce alone 297 -> 265)
-#include <type_traits>
-
 #include "launch.h"
 
 namespace agile {
@@ -108,10 +105,10 @@ __device__ __forceinline__ void add_sum(uint8_t* dst, uint64_t rb, int64_t rlo, 
 // batch has a run in every chunk. A lane holds EPL columns a group's width apart, so that each
 // atomic instruction covers whole lines.
 template <bool GUARD, int W, int EPL, int CH, int TB>
-__global__ __launch_bounds__(TB) void k_scatter_add(DevTable t, DevLog* log, uint8_t* dst,
-                                                         uint64_t rb, const int64_t* idx,
-                                                         const uint8_t* src, uint64_t n,
-                                                         RowsGuard rg, int logon, uint32_t glog2) {
+__global__ __launch_bounds__(TB) void k_scatter_add(DevLog* log, uint8_t* dst, uint64_t rb,
+                                                    const int64_t* idx, const uint8_t* src,
+                                                    uint64_t n, RowsGuard rg, int logon,
+                                                    uint32_t glog2, FinishOf<GUARD> fin) {
     using F = typename FloatOf<W>::F;
     constexpr uint32_t NB = CH / 64;
     __shared__ __align__(16) uint64_t kin[CH], kblk[CH];  // keys as they came, and each 64 sorted
@@ -256,7 +253,7 @@ __global__ __launch_bounds__(TB) void k_scatter_add(DevTable t, DevLog* log, uin
             __syncthreads();
         }
     }
-    if (GUARD && logon) fold_faults(acc, log);
+    if (GUARD && logon) end_faults(acc, log, fin);
 }
 
 // ================================================================ sorted path
@@ -702,10 +699,10 @@ __global__ __launch_bounds__(256, ROW_WAVE ? 4 : 3) void k_srt_reduce(uint8_t* d
 // reduce, whose owned rows take plain stores. All of the sorted path's denials come from these rows,
 // so the last workgroup to finish also records them.
 template <int W>
-__global__ __launch_bounds__(256) void k_srt_slow(DevTable t, DevLog* log, uint8_t* dst, uint64_t rb,
+__global__ __launch_bounds__(256) void k_srt_slow(DevLog* log, uint8_t* dst, uint64_t rb,
                                                   const int64_t* idx, const uint8_t* src,
                                                   uint64_t n, RowsGuard rg, SortBufs b,
-                                                  uint32_t npasses, int logon) {
+                                                  uint32_t npasses, int logon, FinishArgs fin) {
     const uint32_t slow = b.dstart[256];
     if (slow == 0) return;
     const uint32_t* vals = b.vals[b.ctl[4 + npasses]];
@@ -715,7 +712,7 @@ __global__ __launch_bounds__(256) void k_srt_slow(DevTable t, DevLog* log, uint8
     for (uint64_t e0 = n - slow + wave * 4; e0 < n; e0 += step)
         for (uint64_t e = e0; e < n && e < e0 + 4; ++e)
             add_row_exact<true, W>(dst, rb, idx, src, vals[e], rg, acc);
-    if (logon) fold_faults(acc, log);
+    if (logon) end_faults(acc, log, fin);
 }
 
 // Lanes per row: enough to cover its chunks, at most a wave.
@@ -745,77 +742,106 @@ static void reduce_sorted(void* dst, uint64_t rb, const void* src, uint64_t n, c
                            (const uint8_t*)src, n, b, npasses, rg.g.rlo, (uint32_t)zero_dst, tile, gl);
 }
 
+// A scatter-add's launch, and what its denials need.
+struct AddCall {
+    GuardTab t;
+    DevLog* log;
+    uint8_t* dst;
+    uint64_t rb;
+    const int64_t* idx;
+    const uint8_t* src;
+    uint64_t n;
+    RowsGuard rg;
+    FaultSite site;
+    unsigned long long seq;
+    int logon;
+    bool finish;
+    DevInfo d;
+    hipStream_t s;
+};
+
 template <bool G, int W>
-static void scatter_add_sorted(const DevTable& t, DevLog* log, void* dst, uint64_t rb,
-                               const int64_t* idx, const void* src, uint64_t n,
-                               const RowsGuard& rg, uint32_t npasses, void* scratch,
-                               unsigned long long seq, int logon, const DevInfo& d,
-                               hipStream_t s, bool zero_dst) {
-    const SortBufs b = sort_bufs(scratch, n);
-    const uint32_t ntiles = (uint32_t)srt_ntiles(n);
+static hipError_t scatter_add_sorted(const AddCall& c, uint32_t npasses, void* scratch, bool zero_dst) {
+    const SortBufs b = sort_bufs(scratch, c.n);
+    const uint32_t ntiles = (uint32_t)srt_ntiles(c.n);
     // the key pass also writes the first pass's per-tile histograms
-    hipLaunchKernelGGL((k_srt_keys<G>), dim3(ntiles), dim3(SRT_TB), 0, s, idx, n, rg, b);
+    hipLaunchKernelGGL((k_srt_keys<G>), dim3(ntiles), dim3(SRT_TB), 0, c.s, c.idx, c.n, c.rg, b);
     for (uint32_t p = 0; p < npasses; ++p) {
-        if (p > 0) hipLaunchKernelGGL(k_srt_hist, dim3(ntiles), dim3(SRT_TB), 0, s, b, n, p);
-        hipLaunchKernelGGL(k_srt_scan_rows, dim3(p == 0 ? 257 : 256), dim3(SRT_BLOCK), 0, s, b, ntiles);
-        hipLaunchKernelGGL(k_srt_scatter, dim3(ntiles), dim3(SRT_TB), 0, s, b, n, p);
+        if (p > 0) hipLaunchKernelGGL(k_srt_hist, dim3(ntiles), dim3(SRT_TB), 0, c.s, b, c.n, p);
+        hipLaunchKernelGGL(k_srt_scan_rows, dim3(p == 0 ? 257 : 256), dim3(SRT_BLOCK), 0, c.s, b, ntiles);
+        hipLaunchKernelGGL(k_srt_scatter, dim3(ntiles), dim3(SRT_TB), 0, c.s, b, c.n, p);
     }
-    if ((((uint64_t)src | (uint64_t)dst | rb) & 15) == 0)
-        reduce_sorted<G, W, 16 / W>(dst, rb, src, n, rg, npasses, b, d, s, zero_dst);
+    if ((((uint64_t)c.src | (uint64_t)c.dst | c.rb) & 15) == 0)
+        reduce_sorted<G, W, 16 / W>(c.dst, c.rb, c.src, c.n, c.rg, npasses, b, c.d, c.s, zero_dst);
     else
-        reduce_sorted<G, W, 1>(dst, rb, src, n, rg, npasses, b, d, s, zero_dst);
-    if (G) {
-        const uint64_t sb = (n + 255) / 256, cap = (uint64_t)d.num_cu * 4;
-        hipLaunchKernelGGL((k_srt_slow<W>), dim3((uint32_t)(sb < cap ? sb : cap)), dim3(256), 0, s, t, log,
-                           (uint8_t*)dst, rb, idx, (const uint8_t*)src, n, rg, b, npasses, logon);
+        reduce_sorted<G, W, 1>(c.dst, c.rb, c.src, c.n, c.rg, npasses, b, c.d, c.s, zero_dst);
+    if constexpr (G) {
+        const uint64_t sb = (c.n + 255) / 256, cap = (uint64_t)c.d.num_cu * 4;
+        const uint32_t grid = (uint32_t)(sb < cap ? sb : cap);
+        const bool wanted = c.logon && c.finish;
+        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted);
+        hipLaunchKernelGGL((k_srt_slow<W>), dim3(grid), dim3(256), 0, c.s, c.log, c.dst, c.rb, c.idx, c.src,
+                           c.n, c.rg, b, npasses, c.logon, fin);
+        if (wanted && !fin.fused) return launch_fault_finish(c.t, c.log, c.site, c.seq, c.s);
     }
+    return hipGetLastError();
 }
 
 template <bool G, int W, int EPL, int CH, int TB>
-static void launch_chunks(dim3 grid, const DevTable& t, DevLog* log, void* dst, uint64_t rb,
-                          const int64_t* idx, const void* src, uint64_t n, const RowsGuard& rg,
-                          int logon, uint32_t gl, hipStream_t s) {
-    hipLaunchKernelGGL((k_scatter_add<G, W, EPL, CH, TB>), grid, dim3(TB), 0, s, t, log, (uint8_t*)dst, rb,
-                       idx, (const uint8_t*)src, n, rg, logon, gl);
+static hipError_t scatter_add_chunks(const AddCall& c, uint32_t gl) {
+    const uint64_t chunks = (c.n + CH - 1) / CH, cap = (uint64_t)c.d.num_cu * 8;
+    const uint32_t grid = (uint32_t)(chunks < cap ? chunks : cap);
+    const auto launch = [&](const auto& fin) {
+        hipLaunchKernelGGL((k_scatter_add<G, W, EPL, CH, TB>), dim3(grid), dim3(TB), 0, c.s, c.log, c.dst,
+                           c.rb, c.idx, c.src, c.n, c.rg, c.logon, gl, fin);
+    };
+    if constexpr (G) {
+        const bool wanted = c.logon && c.finish;
+        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted);
+        launch(fin);
+        if (wanted && !fin.fused) return launch_fault_finish(c.t, c.log, c.site, c.seq, c.s);
+    } else {
+        launch(NoFinish{});
+    }
+    return hipGetLastError();
 }
 
 template <bool G, int W>
-static void scatter_add_w(const DevTable& t, DevLog* log, void* dst, uint64_t rb,
-                          const int64_t* idx, const void* src, uint64_t n, const RowsGuard& rg,
-                          unsigned long long seq, int logon, const DevInfo& d, hipStream_t s) {
+static hipError_t scatter_add_w(const AddCall& c) {
     constexpr int EPL = W == 4 ? 4 : 2;
-    const uint32_t gl = row_lanes_log2((rb / W + EPL - 1) / EPL);
+    const uint32_t gl = row_lanes_log2((c.rb / W + EPL - 1) / EPL);
     uint64_t ch = 64;
-    while (ch < 1024 && n > SA_CHUNKS * ch) ch *= 2;
-    const uint64_t chunks = (n + ch - 1) / ch, cap = (uint64_t)d.num_cu * 8;
-    const dim3 grid((uint32_t)(chunks < cap ? chunks : cap));
+    while (ch < 1024 && c.n > SA_CHUNKS * ch) ch *= 2;
     switch (ch) {
-        case 64: return launch_chunks<G, W, EPL, 64, 256>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
-        case 128: return launch_chunks<G, W, EPL, 128, 256>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
-        case 256: return launch_chunks<G, W, EPL, 256, 1024>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
-        case 512: return launch_chunks<G, W, EPL, 512, 1024>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
-        default: return launch_chunks<G, W, EPL, 1024, 1024>(grid, t, log, dst, rb, idx, src, n, rg, logon, gl, s);
+        case 64: return scatter_add_chunks<G, W, EPL, 64, 256>(c, gl);
+        case 128: return scatter_add_chunks<G, W, EPL, 128, 256>(c, gl);
+        case 256: return scatter_add_chunks<G, W, EPL, 256, 1024>(c, gl);
+        case 512: return scatter_add_chunks<G, W, EPL, 512, 1024>(c, gl);
+        default: return scatter_add_chunks<G, W, EPL, 1024, 1024>(c, gl);
     }
 }
 
-hipError_t launch_scatter_add(bool guard, const DevTable& t, DevLog* log, const Bind* binds,
+hipError_t launch_scatter_add(bool guard, const GuardTab& t, DevLog* log, const Bind* binds,
                               void* dst, uint64_t rb, const int64_t* idx, const void* src,
                               uint64_t n, uint32_t w, unsigned long long seq, int logon,
                               void* scratch, const DevInfo& d, hipStream_t s, bool finish,
                               bool zero_dst) {
     if (n == 0) return hipSuccess;
-    const RowsGuard rg = guard ? rows_guard(binds[0], binds[1], binds[2], (uint64_t)idx,
-                                            (uint64_t)src, (uint64_t)dst, n, rb, w)
-                               : rows_open(n, rb, w);
+    AddCall c{t, log, static_cast<uint8_t*>(dst), rb, idx, static_cast<const uint8_t*>(src), n,
+              guard ? rows_guard(binds[0], binds[1], binds[2], (uint64_t)idx, (uint64_t)src, (uint64_t)dst,
+                                 n, rb, w)
+                    : rows_open(n, rb, w),
+              FaultSite{}, seq, logon, finish, d, s};
+    if (guard) c.site = rows_fault_site(5 /*OP_SCATTER_ADD*/, w, 2, rb, c.rg.ki, idx, src, dst);
     // sorted path: 32-bit keys (guarded: the destination's row interval minus the sentinel;
     // unguarded: idx + 2^31), positions below 2^32
     uint32_t npasses = 0;
     bool sorted = scratch != nullptr && scatter_add_sorts(n, rb) && n < (1ull << 32);
     if (sorted && guard) {
-        if (!rg.g.bound || rg.g.rhi < rg.g.rlo) {
+        if (!c.rg.g.bound || c.rg.g.rhi < c.rg.g.rlo) {
             npasses = 1;  // no fast rows: every key is the sentinel, the sort is trivial
         } else {
-            const uint64_t span = (uint64_t)rg.g.rhi - (uint64_t)rg.g.rlo;
+            const uint64_t span = (uint64_t)c.rg.g.rhi - (uint64_t)c.rg.g.rlo;
             if (span >= SRT_SENT) sorted = false;
             // enough bits for span + 1, so that no key equals the sentinel in the sorted bits
             // (the largest key of a 2^16-row table is all ones in 16 bits)
@@ -828,24 +854,13 @@ hipError_t launch_scatter_add(bool guard, const DevTable& t, DevLog* log, const 
         npasses = 4;
     }
     if (sorted) {
-        if (guard) {
-            if (w == 4) scatter_add_sorted<true, 4>(t, log, dst, rb, idx, src, n, rg, npasses, scratch, seq, logon, d, s, zero_dst);
-            else scatter_add_sorted<true, 8>(t, log, dst, rb, idx, src, n, rg, npasses, scratch, seq, logon, d, s, zero_dst);
-        } else {
-            if (w == 4) scatter_add_sorted<false, 4>(t, log, dst, rb, idx, src, n, rg, npasses, scratch, seq, logon, d, s, zero_dst);
-            else scatter_add_sorted<false, 8>(t, log, dst, rb, idx, src, n, rg, npasses, scratch, seq, logon, d, s, zero_dst);
-        }
-    } else if (guard) {
-        if (w == 4) scatter_add_w<true, 4>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-        else scatter_add_w<true, 8>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-    } else {
-        if (w == 4) scatter_add_w<false, 4>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
-        else scatter_add_w<false, 8>(t, log, dst, rb, idx, src, n, rg, seq, logon, d, s);
+        if (guard) return w == 4 ? scatter_add_sorted<true, 4>(c, npasses, scratch, zero_dst)
+                                 : scatter_add_sorted<true, 8>(c, npasses, scratch, zero_dst);
+        return w == 4 ? scatter_add_sorted<false, 4>(c, npasses, scratch, zero_dst)
+                      : scatter_add_sorted<false, 8>(c, npasses, scratch, zero_dst);
     }
-    if (guard && logon && finish)
-        return launch_fault_finish(t, log, rows_fault_site(5 /*OP_SCATTER_ADD*/, w, 2, rb, rg.ki, idx,
-                                                             src, dst), seq, s);
-    return hipGetLastError();
+    if (guard) return w == 4 ? scatter_add_w<true, 4>(c) : scatter_add_w<true, 8>(c);
+    return w == 4 ? scatter_add_w<false, 4>(c) : scatter_add_w<false, 8>(c);
 }
 
 }  // namespace agile

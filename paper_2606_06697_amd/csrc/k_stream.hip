@@ -6,8 +6,8 @@
 // length per argument, passed in kernel arguments and so held in scalar registers. The vector
 // loop compares each lane's vector offset with that bound before touching memory; vectors past
 // a bound take the per-element path (denied loads read zero, denied stores are dropped). The
-// denial count and the first denial follow in closed form from the prefix lengths and are
-// logged by one thread. GUARD=false compiles the same loop with no compare (the unguarded twin).
+// denial count and the first denial follow in closed form from the prefix lengths: the caller works
+// them out, with the first denial's reason, and one thread logs them. GUARD=false compiles the same loop with no compare (the unguarded twin).
 #include "launch.h"
 
 #pragma clang fp contract(off)
@@ -38,6 +38,14 @@ struct VecT<1> {
     static __device__ __forceinline__ T zero() { return 0; }
 };
 
+__device__ __forceinline__ void log_stream_fault(const StreamFault& f, DevLog* log,
+                                                 unsigned long long seq) {
+    if (f.count && blockIdx.x == 0 && threadIdx.x == 0) {
+        atomicAdd(&log->count, (unsigned long long)f.count);
+        log_record(log, seq, f.elem, f.operand, f.addr, f.width, f.op, f.verdict, f.owner);
+    }
+}
+
 __device__ inline void copy_bytes_slow(uint8_t* dst, const uint8_t* src, uint64_t b0, uint64_t b1,
                                        uint64_t Ks, uint64_t Kd) {
     for (uint64_t k = b0; k < b1; ++k) {
@@ -48,10 +56,11 @@ __device__ inline void copy_bytes_slow(uint8_t* dst, const uint8_t* src, uint64_
 
 // Ks, Kd: allowed byte prefixes of src and dst (n and n for the unguarded twin).
 template <bool GUARD, int VW>
-__global__ __launch_bounds__(SBLOCK) void k_copy(DevTable t, DevLog* log, uint8_t* __restrict__ dst,
+__global__ __launch_bounds__(SBLOCK) void k_copy(StreamFault f, DevLog* log,
+                                                  uint8_t* __restrict__ dst,
                                                   const uint8_t* __restrict__ src, uint64_t n,
                                                   uint64_t Ks, uint64_t Kd,
-                                                  unsigned long long seq, int logon) {
+                                                  unsigned long long seq) {
     using V = typename VecT<VW>::T;
     const uint64_t K = Ks < Kd ? Ks : Kd;
     const uint64_t nv = n / VW;
@@ -104,19 +113,7 @@ __global__ __launch_bounds__(SBLOCK) void k_copy(DevTable t, DevLog* log, uint8_
         if (!GUARD) dst[tb] = src[tb];
         else copy_bytes_slow(dst, src, tb, tb + 1, Ks, Kd);
     }
-    if (GUARD && logon && blockIdx.x == 0 && threadIdx.x == 0) {
-        const uint64_t cnt = (n - Ks) + (n - Kd);
-        if (cnt) {
-            atomicAdd(&log->count, (unsigned long long)cnt);
-            const uint32_t operand = Ks <= Kd ? 0u : 1u;
-            const uint64_t k = operand ? Kd : Ks;
-            const uint64_t A = (operand ? (uint64_t)dst : (uint64_t)src) + k;
-            uint32_t v;
-            int32_t o;
-            reason_lane(t, A, 1, v, o);
-            log_record(log, seq, k, operand, A, 1, 1 /*OP_COPY*/, v, o);
-        }
-    }
+    if (GUARD) log_stream_fault(f, log, seq);
 }
 
 __device__ __forceinline__ float triad1(float b, float s, float c) {
@@ -135,10 +132,10 @@ __device__ inline void triad_slow(float* a, const float* b, const float* c, floa
 
 // Ka, Kb, Kc: allowed element prefixes of the three operands (all n for the unguarded twin).
 template <bool GUARD, int VE>
-__global__ __launch_bounds__(SBLOCK) void k_triad(DevTable t, DevLog* log, float* a, const float* b,
-                                                   const float* c, float s, uint64_t n,
-                                                   uint64_t Ka, uint64_t Kb, uint64_t Kc,
-                                                   unsigned long long seq, int logon) {
+__global__ __launch_bounds__(SBLOCK) void k_triad(StreamFault f, DevLog* log, float* a,
+                                                   const float* b, const float* c, float s,
+                                                   uint64_t n, uint64_t Ka, uint64_t Kb,
+                                                   uint64_t Kc, unsigned long long seq) {
     uint64_t K = Ka < Kb ? Ka : Kb;
     K = K < Kc ? K : Kc;
     const uint64_t nv = n / VE;
@@ -219,22 +216,7 @@ __global__ __launch_bounds__(SBLOCK) void k_triad(DevTable t, DevLog* log, float
     }
     const uint64_t ti = nv * VE + tid;
     if (ti < n) triad_slow(a, b, c, s, ti, ti + 1, Ka, Kb, Kc);
-    if (GUARD && logon && blockIdx.x == 0 && threadIdx.x == 0) {
-        const uint64_t cnt = (n - Kb) + (n - Kc) + (n - Ka);
-        if (cnt) {
-            atomicAdd(&log->count, (unsigned long long)cnt);
-            uint64_t k = Kb;
-            uint32_t operand = 0;
-            uint64_t p = (uint64_t)b;
-            if (Kc < k) { k = Kc; operand = 1; p = (uint64_t)c; }
-            if (Ka < k) { k = Ka; operand = 2; p = (uint64_t)a; }
-            const uint64_t A = p + 4 * k;
-            uint32_t v;
-            int32_t o;
-            reason_lane(t, A, 4, v, o);
-            log_record(log, seq, k, operand, A, 4, 2 /*OP_TRIAD*/, v, o);
-        }
-    }
+    if (GUARD) log_stream_fault(f, log, seq);
 }
 
 // One pass: as many 128-thread blocks as the vectors need, each thread one vector. Measured on
@@ -242,8 +224,7 @@ __global__ __launch_bounds__(SBLOCK) void k_triad(DevTable t, DevLog* log, float
 // 0.382 ms with one persistent 256-thread workgroup per CU looping over 4 vectors per thread
 // per pass (the hardware's block dispatch balances the end of the launch better than a fixed
 // split), and against 0.51-0.60 ms for the triad with blocks of 64-256 threads and 2-4 vectors.
-static uint32_t stream_grid(uint64_t nv, const DevInfo& d) {
-    (void)d;
+static uint32_t stream_grid(uint64_t nv) {
     uint64_t want = (nv + (uint64_t)SBLOCK * SUNROLL - 1) / ((uint64_t)SBLOCK * SUNROLL);
     const uint64_t cap = 1ull << 30;  // beyond 2^37 vectors the loop takes further passes
     if (want < 1) want = 1;
@@ -251,56 +232,54 @@ static uint32_t stream_grid(uint64_t nv, const DevInfo& d) {
 }
 
 template <bool G>
-static void copy_dispatch(const DevTable& t, DevLog* log, void* dst, const void* src, uint64_t n,
-                          uint64_t Ks, uint64_t Kd, unsigned long long seq, int logon,
-                          const DevInfo& d, hipStream_t s) {
+static void copy_dispatch(const StreamFault& f, DevLog* log, void* dst, const void* src, uint64_t n,
+                          uint64_t Ks, uint64_t Kd, unsigned long long seq, hipStream_t s) {
     const uint64_t ad = (uint64_t)dst | (uint64_t)src;
     if ((ad & 15) == 0)
-        hipLaunchKernelGGL((k_copy<G, 16>), dim3(stream_grid(n / 16, d)), dim3(SBLOCK), 0, s, t, log,
-                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq, logon);
+        hipLaunchKernelGGL((k_copy<G, 16>), dim3(stream_grid(n / 16)), dim3(SBLOCK), 0, s, f, log,
+                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq);
     else if ((ad & 3) == 0)
-        hipLaunchKernelGGL((k_copy<G, 4>), dim3(stream_grid(n / 4, d)), dim3(SBLOCK), 0, s, t, log,
-                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq, logon);
+        hipLaunchKernelGGL((k_copy<G, 4>), dim3(stream_grid(n / 4)), dim3(SBLOCK), 0, s, f, log,
+                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq);
     else
-        hipLaunchKernelGGL((k_copy<G, 1>), dim3(stream_grid(n, d)), dim3(SBLOCK), 0, s, t, log,
-                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq, logon);
+        hipLaunchKernelGGL((k_copy<G, 1>), dim3(stream_grid(n)), dim3(SBLOCK), 0, s, f, log,
+                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq);
 }
 
-hipError_t launch_copy(bool guard, const DevTable& t, DevLog* log, const Bind* binds, void* dst,
-                       const void* src, uint64_t n, unsigned long long seq, int logon,
-                       const DevInfo& d, hipStream_t s) {
+hipError_t launch_copy(bool guard, const StreamFault& f, DevLog* log, const Bind* binds, void* dst,
+                       const void* src, uint64_t n, unsigned long long seq, hipStream_t s) {
     if (n == 0) return hipSuccess;
     if (guard)
-        copy_dispatch<true>(t, log, dst, src, n, clip_prefix(binds[0], (uint64_t)src, n, 1),
-                            clip_prefix(binds[1], (uint64_t)dst, n, 1), seq, logon, d, s);
+        copy_dispatch<true>(f, log, dst, src, n, clip_prefix(binds[0], (uint64_t)src, n, 1),
+                            clip_prefix(binds[1], (uint64_t)dst, n, 1), seq, s);
     else
-        copy_dispatch<false>(t, log, dst, src, n, n, n, seq, logon, d, s);
+        copy_dispatch<false>(f, log, dst, src, n, n, n, seq, s);
     return hipGetLastError();
 }
 
 template <bool G>
-static void triad_dispatch(const DevTable& t, DevLog* log, float* a, const float* b, const float* c,
+static void triad_dispatch(const StreamFault& f, DevLog* log, float* a, const float* b, const float* c,
                            float sc, uint64_t n, uint64_t Ka, uint64_t Kb, uint64_t Kc,
-                           unsigned long long seq, int logon, const DevInfo& d, hipStream_t s) {
+                           unsigned long long seq, hipStream_t s) {
     const uint64_t ad = (uint64_t)a | (uint64_t)b | (uint64_t)c;
     if ((ad & 15) == 0)
-        hipLaunchKernelGGL((k_triad<G, 4>), dim3(stream_grid(n / 4, d)), dim3(SBLOCK), 0, s, t, log,
-                           a, b, c, sc, n, Ka, Kb, Kc, seq, logon);
+        hipLaunchKernelGGL((k_triad<G, 4>), dim3(stream_grid(n / 4)), dim3(SBLOCK), 0, s, f, log, a, b,
+                           c, sc, n, Ka, Kb, Kc, seq);
     else
-        hipLaunchKernelGGL((k_triad<G, 1>), dim3(stream_grid(n, d)), dim3(SBLOCK), 0, s, t, log, a,
-                           b, c, sc, n, Ka, Kb, Kc, seq, logon);
+        hipLaunchKernelGGL((k_triad<G, 1>), dim3(stream_grid(n)), dim3(SBLOCK), 0, s, f, log, a, b, c,
+                           sc, n, Ka, Kb, Kc, seq);
 }
 
-hipError_t launch_triad(bool guard, const DevTable& t, DevLog* log, const Bind* binds, float* a,
+hipError_t launch_triad(bool guard, const StreamFault& f, DevLog* log, const Bind* binds, float* a,
                         const float* b, const float* c, float sc, uint64_t n,
-                        unsigned long long seq, int logon, const DevInfo& d, hipStream_t s) {
+                        unsigned long long seq, hipStream_t s) {
     if (n == 0) return hipSuccess;
     if (guard)
-        triad_dispatch<true>(t, log, a, b, c, sc, n, clip_prefix(binds[2], (uint64_t)a, n, 4),
+        triad_dispatch<true>(f, log, a, b, c, sc, n, clip_prefix(binds[2], (uint64_t)a, n, 4),
                              clip_prefix(binds[0], (uint64_t)b, n, 4),
-                             clip_prefix(binds[1], (uint64_t)c, n, 4), seq, logon, d, s);
+                             clip_prefix(binds[1], (uint64_t)c, n, 4), seq, s);
     else
-        triad_dispatch<false>(t, log, a, b, c, sc, n, n, n, n, seq, logon, d, s);
+        triad_dispatch<false>(f, log, a, b, c, sc, n, n, n, n, seq, s);
     return hipGetLastError();
 }
 

@@ -20,21 +20,36 @@ constexpr uint32_t MAX_RADIX = (1u << 14) + 1;
 hipError_t launch_validate(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
                            uint8_t* verdict, int32_t* owner, bool dma, hipStream_t s);
 
+// The denials of a copy or triad, which follow from its allowed prefixes and are worked out by the
+// caller (count == 0: none, or not logged); the launch writes them to the log.
+struct StreamFault {
+    uint64_t count, elem, addr;
+    uint32_t width, op, operand, verdict;
+    int32_t owner;
+    uint32_t pad;
+};
+
+// The table that a row kernel's first denial is looked up in: in the launch's arguments, or (inl ==
+// null) the uploaded image.
+struct GuardTab {
+    const DevTable* dev;
+    const InlineTab* inl;
+};
+
 // Guarded launches take the bindings of their pointer arguments, looked up on the host from the
 // table the launch is ordered after (`binds` in the operand order of the operation: copy src,
 // dst; triad b, c, a; gather idx, table, out; scatter idx, src, dst). With guard == false
 // `binds` is ignored and may be null.
-hipError_t launch_copy(bool guard, const DevTable& t, DevLog* log, const Bind* binds, void* dst,
-                       const void* src, uint64_t n, unsigned long long seq, int logon,
-                       const DevInfo& d, hipStream_t s);
+hipError_t launch_copy(bool guard, const StreamFault& f, DevLog* log, const Bind* binds, void* dst,
+                       const void* src, uint64_t n, unsigned long long seq, hipStream_t s);
 
-hipError_t launch_triad(bool guard, const DevTable& t, DevLog* log, const Bind* binds, float* a,
+hipError_t launch_triad(bool guard, const StreamFault& f, DevLog* log, const Bind* binds, float* a,
                         const float* b, const float* c, float sc, uint64_t n,
-                        unsigned long long seq, int logon, const DevInfo& d, hipStream_t s);
+                        unsigned long long seq, hipStream_t s);
 
 // finish == false leaves the launch's denials in the log scratch for a later kernel (the
 // redirecting policies' pass) and the finishing kernel.
-hipError_t launch_gather(bool guard, const DevTable& t, DevLog* log, const Bind* binds, void* out,
+hipError_t launch_gather(bool guard, const GuardTab& t, DevLog* log, const Bind* binds, void* out,
                          const void* tab, uint64_t row_bytes, const int64_t* idx, uint64_t n,
                          uint32_t w, unsigned long long seq, int logon, const DevInfo& d,
                          hipStream_t s, bool finish = true);
@@ -42,14 +57,14 @@ hipError_t launch_gather(bool guard, const DevTable& t, DevLog* log, const Bind*
 // Scatter with accumulate = 1 uses `scratch` (device memory of at least
 // scatter_add_scratch_bytes(n) bytes, or null for the chunk path) for its sort; calls that share
 // a scratch buffer must be ordered on one stream.
-hipError_t launch_scatter(bool guard, const DevTable& t, DevLog* log, const Bind* binds, void* dst,
+hipError_t launch_scatter(bool guard, const GuardTab& t, DevLog* log, const Bind* binds, void* dst,
                           uint64_t row_bytes, const int64_t* idx, const void* src, uint64_t n,
                           uint32_t w, int accumulate, unsigned long long seq, int logon,
                           void* scratch, const DevInfo& d, hipStream_t s, bool finish = true);
 
 // zero_dst: the destination rows are +0.0 before the call (scatter-add mode 2); the sorted path
 // then writes each row's sum without reading the row.
-hipError_t launch_scatter_add(bool guard, const DevTable& t, DevLog* log, const Bind* binds,
+hipError_t launch_scatter_add(bool guard, const GuardTab& t, DevLog* log, const Bind* binds,
                               void* dst, uint64_t rb, const int64_t* idx, const void* src,
                               uint64_t n, uint32_t w, unsigned long long seq, int logon,
                               void* scratch, const DevInfo& d, hipStream_t s, bool finish = true,
@@ -97,10 +112,14 @@ hipError_t launch_rows_fix(int op, const DevTable& t, DevLog* log, const Redirec
 
 // After a guarded row kernel: folds the launch's denial count into the log and records the
 // smallest key if the log is empty.
-hipError_t launch_fault_finish(const DevTable& t, DevLog* log, const FaultSite& f,
+hipError_t launch_fault_finish(const GuardTab& t, DevLog* log, const FaultSite& f,
                                unsigned long long seq, hipStream_t s);
 FaultSite rows_fault_site(uint32_t op, uint32_t w, uint32_t row_operand, uint64_t rb, uint64_t ki,
                           const void* idx, const void* cont, const void* rowp);
+// The finishing arguments of a launch of `grid` workgroups: fused when the table is in the arguments
+// and the launch is small enough for its workgroups to count themselves.
+FinishArgs finish_args(const GuardTab& t, const FaultSite& f, unsigned long long seq, uint64_t grid,
+                       bool wanted);
 
 // ---- batched multi-client launch (device images of the public request/result layouts) ----
 struct BatchReq {

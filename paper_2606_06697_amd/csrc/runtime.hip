@@ -3,7 +3,7 @@
 // A handle keeps the allocation table (AgileOS Section V-A/V-C: base and live size of every
 // range, plus its kind from the Table I layout) as a sorted host mirror with stable ids, and a
 // device image rebuilt from it when the table changed. The image is uploaded lazily by the next
-// launch, on that launch's stream, after every other stream that used the handle has been made
+// launch that reads it, on that launch's stream, after every other stream that used the handle has been made
 // to wait for its earlier work; the pinned staging buffer is reused only after its previous
 // upload completed. Guarded calls take consecutive sequence numbers (the first-fault order).
 #include <algorithm>
@@ -38,12 +38,7 @@ constexpr int32_t MAX_ID = (1 << 30) - 1;
 
 // One device copy of the table image (layout below) and its upload state.
 struct Image {
-    uint64_t* split64 = nullptr;
-    uint32_t* split32 = nullptr;
-    PairRec* rec = nullptr;
-    uint32_t* radix = nullptr;
-    uint4* nrec = nullptr;
-    uint8_t* backed = nullptr;       // per bucket: bit 0 first range backed, bit 1 second
+    uint8_t* dev = nullptr;
     void* stage = nullptr;           // pinned staging the upload copies from
     hipEvent_t ready = nullptr;      // recorded after the upload into this image
     hipStream_t ready_stream = nullptr;
@@ -140,22 +135,16 @@ struct agile_rt {
     StreamScratch sa;  // sort scratch of the scatter-add (grown on demand)
 };
 
-// Image layout: split64 | split32 | (64-byte aligned) rec | radix
-static size_t rec_offset(uint32_t cap_nb) {
-    return (((size_t)cap_nb * 12 + 63) / 64) * 64;
-}
-static size_t radix_offset(uint32_t cap_nb) {
-    return rec_offset(cap_nb) + (size_t)cap_nb * sizeof(PairRec);
-}
-static size_t nrec_offset(uint32_t cap_nb) {
-    return radix_offset(cap_nb) + (((size_t)MAX_RADIX * 4 + 63) / 64) * 64;
-}
-static size_t backed_offset(uint32_t cap_nb) {
-    return nrec_offset(cap_nb) + (size_t)cap_nb * 16;
-}
-static size_t image_bytes(uint32_t cap_nb) {
-    return backed_offset(cap_nb) + (((size_t)cap_nb + 63) / 64) * 64;
-}
+// Image layout for nb buckets, the same on the device and in the staging buffer, so that an upload is
+// one copy: split64 | rec | split32 | backed | radix | nrec (each 64-byte aligned; nrec follows the
+// radix entries in use).
+static size_t up64(size_t x) { return (x + 63) & ~(size_t)63; }
+static size_t rec_offset(size_t nb) { return up64(nb * 8); }
+static size_t split32_offset(size_t nb) { return rec_offset(nb) + nb * sizeof(PairRec); }
+static size_t backed_offset(size_t nb) { return up64(split32_offset(nb) + nb * 4); }
+static size_t radix_offset(size_t nb) { return up64(backed_offset(nb) + nb); }
+static size_t nrec_offset(size_t nb, size_t nr) { return up64(radix_offset(nb) + (nr + 1) * 4); }
+static size_t image_bytes(size_t cap_nb) { return nrec_offset(cap_nb, MAX_RADIX) + cap_nb * 16; }
 
 static uint32_t bitlen(uint64_t x) {
     uint32_t b = 0;
@@ -299,11 +288,10 @@ static int upload(agile_rt* rt, hipStream_t s) {
     const uint32_t nb = (n + 1) / 2;
     uint8_t* h = static_cast<uint8_t*>(im.stage);
     uint64_t* s64 = reinterpret_cast<uint64_t*>(h);
-    uint32_t* s32 = reinterpret_cast<uint32_t*>(h + (size_t)rt->cap_nb * 8);
-    PairRec* rec = reinterpret_cast<PairRec*>(h + rec_offset(rt->cap_nb));
-    uint32_t* radix = reinterpret_cast<uint32_t*>(h + radix_offset(rt->cap_nb));
-    uint32_t* nrec = reinterpret_cast<uint32_t*>(h + nrec_offset(rt->cap_nb));
-    uint8_t* bk = h + backed_offset(rt->cap_nb);
+    PairRec* rec = reinterpret_cast<PairRec*>(h + rec_offset(nb));
+    uint32_t* s32 = reinterpret_cast<uint32_t*>(h + split32_offset(nb));
+    uint8_t* bk = h + backed_offset(nb);
+    uint32_t* radix = reinterpret_cast<uint32_t*>(h + radix_offset(nb));
     const auto& E = rt->entries;
     for (uint32_t b = 0; b < nb; ++b) {
         const Entry& e0 = E[2 * b];
@@ -325,11 +313,11 @@ static int upload(agile_rt* rt, hipStream_t s) {
         rec[b] = r;
     }
     DevTable t{};
-    t.split64 = im.split64;
-    t.split32 = im.split32;
-    t.rec = im.rec;
-    t.radix = im.radix;
-    t.backed = im.backed;
+    t.split64 = reinterpret_cast<const uint64_t*>(im.dev);
+    t.rec = reinterpret_cast<const PairRec*>(im.dev + rec_offset(nb));
+    t.split32 = reinterpret_cast<const uint32_t*>(im.dev + split32_offset(nb));
+    t.backed = im.dev + backed_offset(nb);
+    t.radix = reinterpret_cast<const uint32_t*>(im.dev + radix_offset(nb));
     t.nb = nb;
     t.compressed = 0;
     if (nb > 0) {
@@ -348,8 +336,9 @@ static int upload(agile_rt* rt, hipStream_t s) {
         }
     }
     search_geometry(t, s64, radix, std::min(rt->lds_budget, rt->info.lds_per_block), rt->min_lift);
-    t.nrec = im.nrec;
-    if (!rt->wide_only) build_narrow(t, s64, rec, nrec);
+    const size_t o_nrec = nrec_offset(nb, t.nr);
+    t.nrec = reinterpret_cast<const uint4*>(im.dev + o_nrec);
+    if (!rt->wide_only) build_narrow(t, s64, rec, reinterpret_cast<uint32_t*>(h + o_nrec));
     // the last readers of image x
     for (hipEvent_t e : im.retired)
         if (hipStreamWaitEvent(s, e, 0) != hipSuccess) return AGILE_EDEVICE;
@@ -364,22 +353,8 @@ static int upload(agile_rt* rt, hipStream_t s) {
         if (hipEventRecord(ev, o) != hipSuccess) return AGILE_EDEVICE;
     }
     rt->streams_used.clear();
-    if (nb > 0) {
-        if (hipMemcpyAsync(im.split64, s64, (size_t)nb * 8, hipMemcpyHostToDevice, s) != hipSuccess)
-            return AGILE_EDEVICE;
-        if (t.compressed &&
-            hipMemcpyAsync(im.split32, s32, (size_t)nb * 4, hipMemcpyHostToDevice, s) != hipSuccess)
-            return AGILE_EDEVICE;
-        if (hipMemcpyAsync(im.rec, rec, (size_t)nb * sizeof(PairRec), hipMemcpyHostToDevice, s) !=
-                hipSuccess ||
-            hipMemcpyAsync(im.backed, bk, nb, hipMemcpyHostToDevice, s) != hipSuccess)
-            return AGILE_EDEVICE;
-    }
-    if (t.narrow &&
-        hipMemcpyAsync(im.nrec, nrec, (size_t)nb * 16, hipMemcpyHostToDevice, s) != hipSuccess)
-        return AGILE_EDEVICE;
-    if (hipMemcpyAsync(im.radix, radix, (size_t)(t.nr + 1) * 4, hipMemcpyHostToDevice, s) !=
-            hipSuccess ||
+    const size_t bytes = t.narrow ? o_nrec + (size_t)nb * 16 : radix_offset(nb) + ((size_t)t.nr + 1) * 4;
+    if (hipMemcpyAsync(im.dev, h, bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipEventRecord(im.ready, s) != hipSuccess)
         return AGILE_EDEVICE;
     im.uploaded = true;
@@ -503,12 +478,7 @@ int agile_rt_create(agile_rt** out, uint32_t capacity, int device) {
     for (int k = 0; k < 2; ++k) {
         uint8_t* d = static_cast<uint8_t*>(rt->dmem) + k * img_bytes;
         Image& im = rt->img[k];
-        im.split64 = reinterpret_cast<uint64_t*>(d);
-        im.split32 = reinterpret_cast<uint32_t*>(d + (size_t)rt->cap_nb * 8);
-        im.rec = reinterpret_cast<PairRec*>(d + rec_offset(rt->cap_nb));
-        im.radix = reinterpret_cast<uint32_t*>(d + radix_offset(rt->cap_nb));
-        im.nrec = reinterpret_cast<uint4*>(d + nrec_offset(rt->cap_nb));
-        im.backed = d + backed_offset(rt->cap_nb);
+        im.dev = d;
         if (hipHostMalloc(&im.stage, rt->stage_bytes, hipHostMallocDefault) != hipSuccess ||
             hipEventCreateWithFlags(&im.ready, hipEventDisableTiming) != hipSuccess) {
             agile_rt_destroy(rt);
@@ -760,6 +730,60 @@ static Bind host_bind(const agile_rt* rt, uint64_t p) {
     return Bind{0, 0};
 }
 
+// Reason of a denied access at address a, from the host copy of the table (as reason_lane).
+static void host_reason(const agile_rt* rt, uint64_t a, uint32_t w, uint32_t* v, int32_t* owner) {
+    const auto& e = rt->entries;
+    auto it = std::upper_bound(e.begin(), e.end(), a,
+                               [](uint64_t x, const Entry& y) { return x < y.base; });
+    *v = AGILE_V_UNMAPPED;
+    *owner = -1;
+    if (it == e.begin() || a >= (--it)->end) return;
+    *owner = it->id;
+    *v = it->kind != AGILE_KIND_USER ? AGILE_V_PROTECTED
+                                     : (w <= it->end - a ? AGILE_V_CROSS_ALLOC : AGILE_V_STRADDLE);
+}
+
+// The denials of a copy or triad of n elements of width w: operand j, at ptr[j], is allowed its first
+// K[j] elements; the first denial is the smallest (element, operand).
+static StreamFault stream_fault(const agile_rt* rt, int policy, uint32_t op, uint32_t w, uint64_t n,
+                                const uint64_t* ptr, const uint64_t* K, uint32_t operands) {
+    StreamFault f{};
+    if (!log_on(policy)) return f;
+    for (uint32_t j = 0; j < operands; ++j) {
+        f.count += n - K[j];
+        if (K[j] < K[f.operand]) f.operand = j;
+    }
+    if (!f.count) return f;
+    f.elem = K[f.operand];
+    f.addr = ptr[f.operand] + f.elem * w;
+    f.width = w;
+    f.op = op;
+    host_reason(rt, f.addr, w, &f.verdict, &f.owner);
+    return f;
+}
+
+// Brings the image up to date for a guarded call, if the call reads it: the redirecting policies do,
+// and row kernels on a table that does not fit their arguments. The others need no upload (a training
+// step changes its table at every call: two uploads of about 28 us each were more than its kernels).
+static int prepare_guarded(agile_rt* rt, int policy, bool rows, hipStream_t s) {
+    if (redirecting(policy) || (rows && rt->entries.size() > INLINE_RANGES)) return prepare(rt, s);
+    return AGILE_OK;
+}
+
+// Where a row kernel looks up its first denial; inl is filled when the table fits.
+static GuardTab guard_tab(const agile_rt* rt, InlineTab* inl) {
+    const auto& e = rt->entries;
+    if (e.size() > INLINE_RANGES) return GuardTab{&rt->tab, nullptr};
+    inl->n = (uint32_t)e.size();
+    inl->pad = 0;
+    for (size_t k = 0; k < e.size(); ++k) {
+        inl->base[k] = e[k].base;
+        inl->end[k] = e[k].end;
+        inl->meta[k] = ((uint32_t)e[k].id << 2) | e[k].kind;
+    }
+    return GuardTab{&rt->tab, inl};
+}
+
 int agile_guarded_copy(agile_rt* rt, void* d_dst, const void* d_src, uint64_t nbytes, int policy,
                        void* stream) {
     if (!rt || !policy_ok(policy)) return AGILE_EINVAL;
@@ -769,19 +793,19 @@ int agile_guarded_copy(agile_rt* rt, void* d_dst, const void* d_src, uint64_t nb
     DeviceGuard dg(rt->device);
     if (!dg.ok) return AGILE_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = prepare(rt, s);
+    int rc = prepare_guarded(rt, policy, false, s);
     if (rc != AGILE_OK) return rc;
     rc = trap_begin(rt, policy, s);
     if (rc != AGILE_OK) return rc;
     const unsigned long long seq = rt->seq++;
     const Bind b[2] = {host_bind(rt, (uint64_t)d_src), host_bind(rt, (uint64_t)d_dst)};
-    if (launch_copy(true, rt->tab, rt->d_log, b, d_dst, d_src, nbytes, seq,
-                    log_on(policy), rt->info, s) != hipSuccess)
+    const uint64_t p[2] = {(uint64_t)d_src, (uint64_t)d_dst};
+    const uint64_t K[2] = {clip_prefix(b[0], p[0], nbytes, 1), clip_prefix(b[1], p[1], nbytes, 1)};
+    const StreamFault f = stream_fault(rt, policy, AGILE_OP_COPY, 1, nbytes, p, K, 2);
+    if (launch_copy(true, f, rt->d_log, b, d_dst, d_src, nbytes, seq, s) != hipSuccess)
         return AGILE_EDEVICE;
-    if (redirecting(policy) &&
-        launch_copy_fix(rt->tab, rd, b[0], b[1], d_dst, d_src, nbytes,
-                        clip_prefix(b[0], (uint64_t)d_src, nbytes, 1),
-                        clip_prefix(b[1], (uint64_t)d_dst, nbytes, 1), rt->info, s) != hipSuccess)
+    if (redirecting(policy) && launch_copy_fix(rt->tab, rd, b[0], b[1], d_dst, d_src, nbytes, K[0], K[1],
+                                               rt->info, s) != hipSuccess)
         return AGILE_EDEVICE;
     return trap_end(rt, policy, s);
 }
@@ -797,21 +821,20 @@ int agile_guarded_triad(agile_rt* rt, float* d_a, const float* d_b, const float*
     DeviceGuard dg(rt->device);
     if (!dg.ok) return AGILE_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = prepare(rt, s);
+    int rc = prepare_guarded(rt, policy, false, s);
     if (rc != AGILE_OK) return rc;
     rc = trap_begin(rt, policy, s);
     if (rc != AGILE_OK) return rc;
     const unsigned long long seq = rt->seq++;
-    const Bind b[3] = {host_bind(rt, (uint64_t)d_b), host_bind(rt, (uint64_t)d_c),
-                       host_bind(rt, (uint64_t)d_a)};
-    if (launch_triad(true, rt->tab, rt->d_log, b, d_a, d_b, d_c, s_, n, seq,
-                     log_on(policy), rt->info, s) != hipSuccess)
+    const uint64_t p[3] = {(uint64_t)d_b, (uint64_t)d_c, (uint64_t)d_a};
+    const Bind b[3] = {host_bind(rt, p[0]), host_bind(rt, p[1]), host_bind(rt, p[2])};
+    const uint64_t K[3] = {clip_prefix(b[0], p[0], n, 4), clip_prefix(b[1], p[1], n, 4),
+                           clip_prefix(b[2], p[2], n, 4)};
+    const StreamFault f = stream_fault(rt, policy, AGILE_OP_TRIAD, 4, n, p, K, 3);
+    if (launch_triad(true, f, rt->d_log, b, d_a, d_b, d_c, s_, n, seq, s) != hipSuccess)
         return AGILE_EDEVICE;
-    if (redirecting(policy) &&
-        launch_triad_fix(rt->tab, rd, b[2], b[0], b[1], d_a, d_b, d_c, s_, n,
-                         clip_prefix(b[2], (uint64_t)d_a, n, 4),
-                         clip_prefix(b[0], (uint64_t)d_b, n, 4),
-                         clip_prefix(b[1], (uint64_t)d_c, n, 4), rt->info, s) != hipSuccess)
+    if (redirecting(policy) && launch_triad_fix(rt->tab, rd, b[2], b[0], b[1], d_a, d_b, d_c, s_, n, K[2],
+                                                K[0], K[1], rt->info, s) != hipSuccess)
         return AGILE_EDEVICE;
     return trap_end(rt, policy, s);
 }
@@ -840,28 +863,30 @@ int agile_guarded_gather(agile_rt* rt, void* d_out, const void* d_table, uint64_
     DeviceGuard dg(rt->device);
     if (!dg.ok) return AGILE_EDEVICE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    rc = prepare(rt, s);
+    rc = prepare_guarded(rt, policy, true, s);
     if (rc != AGILE_OK) return rc;
     rc = trap_begin(rt, policy, s);
     if (rc != AGILE_OK) return rc;
     const unsigned long long seq = rt->seq++;
+    InlineTab inl;
+    const GuardTab tab = guard_tab(rt, &inl);
     const Bind b[3] = {host_bind(rt, (uint64_t)d_idx), host_bind(rt, (uint64_t)d_table),
                        host_bind(rt, (uint64_t)d_out)};
     if (redirecting(policy)) {
         // the guarded kernel runs the rows whose index is readable, the redirect pass the rest
         const RowsGuard full = rows_guard(b[0], b[2], b[1], (uint64_t)d_idx, (uint64_t)d_out,
                                           (uint64_t)d_table, n, row_bytes, w);
-        if (launch_gather(true, rt->tab, rt->d_log, b, d_out, d_table, row_bytes, d_idx, full.ki,
+        if (launch_gather(true, tab, rt->d_log, b, d_out, d_table, row_bytes, d_idx, full.ki,
                           w, seq, 1, rt->info, s, false) != hipSuccess ||
             launch_rows_fix(0, rt->tab, rt->d_log, rd, RowBinds{b[0], b[2], b[1]}, d_out,
                             const_cast<void*>(d_table),
                             row_bytes, d_idx, n, full, w, rt->info, s) != hipSuccess ||
-            launch_fault_finish(rt->tab, rt->d_log,
+            launch_fault_finish(tab, rt->d_log,
                                 rows_fault_site(AGILE_OP_GATHER, w, 1, row_bytes, full.ki, d_idx,
                                                 d_out, d_table),
                                 seq, s) != hipSuccess)
             return AGILE_EDEVICE;
-    } else if (launch_gather(true, rt->tab, rt->d_log, b, d_out, d_table, row_bytes, d_idx, n, w,
+    } else if (launch_gather(true, tab, rt->d_log, b, d_out, d_table, row_bytes, d_idx, n, w,
                              seq, log_on(policy), rt->info, s) != hipSuccess) {
         return AGILE_EDEVICE;
     }
@@ -891,28 +916,30 @@ static int scatter_impl(agile_rt* rt, void* d_dst, uint64_t row_bytes, const int
         fixed = noalloc_scratch(rt->device);
         if (!fixed) return AGILE_EDEVICE;
     }
-    rc = prepare(rt, s);
+    rc = prepare_guarded(rt, policy, true, s);
     if (rc != AGILE_OK) return rc;
     rc = trap_begin(rt, policy, s);
     if (rc != AGILE_OK) return rc;
     const unsigned long long seq = rt->seq++;
+    InlineTab inl;
+    const GuardTab tab = guard_tab(rt, &inl);
     const Bind b[3] = {host_bind(rt, (uint64_t)d_idx), host_bind(rt, (uint64_t)d_src),
                        host_bind(rt, (uint64_t)d_dst)};
     void* scr = !sort ? nullptr : (noalloc ? fixed : rt->sa.get(scatter_add_scratch_bytes(n), s));
     if (redirecting(policy)) {
         const RowsGuard full = rows_guard(b[0], b[1], b[2], (uint64_t)d_idx, (uint64_t)d_src,
                                           (uint64_t)d_dst, n, row_bytes, w);
-        if (launch_scatter(true, rt->tab, rt->d_log, b, d_dst, row_bytes, d_idx, d_src, full.ki, w,
+        if (launch_scatter(true, tab, rt->d_log, b, d_dst, row_bytes, d_idx, d_src, full.ki, w,
                            accumulate, seq, 1, scr, rt->info, s, false) != hipSuccess ||
             launch_rows_fix(accumulate ? 2 : 1, rt->tab, rt->d_log, rd,
                             RowBinds{b[0], b[1], b[2]}, const_cast<void*>(d_src), d_dst,
                             row_bytes, d_idx, n, full, w, rt->info, s) != hipSuccess ||
-            launch_fault_finish(rt->tab, rt->d_log,
+            launch_fault_finish(tab, rt->d_log,
                                 rows_fault_site(accumulate ? AGILE_OP_SCATTER_ADD : AGILE_OP_SCATTER,
                                                 w, 2, row_bytes, full.ki, d_idx, d_src, d_dst),
                                 seq, s) != hipSuccess)
             return AGILE_EDEVICE;
-    } else if (launch_scatter(true, rt->tab, rt->d_log, b, d_dst, row_bytes, d_idx, d_src, n, w,
+    } else if (launch_scatter(true, tab, rt->d_log, b, d_dst, row_bytes, d_idx, d_src, n, w,
                               accumulate, seq, log_on(policy), scr, rt->info, s) != hipSuccess) {
         return AGILE_EDEVICE;
     }
@@ -1169,7 +1196,7 @@ static DevInfo current_info() {
 
 int agile_unguarded_copy(void* d_dst, const void* d_src, uint64_t nbytes, void* stream) {
     if (nbytes && (!d_dst || !d_src)) return AGILE_EINVAL;
-    return launch_copy(false, DevTable{}, nullptr, nullptr, d_dst, d_src, nbytes, 0, 0, current_info(),
+    return launch_copy(false, StreamFault{}, nullptr, nullptr, d_dst, d_src, nbytes, 0,
                        static_cast<hipStream_t>(stream)) == hipSuccess
                ? AGILE_OK
                : AGILE_EDEVICE;
@@ -1179,7 +1206,7 @@ int agile_unguarded_triad(float* d_a, const float* d_b, const float* d_c, float 
                           void* stream) {
     if (n && (!d_a || !d_b || !d_c)) return AGILE_EINVAL;
     if (((uint64_t)d_a | (uint64_t)d_b | (uint64_t)d_c) & 3) return AGILE_EINVAL;
-    return launch_triad(false, DevTable{}, nullptr, nullptr, d_a, d_b, d_c, s_, n, 0, 0, current_info(),
+    return launch_triad(false, StreamFault{}, nullptr, nullptr, d_a, d_b, d_c, s_, n, 0,
                         static_cast<hipStream_t>(stream)) == hipSuccess
                ? AGILE_OK
                : AGILE_EDEVICE;
@@ -1191,7 +1218,7 @@ int agile_unguarded_gather(void* d_out, const void* d_table, uint64_t row_bytes,
     int rc = rows_args_ok(row_bytes, n, dtype, d_out, d_table, &w);
     if (rc != AGILE_OK) return rc;
     if (n && (!d_out || !d_table || !d_idx)) return AGILE_EINVAL;
-    return launch_gather(false, DevTable{}, nullptr, nullptr, d_out, d_table, row_bytes, d_idx, n, w, 0, 0,
+    return launch_gather(false, GuardTab{}, nullptr, nullptr, d_out, d_table, row_bytes, d_idx, n, w, 0, 0,
                          current_info(), static_cast<hipStream_t>(stream)) == hipSuccess
                ? AGILE_OK
                : AGILE_EDEVICE;
@@ -1216,7 +1243,7 @@ int agile_unguarded_scatter(void* d_dst, uint64_t row_bytes, const int64_t* d_id
         if ((size_t)dev >= per_dev.size()) per_dev.resize(dev + 1);
         scr = per_dev[dev].get(scatter_add_scratch_bytes(n), static_cast<hipStream_t>(stream));
     }
-    return launch_scatter(false, DevTable{}, nullptr, nullptr, d_dst, row_bytes, d_idx, d_src, n, w,
+    return launch_scatter(false, GuardTab{}, nullptr, nullptr, d_dst, row_bytes, d_idx, d_src, n, w,
                           accumulate, 0, 0, scr, current_info(),
                           static_cast<hipStream_t>(stream)) == hipSuccess
                ? AGILE_OK

@@ -165,8 +165,16 @@ def _ptr(x) -> int:
     return int(x) & ((1 << 64) - 1)
 
 
+# the handle of this thread's current stream, without the stream object that current_stream() makes
+# (0.3 us a call instead of 2.8, and of 14 in an autograd thread)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(s):
     if s is None:
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(s, torch.cuda.Stream):
         return s.cuda_stream

@@ -325,3 +325,68 @@ def test_elements_straddling_an_allocation_end():
             log_matches(tw, ol, f"scatter straddle D={D} w={w} acc={acc}")
         ar.write(I[0], idx)
     tw.close()
+
+
+@pytest.mark.parametrize("n_ranges", [8, 63, 64, 65, 300])
+def test_first_denial_in_tables_around_the_inline_limit(n_ranges):
+    """A table of at most 64 ranges travels in a launch's arguments, a larger one is uploaded: every
+    operation's record names the range (of any place in the table, its last bytes, a hole) that its
+    first denied access met, and the call after a table change sees the change."""
+    need_gpu()
+    ar = Arena(ARENA, n_ranges)
+    tw = Twin(n_ranges)
+    for k, (lo, hi, kind) in REG.items():
+        tw.insert(ar.addr(lo), hi - lo, kind)
+    rng = random.Random(n_ranges)
+    far = []
+    for k in range(n_ranges - len(REG)):
+        # alternately below and above the arena's addresses
+        base = (1 << 30) + k * 16384 if k % 2 else (1 << 47) + (k << 20)
+        kind = rng.choice([0, 1, 2])
+        far.append((tw.insert(base, 4096 + 8 * k, kind), base, 4096 + 8 * k, kind))
+    ol = G.FaultLog()
+    lo_c, lo_o, lo_i = (REG[k][0] for k in ("C", "O", "I"))
+    for trial in range(24):
+        if far:
+            rid, base, size, kind = far[rng.randrange(len(far))]
+            target = base + rng.choice([0, 4, size // 2 // 4 * 4, size - 4, size, size + 4096])
+        else:
+            target = ar.addr(REG["P"][0])
+        n = rng.choice([1, 70, 500])
+        idx = np.arange(n, dtype=np.int64) % 64
+        idx[rng.randrange(n)] = (target - ar.addr(lo_c)) // 4
+        ar.write(lo_i, idx)
+        args = (ar.addr(lo_o), ar.addr(lo_c), 4, ar.addr(lo_i), n)
+        tw.g.agile_guarded_gather(tw.h, *args)
+        G.gather_vec(tw.ot, ar.mem, ol, tw.next_seq(), *args, 4)
+        ar.check(f"gather, {n_ranges} ranges, trial {trial}")
+        log_matches(tw, ol, f"gather, {n_ranges} ranges, trial {trial}")
+        # (with the source before the destination, scatter's and scatter-add's operand order)
+        for accumulate in (0, 1):
+            ar.write(lo_o, np.arange(n, dtype=np.float32))
+            args = (ar.addr(lo_c), 4, ar.addr(lo_i), ar.addr(lo_o), n)
+            idx2 = np.unique(idx)
+            ar.write(lo_i, np.resize(idx2, n) if accumulate else idx2)
+            m = n if accumulate else idx2.size
+            ar.write(lo_c, np.zeros(256, np.float32))
+            tw.g.agile_guarded_scatter(tw.h, *args[:4], m, 0, accumulate)
+            G.scatter_vec(tw.ot, ar.mem, ol, tw.next_seq(), *args[:4], m, 4, bool(accumulate))
+            ar.check(f"scatter {accumulate}, {n_ranges} ranges, trial {trial}")
+            log_matches(tw, ol, f"scatter {accumulate}, {n_ranges} ranges, trial {trial}")
+        # pointer arguments: never into a USER range without memory behind it (it would be allowed)
+        closed = [b + rng.choice([0, 8, s - 4]) for _, b, s, kind in far if kind != 0]
+        target = rng.choice(closed) if closed else ar.addr(REG["P"][0])
+        src, dst = rng.choice([(target, ar.addr(lo_o)), (ar.addr(lo_c), target),
+                               (ar.addr(lo_c + 0x7FF0), ar.addr(lo_o))])
+        tw.g.agile_guarded_copy(tw.h, dst, src, 64)
+        G.copy_vec(tw.ot, ar.mem, ol, tw.next_seq(), dst, src, 64)
+        log_matches(tw, ol, f"copy, {n_ranges} ranges, trial {trial}")
+        tri = [ar.addr(lo_o), ar.addr(lo_c), ar.addr(REG["A"][0])]
+        tri[rng.randrange(3)] = target & ~3
+        tw.g.agile_guarded_triad(tw.h, *tri, 2.0, 40)
+        G.triad_vec(tw.ot, ar.mem, ol, tw.next_seq(), *tri, 2.0, 40)
+        log_matches(tw, ol, f"triad, {n_ranges} ranges, trial {trial}")
+        if far and trial % 3 == 2:
+            k = rng.randrange(len(far))
+            tw.remove(far.pop(k)[0])
+    tw.close()
