@@ -14,29 +14,12 @@
 
 namespace agile {
 
-constexpr int SBLOCK = 128;
-constexpr int SUNROLL = 1;  // vectors per thread per pass
+constexpr int CBLOCK = 256, SBLOCK = 128;  // threads of the copy and the triad
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(1)));  // a vector load at any address
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <int VW>
-struct VecT;
-template <>
-struct VecT<16> {
-    using T = u32x4;
-    static __device__ __forceinline__ T zero() { return T{0u, 0u, 0u, 0u}; }
-};
-template <>
-struct VecT<4> {
-    using T = uint32_t;
-    static __device__ __forceinline__ T zero() { return 0u; }
-};
-template <>
-struct VecT<1> {
-    using T = uint8_t;
-    static __device__ __forceinline__ T zero() { return 0; }
-};
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 
 __device__ __forceinline__ void log_stream_fault(const StreamFault& f, DevLog* log,
                                                  unsigned long long seq) {
@@ -54,65 +37,39 @@ __device__ inline void copy_bytes_slow(uint8_t* dst, const uint8_t* src, uint64_
     }
 }
 
-// Ks, Kd: allowed byte prefixes of src and dst (n and n for the unguarded twin).
-template <bool GUARD, int VW>
-__global__ __launch_bounds__(SBLOCK) void k_copy(StreamFault f, DevLog* log,
+// Ks, Kd: allowed byte prefixes of src and dst (n and n for the unguarded twin). The first `up` bytes
+// bring the destination to a 16-byte boundary; from there one vector per thread, stored aligned and
+// loaded from wherever the source lies. 64 MiB: 22 us, from an odd address 24 us (126 with the one byte
+// per thread that such a pointer took before), from one 4 bytes off 23 us (42 with 4-byte words).
+template <bool GUARD>
+__global__ __launch_bounds__(CBLOCK) void k_copy(StreamFault f, DevLog* log,
                                                   uint8_t* __restrict__ dst,
                                                   const uint8_t* __restrict__ src, uint64_t n,
                                                   uint64_t Ks, uint64_t Kd,
                                                   unsigned long long seq) {
-    using V = typename VecT<VW>::T;
     const uint64_t K = Ks < Kd ? Ks : Kd;
-    const uint64_t nv = n / VW;
-    const uint64_t tid = (uint64_t)blockIdx.x * SBLOCK + threadIdx.x;
-    const uint64_t stride = (uint64_t)gridDim.x * SBLOCK;
-    const V* sv = reinterpret_cast<const V*>(src);
-    V* dv = reinterpret_cast<V*>(dst);
-    // Main loop: every vector of the pass lies inside both allowed prefixes (they are prefixes,
-    // so one scalar bound covers the pass), so the loads issue unconditionally, back to back.
-    const uint64_t lim = GUARD ? (K / VW < nv ? K / VW : nv) : nv;
-    uint64_t v0 = tid;
-    for (; v0 + (SUNROLL - 1) * stride < lim; v0 += SUNROLL * stride) {
-        V x[SUNROLL];
-#pragma unroll
-        for (int u = 0; u < SUNROLL; ++u) x[u] = __builtin_nontemporal_load(sv + v0 + u * stride);
-#pragma unroll
-        for (int u = 0; u < SUNROLL; ++u) __builtin_nontemporal_store(x[u], dv + v0 + u * stride);
-    }
-    // Last pass of this thread: per-vector bounds, and the guard's per-element path.
-    for (; v0 < nv; v0 += SUNROLL * stride) {
-        V x[SUNROLL];
-        bool m[SUNROLL];
-#pragma unroll
-        for (int u = 0; u < SUNROLL; ++u) {
-            const uint64_t v = v0 + u * stride;
-            m[u] = v < nv && (!GUARD || (v + 1) * VW <= K);
-            if (m[u]) x[u] = __builtin_nontemporal_load(sv + v);
-        }
-#pragma unroll
-        for (int u = 0; u < SUNROLL; ++u)
-            if (m[u]) __builtin_nontemporal_store(x[u], dv + (v0 + u * stride));
-        if (GUARD) {
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u) {
-                const uint64_t v = v0 + u * stride;
-                if (v < nv && !m[u]) {
-                    const uint64_t b0 = v * VW;
-                    if (b0 >= Ks && b0 + VW <= Kd) {
-                        dv[v] = VecT<VW>::zero();
-                    } else if (b0 < Kd) {
-                        copy_bytes_slow(dst, src, b0, b0 + VW, Ks, Kd);
-                    }
-                }
-            }
+    const uint64_t tid = (uint64_t)blockIdx.x * CBLOCK + threadIdx.x;
+    const uint64_t stride = (uint64_t)gridDim.x * CBLOCK;
+    const uint64_t off = (0 - (uint64_t)dst) & 15, up = off < n ? off : n;
+    const uint64_t nv = (n - up) / 16;
+    const u32x4_any* sv = reinterpret_cast<const u32x4_any*>(src + up);
+    u32x4* dv = reinterpret_cast<u32x4*>(dst + up);
+    // vectors inside both allowed prefixes (they are prefixes, so one scalar bound covers them)
+    const uint64_t in = K > up ? (K - up) / 16 : 0, lim = GUARD ? (in < nv ? in : nv) : nv;
+    uint64_t v = tid;
+    for (; v < lim; v += stride) __builtin_nontemporal_store(__builtin_nontemporal_load(sv + v), dv + v);
+    // the guard's per-element path
+    if (GUARD) {
+        for (; v < nv; v += stride) {
+            const uint64_t b0 = up + v * 16;
+            if (b0 >= Ks && b0 + 16 <= Kd) dv[v] = u32x4{0u, 0u, 0u, 0u};
+            else if (b0 < Kd) copy_bytes_slow(dst, src, b0, b0 + 16, Ks, Kd);
         }
     }
-    // tail bytes
-    const uint64_t tb = nv * VW + tid;
-    if (tb < n) {
-        if (!GUARD) dst[tb] = src[tb];
-        else copy_bytes_slow(dst, src, tb, tb + 1, Ks, Kd);
-    }
+    // bytes before the first vector and after the last
+    if (tid < up) copy_bytes_slow(dst, src, tid, tid + 1, Ks, Kd);
+    const uint64_t tb = up + nv * 16 + tid;
+    if (tb < n) copy_bytes_slow(dst, src, tb, tb + 1, Ks, Kd);
     if (GUARD) log_stream_fault(f, log, seq);
 }
 
@@ -130,156 +87,84 @@ __device__ inline void triad_slow(float* a, const float* b, const float* c, floa
     }
 }
 
-// Ka, Kb, Kc: allowed element prefixes of the three operands (all n for the unguarded twin).
-template <bool GUARD, int VE>
+// Ka, Kb, Kc: allowed element prefixes of the three operands (all n for the unguarded twin). The
+// first `up` elements bring `a` to a 16-byte boundary; from there one vector per thread, b and c loaded
+// from wherever they lie (2^25 elements: 61.5 us, one element off 67 us; with single elements 94 us).
+template <bool GUARD>
 __global__ __launch_bounds__(SBLOCK) void k_triad(StreamFault f, DevLog* log, float* a,
                                                    const float* b, const float* c, float s,
                                                    uint64_t n, uint64_t Ka, uint64_t Kb,
                                                    uint64_t Kc, unsigned long long seq) {
     uint64_t K = Ka < Kb ? Ka : Kb;
     K = K < Kc ? K : Kc;
-    const uint64_t nv = n / VE;
     const uint64_t tid = (uint64_t)blockIdx.x * SBLOCK + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * SBLOCK;
-    // Main loop: every vector of the pass is inside all three allowed prefixes.
-    const uint64_t lim = GUARD ? (K / VE < nv ? K / VE : nv) : nv;
-    uint64_t v0 = tid;
-    if (VE == 4) {
-        const f32x4* b4 = reinterpret_cast<const f32x4*>(b);
-        const f32x4* c4 = reinterpret_cast<const f32x4*>(c);
-        f32x4* a4 = reinterpret_cast<f32x4*>(a);
-        for (; v0 + (SUNROLL - 1) * stride < lim; v0 += SUNROLL * stride) {
-            f32x4 xb[SUNROLL], xc[SUNROLL];
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u) {
-                xb[u] = __builtin_nontemporal_load(b4 + v0 + u * stride);
-                xc[u] = __builtin_nontemporal_load(c4 + v0 + u * stride);
-            }
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u) {
-                f32x4 r;
-                r.x = triad1(xb[u].x, s, xc[u].x);
-                r.y = triad1(xb[u].y, s, xc[u].y);
-                r.z = triad1(xb[u].z, s, xc[u].z);
-                r.w = triad1(xb[u].w, s, xc[u].w);
-                __builtin_nontemporal_store(r, a4 + v0 + u * stride);
-            }
-        }
+    const uint64_t off = ((0 - (uint64_t)a) & 15) / 4, up = off < n ? off : n;
+    const uint64_t nv = (n - up) / 4;
+    const f32x4_any* b4 = reinterpret_cast<const f32x4_any*>(b + up);
+    const f32x4_any* c4 = reinterpret_cast<const f32x4_any*>(c + up);
+    f32x4* a4 = reinterpret_cast<f32x4*>(a + up);
+    const uint64_t in = K > up ? (K - up) / 4 : 0, lim = GUARD ? (in < nv ? in : nv) : nv;
+    uint64_t v = tid;
+    for (; v < lim; v += stride) {
+        const f32x4 xb = __builtin_nontemporal_load(b4 + v);
+        const f32x4 xc = __builtin_nontemporal_load(c4 + v);
+        f32x4 r;
+        r.x = triad1(xb.x, s, xc.x);
+        r.y = triad1(xb.y, s, xc.y);
+        r.z = triad1(xb.z, s, xc.z);
+        r.w = triad1(xb.w, s, xc.w);
+        __builtin_nontemporal_store(r, a4 + v);
     }
-    // Last pass of this thread (and the whole range for unaligned operands).
-    for (; v0 < nv; v0 += SUNROLL * stride) {
-        bool m[SUNROLL];
-        if (VE == 4) {
-            f32x4 xb[SUNROLL], xc[SUNROLL];
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u) {
-                const uint64_t v = v0 + u * stride;
-                m[u] = v < nv && (!GUARD || (v + 1) * 4 <= K);
-                if (m[u]) {
-                    xb[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(b) + v);
-                    xc[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(c) + v);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u) {
-                if (m[u]) {
-                    f32x4 r;
-                    r.x = triad1(xb[u].x, s, xc[u].x);
-                    r.y = triad1(xb[u].y, s, xc[u].y);
-                    r.z = triad1(xb[u].z, s, xc[u].z);
-                    r.w = triad1(xb[u].w, s, xc[u].w);
-                    __builtin_nontemporal_store(r, reinterpret_cast<f32x4*>(a) + (v0 + u * stride));
-                }
-            }
-        } else {
-            float xb[SUNROLL], xc[SUNROLL];
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u) {
-                const uint64_t v = v0 + u * stride;
-                m[u] = v < nv && (!GUARD || v + 1 <= K);
-                if (m[u]) {
-                    xb[u] = b[v];
-                    xc[u] = c[v];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u)
-                if (m[u]) a[v0 + u * stride] = triad1(xb[u], s, xc[u]);
-        }
-        if (GUARD) {
-#pragma unroll
-            for (int u = 0; u < SUNROLL; ++u) {
-                const uint64_t v = v0 + u * stride;
-                if (v < nv && !m[u]) triad_slow(a, b, c, s, v * VE, v * VE + VE, Ka, Kb, Kc);
-            }
-        }
+    if (GUARD) {
+        for (; v < nv; v += stride) triad_slow(a, b, c, s, up + v * 4, up + v * 4 + 4, Ka, Kb, Kc);
     }
-    const uint64_t ti = nv * VE + tid;
+    if (tid < up) triad_slow(a, b, c, s, tid, tid + 1, Ka, Kb, Kc);
+    const uint64_t ti = up + nv * 4 + tid;
     if (ti < n) triad_slow(a, b, c, s, ti, ti + 1, Ka, Kb, Kc);
     if (GUARD) log_stream_fault(f, log, seq);
 }
 
-// One pass: as many 128-thread blocks as the vectors need, each thread one vector. Measured on
+// One pass: as many blocks as the vectors need, each thread one vector. Bound by HBM; measured on
 // MI355X for 2^28 fp32 (triad) and 1 GiB (copy): 0.492 ms and 0.339 ms, against 0.540 ms and
 // 0.382 ms with one persistent 256-thread workgroup per CU looping over 4 vectors per thread
 // per pass (the hardware's block dispatch balances the end of the launch better than a fixed
 // split), and against 0.51-0.60 ms for the triad with blocks of 64-256 threads and 2-4 vectors.
-static uint32_t stream_grid(uint64_t nv) {
-    uint64_t want = (nv + (uint64_t)SBLOCK * SUNROLL - 1) / ((uint64_t)SBLOCK * SUNROLL);
+// One vector a thread, blocks of 128 / 256 threads: 256 MiB copy 83.9 / 83.7 us, from an odd address
+// 90.2 / 89.6; triad of 2^25 61.5 / 62.8.
+static uint32_t stream_grid(uint64_t nv, uint64_t block) {
+    uint64_t want = (nv + block - 1) / block;
     const uint64_t cap = 1ull << 30;  // beyond 2^37 vectors the loop takes further passes
     if (want < 1) want = 1;
     return (uint32_t)(want < cap ? want : cap);
 }
 
-template <bool G>
-static void copy_dispatch(const StreamFault& f, DevLog* log, void* dst, const void* src, uint64_t n,
-                          uint64_t Ks, uint64_t Kd, unsigned long long seq, hipStream_t s) {
-    const uint64_t ad = (uint64_t)dst | (uint64_t)src;
-    if ((ad & 15) == 0)
-        hipLaunchKernelGGL((k_copy<G, 16>), dim3(stream_grid(n / 16)), dim3(SBLOCK), 0, s, f, log,
-                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq);
-    else if ((ad & 3) == 0)
-        hipLaunchKernelGGL((k_copy<G, 4>), dim3(stream_grid(n / 4)), dim3(SBLOCK), 0, s, f, log,
-                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq);
-    else
-        hipLaunchKernelGGL((k_copy<G, 1>), dim3(stream_grid(n)), dim3(SBLOCK), 0, s, f, log,
-                           (uint8_t*)dst, (const uint8_t*)src, n, Ks, Kd, seq);
-}
-
 hipError_t launch_copy(bool guard, const StreamFault& f, DevLog* log, const Bind* binds, void* dst,
                        const void* src, uint64_t n, unsigned long long seq, hipStream_t s) {
     if (n == 0) return hipSuccess;
+    const dim3 grid(stream_grid(n / 16, CBLOCK)), block(CBLOCK);
     if (guard)
-        copy_dispatch<true>(f, log, dst, src, n, clip_prefix(binds[0], (uint64_t)src, n, 1),
-                            clip_prefix(binds[1], (uint64_t)dst, n, 1), seq, s);
+        hipLaunchKernelGGL(k_copy<true>, grid, block, 0, s, f, log, (uint8_t*)dst, (const uint8_t*)src, n,
+                           clip_prefix(binds[0], (uint64_t)src, n, 1),
+                           clip_prefix(binds[1], (uint64_t)dst, n, 1), seq);
     else
-        copy_dispatch<false>(f, log, dst, src, n, n, n, seq, s);
+        hipLaunchKernelGGL(k_copy<false>, grid, block, 0, s, f, log, (uint8_t*)dst, (const uint8_t*)src, n,
+                           n, n, seq);
     return hipGetLastError();
-}
-
-template <bool G>
-static void triad_dispatch(const StreamFault& f, DevLog* log, float* a, const float* b, const float* c,
-                           float sc, uint64_t n, uint64_t Ka, uint64_t Kb, uint64_t Kc,
-                           unsigned long long seq, hipStream_t s) {
-    const uint64_t ad = (uint64_t)a | (uint64_t)b | (uint64_t)c;
-    if ((ad & 15) == 0)
-        hipLaunchKernelGGL((k_triad<G, 4>), dim3(stream_grid(n / 4)), dim3(SBLOCK), 0, s, f, log, a, b,
-                           c, sc, n, Ka, Kb, Kc, seq);
-    else
-        hipLaunchKernelGGL((k_triad<G, 1>), dim3(stream_grid(n)), dim3(SBLOCK), 0, s, f, log, a, b, c,
-                           sc, n, Ka, Kb, Kc, seq);
 }
 
 hipError_t launch_triad(bool guard, const StreamFault& f, DevLog* log, const Bind* binds, float* a,
                         const float* b, const float* c, float sc, uint64_t n,
                         unsigned long long seq, hipStream_t s) {
     if (n == 0) return hipSuccess;
+    const dim3 grid(stream_grid(n / 4, SBLOCK)), block(SBLOCK);
     if (guard)
-        triad_dispatch<true>(f, log, a, b, c, sc, n, clip_prefix(binds[2], (uint64_t)a, n, 4),
-                             clip_prefix(binds[0], (uint64_t)b, n, 4),
-                             clip_prefix(binds[1], (uint64_t)c, n, 4), seq, s);
+        hipLaunchKernelGGL(k_triad<true>, grid, block, 0, s, f, log, a, b, c, sc, n,
+                           clip_prefix(binds[2], (uint64_t)a, n, 4),
+                           clip_prefix(binds[0], (uint64_t)b, n, 4),
+                           clip_prefix(binds[1], (uint64_t)c, n, 4), seq);
     else
-        triad_dispatch<false>(f, log, a, b, c, sc, n, n, n, n, seq, s);
+        hipLaunchKernelGGL(k_triad<false>, grid, block, 0, s, f, log, a, b, c, sc, n, n, n, n, seq);
     return hipGetLastError();
 }
 

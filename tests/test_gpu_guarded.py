@@ -390,3 +390,37 @@ def test_first_denial_in_tables_around_the_inline_limit(n_ranges):
             k = rng.randrange(len(far))
             tw.remove(far.pop(k)[0])
     tw.close()
+
+
+@pytest.mark.parametrize("src_off,dst_off", [(0, 0), (1, 0), (0, 1), (4, 8), (15, 15), (7, 12)])
+def test_copy_and_triad_at_every_place_in_a_vector(src_off, dst_off):
+    """Copies and triads whose operands lie at any place in a 16-byte vector, from sizes below a
+    vector to several blocks, whole and with each operand's range ending before the call's end (on
+    and off the vectors' grid), against the oracle byte for byte and in the fault record."""
+    need_gpu()
+    ar = Arena(1 << 16, 100 + src_off * 16 + dst_off)
+    ar.write(0, np.random.default_rng(src_off).standard_normal(1 << 14).astype(np.float32))
+    A, B, C = 0x100, 0x5000, 0xA000
+    for cut in (None, 0, 1, 2):             # the operand whose range ends early (dst / a, src / b, c)
+        for n in (1, 3, 5, 16, 31, 64, 1029, 4100):
+            for short in (1, 4, 18) if cut is not None else (0,):
+                for op in ("copy", "triad"):
+                    w, k = (1, 1) if op == "copy" else (4, 4)
+                    offs = [A + dst_off * k, B + src_off * k, C + (3 * src_off % 16) * k]
+                    used = offs[:2] if op == "copy" else offs
+                    if n <= short or (cut is not None and cut >= len(used)):
+                        continue
+                    tw, ol = Twin(8), G.FaultLog()
+                    for j, o in enumerate(used):
+                        tw.insert(ar.addr(o), (n - (short if j == cut else 0)) * w, 0)
+                    p = [ar.addr(o) for o in used]
+                    if op == "copy":
+                        tw.g.agile_guarded_copy(tw.h, p[0], p[1], n)
+                        G.copy_vec(tw.ot, ar.mem, ol, tw.next_seq(), p[0], p[1], n)
+                    else:
+                        tw.g.agile_guarded_triad(tw.h, *p, -1.5, n)
+                        G.triad_vec(tw.ot, ar.mem, ol, tw.next_seq(), *p, -1.5, n)
+                    what = f"{op} n={n} cut={cut} short={short}"
+                    ar.check(what)
+                    log_matches(tw, ol, what)
+                    tw.close()
