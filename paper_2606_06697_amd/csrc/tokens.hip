@@ -9,9 +9,12 @@
 // lowest free slot; releasing advances the slot's generation, and a slot released in its last
 // generation is retired.
 //
-// Device record per slot (8 bytes): {owner client, or FREE / RETIRED; gen << 8 | kind}. The
+// Device record per slot: {owner client, or FREE / RETIRED; gen << 8 | kind} in 8 bytes, or packed
+// into 4 as long as the table's owners and generations leave room: kind in 8 bits, the owner in the
+// next `ob` (its two largest values stand for FREE and RETIRED), the generation above. The
 // host keeps the authoritative copy and uploads the dirty slot range in stream order before a
-// check that follows a change.
+// check that follows a change; an owner or generation that outgrows its field changes the layout,
+// and the whole table is uploaded again.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,7 +31,8 @@ namespace agile {
 constexpr uint32_t SLOT_MAX = 1u << 24;
 constexpr uint32_t GEN_MASK = (1u << 24) - 1;
 constexpr uint32_t OWNER_FREE = 0xFFFFFFFFu, OWNER_RETIRED = 0xFFFFFFFEu;
-constexpr int TBLOCK = 256, TPT = 4;  // tokens per thread per pass
+constexpr int TBLOCK = 256;
+constexpr int TPAIRS = 2;  // pairs of tokens per thread
 
 static __host__ __device__ inline uint64_t splitmix64(uint64_t x) {
     uint64_t z = x + 0x9E3779B97F4A7C15ull;
@@ -54,39 +58,95 @@ static __device__ __forceinline__ uint8_t token_verdict(uint64_t tok, uint32_t s
     return AGILE_TOKEN_VALID;
 }
 
-// Grid-stride over groups of TPT tokens per thread: the token, client and kind loads are
-// coalesced, the TPT slot-record loads of a thread are issued together (random 8-byte reads of
-// an L2-resident table), then each token gets its verdict.
+// How the slot records are laid out on the device: ob == 0 for 8 bytes, else packed.
+struct RecLayout {
+    uint32_t ob;
+};
+
+static __host__ __device__ inline uint32_t pack_rec(uint2 r, uint32_t ob) {
+    // FREE and RETIRED, the two largest owners, are cut to the field's two largest values
+    return (r.y >> 8) << (8 + ob) | (r.x & ((1u << ob) - 1)) << 8 | (r.y & 0xFFu);
+}
+static __host__ __device__ inline uint2 unpack_rec(uint32_t p, uint32_t ob) {
+    const uint32_t free_code = (1u << ob) - 1, f = (p >> 8) & free_code;
+    const uint32_t owner = f == free_code ? OWNER_FREE : f == free_code - 1 ? OWNER_RETIRED : f;
+    return make_uint2(owner, (p >> (8 + ob)) << 8 | (p & 0xFFu));
+}
+
+typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u64x2 u64x2_at8 __attribute__((aligned(8)));
+typedef u32x2 u32x2_at4 __attribute__((aligned(4)));
+typedef uint16_t u16_any __attribute__((aligned(1)));
+
+// One pass, TPAIRS pairs of neighbouring tokens per thread: a pair's tokens, clients and kinds are one
+// load each and its verdicts and slots one store each (the vector memory path takes instructions in
+// order, so fewer of them leave it to the record reads), and a thread's record reads, random ones of a
+// table that the L2s hold, are issued together. The streams are non-temporal, so that they do not push
+// the slot records out of L2. Bound by the record reads, a 128-byte line from L2 for each of them
+// whatever its width (without them 48 us for 2^24 tokens, the streams' time); 4-byte records halve the
+// lines that miss L2 or L1. 2^24 tokens over 2^20 slots: 131 us (141 with 8-byte records and four single
+// tokens a thread), over 2^18 129 (132), 2^14 97 (115), 2^12 64 (69); four pairs a thread 133.
+template <bool PACKED>
 __global__ __launch_bounds__(TBLOCK) void k_tokens_check(
-    const uint2* __restrict__ recs, uint32_t cap, uint64_t key, const uint64_t* __restrict__ tok,
-    const uint32_t* __restrict__ cli, const uint8_t* __restrict__ kinds, uint64_t n,
-    uint8_t* __restrict__ verdict, int32_t* __restrict__ slot_out) {
-    const uint64_t nth = (uint64_t)gridDim.x * TBLOCK;
-    for (uint64_t i0 = (uint64_t)blockIdx.x * TBLOCK + threadIdx.x; i0 < n; i0 += nth * TPT) {
-        uint64_t t[TPT];
-        uint32_t c[TPT], w[TPT], s[TPT];
-        uint2 r[TPT];
+    const void* __restrict__ recs, uint32_t cap, RecLayout lay, uint64_t key,
+    const uint64_t* __restrict__ tok, const uint32_t* __restrict__ cli,
+    const uint8_t* __restrict__ kinds, uint64_t n, uint8_t* __restrict__ verdict,
+    int32_t* __restrict__ slot_out) {
+    const auto record = [&](uint32_t s) {
+        if (PACKED) return unpack_rec(static_cast<const uint32_t*>(recs)[s], lay.ob);
+        return static_cast<const uint2*>(recs)[s];
+    };
+    const uint64_t np = n / 2, nth = (uint64_t)gridDim.x * TBLOCK;
+    const uint64_t tid = (uint64_t)blockIdx.x * TBLOCK + threadIdx.x;
+    for (uint64_t p0 = tid; p0 < np; p0 += nth * TPAIRS) {
+        u64x2 t[TPAIRS];
+        u32x2 c[TPAIRS];
+        uint32_t w[TPAIRS];
+        uint2 r[TPAIRS][2];
 #pragma unroll
-        for (int j = 0; j < TPT; ++j) {
-            const uint64_t i = i0 + (uint64_t)j * nth;
-            const bool in = i < n;
-            // streamed once: non-temporal, so they do not push the slot records out of L2
-            t[j] = in ? __builtin_nontemporal_load(tok + i) : 0;
-            c[j] = in ? __builtin_nontemporal_load(cli + i) : 0;
-            w[j] = (in && kinds) ? kinds[i] : AGILE_TOKEN_ANY_KIND;
-            s[j] = (uint32_t)(t[j] >> 40);
+        for (int j = 0; j < TPAIRS; ++j) {
+            // past the last pair: the last one again, not stored
+            const uint64_t p = p0 + j * nth < np ? p0 + j * nth : np - 1;
+            t[j] = __builtin_nontemporal_load(reinterpret_cast<const u64x2_at8*>(tok) + p);
+            c[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x2_at4*>(cli) + p);
+            w[j] = kinds ? __builtin_nontemporal_load(reinterpret_cast<const u16_any*>(kinds) + p)
+                         : AGILE_TOKEN_ANY_KIND * 0x101u;
         }
 #pragma unroll
-        for (int j = 0; j < TPT; ++j) r[j] = s[j] < cap ? recs[s[j]] : make_uint2(OWNER_FREE, 0);
+        for (int j = 0; j < TPAIRS; ++j)
 #pragma unroll
-        for (int j = 0; j < TPT; ++j) {
-            const uint64_t i = i0 + (uint64_t)j * nth;
-            if (i >= n) break;
-            const uint8_t v = s[j] < cap ? token_verdict(t[j], s[j], r[j], key, c[j], w[j])
-                                         : (uint8_t)AGILE_TOKEN_FORGED;
-            __builtin_nontemporal_store(v, verdict + i);
-            __builtin_nontemporal_store(v == AGILE_TOKEN_VALID ? (int32_t)s[j] : -1, slot_out + i);
+            for (int q = 0; q < 2; ++q) {
+                const uint32_t s = (uint32_t)(t[j][q] >> 40);
+                r[j][q] = s < cap ? record(s) : make_uint2(OWNER_FREE, 0);
+            }
+#pragma unroll
+        for (int j = 0; j < TPAIRS; ++j) {
+            const uint64_t p = p0 + j * nth;
+            uint32_t v[2];
+            u32x2 so;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const uint32_t s = (uint32_t)(t[j][q] >> 40);
+                v[q] = s < cap ? token_verdict(t[j][q], s, r[j][q], key, c[j][q], (w[j] >> (8 * q)) & 0xFFu)
+                               : (uint8_t)AGILE_TOKEN_FORGED;
+                so[q] = v[q] == AGILE_TOKEN_VALID ? s : 0xFFFFFFFFu;
+            }
+            if (p < np) {
+                __builtin_nontemporal_store((uint16_t)(v[0] | v[1] << 8),
+                                            reinterpret_cast<u16_any*>(verdict) + p);
+                __builtin_nontemporal_store(so, reinterpret_cast<u32x2_at4*>(slot_out) + p);
+            }
         }
+    }
+    if ((n & 1) && tid == 0) {
+        const uint64_t i = n - 1;
+        const uint32_t s = (uint32_t)(tok[i] >> 40);
+        const uint8_t v = s < cap ? token_verdict(tok[i], s, record(s), key, cli[i],
+                                                  kinds ? kinds[i] : AGILE_TOKEN_ANY_KIND)
+                                  : (uint8_t)AGILE_TOKEN_FORGED;
+        verdict[i] = v;
+        slot_out[i] = v == AGILE_TOKEN_VALID ? (int32_t)s : -1;
     }
 }
 
@@ -101,7 +161,7 @@ using agile::OWNER_FREE;
 using agile::OWNER_RETIRED;
 using agile::SLOT_MAX;
 using agile::TBLOCK;
-using agile::TPT;
+using agile::TPAIRS;
 using agile::token_tag;
 
 struct agile_tokens {
@@ -112,8 +172,10 @@ struct agile_tokens {
     std::set<uint32_t> free_slots;    // released, reusable
     uint32_t next_new = 0;
     uint32_t dlo = 0, dhi = 0;        // dirty slot range [dlo, dhi)
-    uint2* d_rec = nullptr;
-    uint2* h_stage = nullptr;         // pinned staging of the upload
+    agile::RecLayout lay{10};         // packed until an owner or a generation asks for more
+    uint32_t max_owner = 0, max_gen = 0;  // over every record written so far
+    void* d_rec = nullptr;
+    void* h_stage = nullptr;          // pinned staging of the upload
     hipEvent_t upload_done = nullptr;
     bool upload_pending = false;
     hipStream_t upload_stream = nullptr;
@@ -131,6 +193,23 @@ static void mark_dirty(agile_tokens* ts, uint32_t s) {
     }
 }
 
+// Sets slot s's record; a value that its field cannot hold changes the layout of the device records.
+static void set_rec(agile_tokens* ts, uint32_t s, uint2 r) {
+    ts->rec[s] = r;
+    mark_dirty(ts, s);
+    if (r.x < OWNER_RETIRED) ts->max_owner = std::max(ts->max_owner, r.x);
+    ts->max_gen = std::max(ts->max_gen, r.y >> 8);
+    const auto fits = [&](uint32_t ob) {
+        return (uint64_t)ts->max_owner + 2 < (1ull << ob) && (ts->max_gen >> (24 - ob)) == 0;
+    };
+    if (ts->lay.ob == 0 || fits(ts->lay.ob)) return;
+    uint32_t ob = 2;  // the narrowest owner field, which leaves the generations the most room
+    while (ob < 24 && (uint64_t)ts->max_owner + 2 >= (1ull << ob)) ++ob;
+    ts->lay.ob = ob < 24 && fits(ob) ? ob : 0;
+    ts->dlo = 0;
+    ts->dhi = ts->cap;
+}
+
 int agile_tokens_create(agile_tokens** out, uint32_t capacity, uint64_t key, int device) {
     if (!out || capacity < 1 || capacity > SLOT_MAX) return AGILE_EINVAL;
     int ndev = 0;
@@ -145,7 +224,7 @@ int agile_tokens_create(agile_tokens** out, uint32_t capacity, uint64_t key, int
     ts->key = key;
     ts->rec.assign(capacity, make_uint2(OWNER_FREE, 0u));
     if (hipMalloc(&ts->d_rec, (size_t)capacity * sizeof(uint2)) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void**>(&ts->h_stage), (size_t)capacity * sizeof(uint2),
+        hipHostMalloc(&ts->h_stage, (size_t)capacity * sizeof(uint2),
                       hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&ts->upload_done, hipEventDisableTiming) != hipSuccess) {
         agile_tokens_destroy(ts);
@@ -182,8 +261,7 @@ int agile_token_mint(agile_tokens* ts, uint32_t client, uint32_t kind, uint64_t*
         return AGILE_ENOSPC;
     }
     const uint32_t gen = ts->rec[s].y >> 8;
-    ts->rec[s] = make_uint2(client, (gen << 8) | kind);
-    mark_dirty(ts, s);
+    set_rec(ts, s, make_uint2(client, (gen << 8) | kind));
     *out_token = ((uint64_t)s << 40) | ((uint64_t)gen << 16) | token_tag(ts->key, s, gen);
     return AGILE_OK;
 }
@@ -208,12 +286,11 @@ int agile_token_release(agile_tokens* ts, uint64_t token, uint32_t client) {
     if (host_token_verdict(ts, token, client, &s) != AGILE_TOKEN_VALID) return AGILE_ENOENT;
     const uint32_t gen = ts->rec[s].y >> 8;
     if (gen == GEN_MASK) {
-        ts->rec[s] = make_uint2(OWNER_RETIRED, gen << 8);
+        set_rec(ts, s, make_uint2(OWNER_RETIRED, gen << 8));
     } else {
-        ts->rec[s] = make_uint2(OWNER_FREE, (gen + 1) << 8);
+        set_rec(ts, s, make_uint2(OWNER_FREE, (gen + 1) << 8));
         ts->free_slots.insert(s);
     }
-    mark_dirty(ts, s);
     return AGILE_OK;
 }
 
@@ -234,8 +311,18 @@ static int tokens_prepare(agile_tokens* ts, hipStream_t s) {
         if (ts->upload_pending && hipEventSynchronize(ts->upload_done) != hipSuccess)
             return AGILE_EDEVICE;
         const size_t lo = ts->dlo, cnt = (size_t)ts->dhi - ts->dlo;
-        std::copy(ts->rec.begin() + lo, ts->rec.begin() + lo + cnt, ts->h_stage + lo);
-        if (hipMemcpyAsync(ts->d_rec + lo, ts->h_stage + lo, cnt * sizeof(uint2),
+        const size_t w = ts->lay.ob ? sizeof(uint32_t) : sizeof(uint2);
+        if (ts->lay.ob) {
+            uint32_t* __restrict__ st = static_cast<uint32_t*>(ts->h_stage) + lo;
+            const uint2* __restrict__ r = ts->rec.data() + lo;
+            const uint32_t ob = ts->lay.ob;
+            for (size_t k = 0; k < cnt; ++k) st[k] = agile::pack_rec(r[k], ob);
+        } else {
+            std::copy(ts->rec.begin() + lo, ts->rec.begin() + lo + cnt,
+                      static_cast<uint2*>(ts->h_stage) + lo);
+        }
+        if (hipMemcpyAsync(static_cast<uint8_t*>(ts->d_rec) + lo * w,
+                           static_cast<const uint8_t*>(ts->h_stage) + lo * w, cnt * w,
                            hipMemcpyHostToDevice, s) != hipSuccess ||
             hipEventRecord(ts->upload_done, s) != hipSuccess)
             return AGILE_EDEVICE;
@@ -264,12 +351,14 @@ int agile_tokens_check(agile_tokens* ts, const uint64_t* d_tokens, const uint32_
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int rc = tokens_prepare(ts, s);
     if (rc != AGILE_OK) return rc;
-    const uint64_t per_block = (uint64_t)TBLOCK * TPT;
-    uint64_t grid = (n + per_block - 1) / per_block;
-    // one pass (0.603 ms for 2^26 tokens, against 0.628 ms with 8 workgroups per CU looping)
-    const uint64_t cap = 1ull << 30;
+    const uint64_t per_block = (uint64_t)TBLOCK * TPAIRS;
+    uint64_t grid = (n / 2 + per_block - 1) / per_block;
+    // one pass (2^26 tokens took 4% longer with 8 workgroups per CU looping)
+    const uint64_t cap = 1ull << 23;
     if (grid > cap) grid = cap;
-    hipLaunchKernelGGL(agile::k_tokens_check, dim3((uint32_t)grid), dim3(TBLOCK), 0, s, ts->d_rec,
-                       ts->cap, ts->key, d_tokens, d_clients, d_kinds, n, d_verdict, d_slot);
+    if (grid < 1) grid = 1;
+    auto k = ts->lay.ob ? agile::k_tokens_check<true> : agile::k_tokens_check<false>;
+    hipLaunchKernelGGL(k, dim3((uint32_t)grid), dim3(TBLOCK), 0, s, ts->d_rec, ts->cap, ts->lay, ts->key,
+                       d_tokens, d_clients, d_kinds, n, d_verdict, d_slot);
     return hipGetLastError() == hipSuccess ? AGILE_OK : AGILE_EDEVICE;
 }

@@ -162,3 +162,45 @@ def test_tokens_two_streams_see_changes_in_order():
             ts.mint(*bad)
         assert e.value.code == g.AGILE_EINVAL
     ts.close()
+
+
+@pytest.mark.parametrize("clients", [(0, 1, 1020, 1021, 1022, 1 << 14), (3, (1 << 20) - 3, 1 << 22),
+                                     (5, 0xFFFFFFFD), (7,)])
+def test_records_that_outgrow_their_layout(clients):
+    """Slot records are packed while owners and generations leave room: checks before and after the
+    owners that no longer fit (in any order of growth), and after generations that no longer fit
+    beside them, against the oracle; odd and even counts of tokens, with and without kinds."""
+    need_gpu()
+    g = guard_mod()
+    rng = random.Random(len(clients))
+    key = rng.getrandbits(64)
+    ts, ot = g.TokenTable(16, key), T.TokenTable(16, key)
+    minted = {}
+
+    def check():
+        for cut in (0, 1):
+            pres = presented(rng, minted, key, list(clients) + [1 << 30, 0xFFFFFFFF, 0xFFFFFFFE],
+                             [0, 3, 254], 20)[cut:]
+            for with_kinds in (True, False):
+                v, s = device_check(g, ts, pres, with_kinds)
+                want = [ot.check(t, c, k if with_kinds else T.ANY_KIND) for t, c, k in pres]
+                assert v.tolist() == [w[0] for w in want] and s.tolist() == [w[1] for w in want]
+
+    for c in clients:
+        for kind in (0, 254):
+            tok = ts.mint(c, kind)
+            assert tok == ot.mint(c, kind)
+            minted[tok] = (c, kind)
+        check()
+    tok, own = next(iter(minted)), clients[0]
+    for gen in range((1 << 14) + 2):
+        ts.release(tok, own)
+        ot.release(tok, own)
+        tok = ts.mint(own, 3)
+        assert tok == ot.mint(own, 3)
+        if gen in (0, (1 << 14) - 2, (1 << 14) - 1, 1 << 14):
+            minted[tok] = (own, 3)
+            check()
+    minted[tok] = (own, 3)
+    check()
+    ts.close()
