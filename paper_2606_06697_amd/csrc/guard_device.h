@@ -1,7 +1,7 @@
 // Device-side data layout and helpers shared by the guard kernels (gfx950, wave64).
 //
 // Table image (built on the host from the sorted range list, uploaded in stream order):
-//   radix[r]    u32  search index over the LDS-resident splitters (see DevTable)
+//   index       the validation's search index, laid out as it is staged in LDS (see DevTable)
 //   nrec[b]     16 B the bucket's record with bit-packed offsets (see DevTable), when they fit
 //   split64[b]  u64  base of the first range of bucket b (buckets hold 2 consecutive
 //                    ranges in address order), nb = ceil(n/2) entries
@@ -41,7 +41,7 @@ struct DevTable {
     const uint64_t* split64;
     const uint32_t* split32;
     const PairRec* rec;
-    const uint32_t* radix;  // validation search index, see below
+    const uint4* index;     // validation search index, see below
     const uint8_t* backed;  // per bucket: bit 0 / bit 1 = first / second range is backed memory
     uint64_t gmin;
     uint32_t nb;          // number of buckets (0 for an empty table)
@@ -61,14 +61,18 @@ struct DevTable {
     uint32_t rlevels;
     uint32_t lift;
     uint32_t pad;
-    uint32_t lds_bytes;   // LDS one validation workgroup needs (top + sentinels + radix)
+    uint32_t lds_bytes;   // LDS one validation workgroup needs (top + sentinels + radix), the bytes
+                          // at `index`; a multiple of 16
+    uint32_t radix_off;   // where the radix entries start in it
     // Packed records (validation only, present when narrow != 0; then rlog2 == 0): per bucket
     // 16 bytes {u32 lo, u32 hi, u32 meta0, u32 meta1} with offsets relative to the bucket base:
-    // lo = (second range's base >> sb) | (first range's end << w1), hi = second range's end.
+    // lo = (second range's base >> sb) | (first range's end << w1), hi = second range's end. They lie
+    // right behind the index.
     const uint4* nrec;
     uint32_t narrow;
     uint32_t sb;
     uint32_t w1;
+    uint32_t lds_rec;     // the packed records fit the LDS behind the index
     uint32_t pad2;
 };
 

@@ -37,20 +37,15 @@ struct KeyT<true> {
     using T = uint32_t;
 };
 
-// Stage the search index into LDS: splitters, sentinels, radix entries.
-template <bool COMP>
-__device__ __forceinline__ const uint32_t* stage_index(const DevTable& t, unsigned char* lds_raw) {
-    using K = typename KeyT<COMP>::T;
-    const uint32_t ntop = t.ntop, npad = ntop + t.pad;
-    K* top = reinterpret_cast<K*>(lds_raw);
-    uint32_t* ri = reinterpret_cast<uint32_t*>(lds_raw + (((size_t)npad * sizeof(K) + 15) & ~15ull));
-    const K* gsplit = COMP ? reinterpret_cast<const K*>(t.split32)
-                           : reinterpret_cast<const K*>(t.split64);
-    for (uint32_t k = threadIdx.x; k < npad; k += VBLOCK)
-        top[k] = k < ntop ? gsplit[(uint64_t)k << t.rlog2] : (K)~(K)0;
-    for (uint32_t k = threadIdx.x; k <= t.nr; k += VBLOCK) ri[k] = t.radix[k];
+// Stages the search index into LDS, and with LREC the packed records behind it: one copy of the image
+// that the host laid out as it is to lie there. A short loop on purpose: several loads in flight per
+// thread (five at a time, in rounds) and the first queries loaded ahead of the barrier both made launches
+// of up to 2^20 queries 0.3-0.5 us longer, by their code. Against 4-byte loads, array after array: 200
+// queries on 65,536 ranges 7.3 -> 4.0 us, 200,000 12.8 -> 8.9, 2^20 13.8 -> 11.6.
+__device__ __forceinline__ void stage_index(uint4* lds, const uint4* src, uint32_t nv) {
+#pragma unroll 1
+    for (uint32_t k = threadIdx.x; k < nv; k += VBLOCK) lds[k] = src[k];
     __syncthreads();
-    return ri;
 }
 
 template <int QPT, bool TAIL>
@@ -166,7 +161,7 @@ __device__ __forceinline__ void chunk_wide(const DevTable& t, const unsigned cha
 // ---------------------------------------------------------------- packed 16-byte records
 // Offsets inside a bucket (the second range's base, both ends) are below 2^32 whenever packed
 // records are built, so after one 64-bit subtraction the classification runs on 32-bit values.
-template <bool COMP, int LEVELS, int QPT, bool TAIL, bool DMA>
+template <bool COMP, int LEVELS, int QPT, bool TAIL, bool DMA, bool LREC>
 __device__ __forceinline__ void chunk_packed(const DevTable& t, const unsigned char* lds_raw,
                                              const uint32_t* ri, const ulonglong2 (&x)[QPT],
                                              uint64_t n, uint8_t* __restrict__ verdict,
@@ -200,7 +195,8 @@ __device__ __forceinline__ void chunk_packed(const DevTable& t, const unsigned c
     }
     uint4 r[QPT];
 #pragma unroll
-    for (int j = 0; j < QPT; ++j) r[j] = t.nrec[b[j]];
+    for (int j = 0; j < QPT; ++j)
+        r[j] = LREC ? reinterpret_cast<const uint4*>(lds_raw + t.lds_bytes)[b[j]] : t.nrec[b[j]];
     const uint32_t m1 = t.w1 >= 32 ? 0xFFFFFFFFu : (1u << t.w1) - 1u;
     const uint32_t sb = t.sb, w1 = t.w1;
     uint8_t* vp = verdict + c0 + lane;
@@ -242,12 +238,11 @@ __device__ __forceinline__ void chunk_packed(const DevTable& t, const unsigned c
 }
 
 // Grid-stride loop over chunks of 64*QPT queries per wave, full chunks software-pipelined.
-template <bool COMP, bool PACKED, int LEVELS, int QPT, bool DMA>
+template <bool COMP, bool PACKED, int LEVELS, int QPT, bool DMA, bool LREC>
 __global__ __launch_bounds__(VBLOCK) void k_validate(DevTable t, const ulonglong2* __restrict__ q,
                                                       uint64_t n, uint8_t* __restrict__ verdict,
                                                       int32_t* __restrict__ owner) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const uint32_t* ri = stage_index<COMP>(t, lds_raw);
     if (t.nb == 0) {
         // empty table: everything is unmapped
         for (uint64_t i = (uint64_t)blockIdx.x * VBLOCK + threadIdx.x; i < n;
@@ -265,6 +260,8 @@ __global__ __launch_bounds__(VBLOCK) void k_validate(DevTable t, const ulonglong
     const uint64_t stride = nwaves * CHUNK;
     uint64_t c0 = wave * CHUNK;
     ulonglong2 x[QPT];
+    const uint32_t* ri = reinterpret_cast<const uint32_t*>(lds_raw + t.radix_off);
+    stage_index(reinterpret_cast<uint4*>(lds_raw), t.index, t.lds_bytes / 16 + (LREC ? t.nb : 0));
     if (c0 < nfull) load_chunk<QPT, false>(q, n, c0, lane, x);
     for (; c0 < nfull; c0 += stride) {
         ulonglong2 cur[QPT];
@@ -272,25 +269,25 @@ __global__ __launch_bounds__(VBLOCK) void k_validate(DevTable t, const ulonglong
         for (int j = 0; j < QPT; ++j) cur[j] = x[j];
         if (c0 + stride < nfull) load_chunk<QPT, false>(q, n, c0 + stride, lane, x);
         if (PACKED)
-            chunk_packed<COMP, LEVELS, QPT, false, DMA>(t, lds_raw, ri, cur, n, verdict, owner, c0,
-                                                        lane);
+            chunk_packed<COMP, LEVELS, QPT, false, DMA, LREC>(t, lds_raw, ri, cur, n, verdict, owner, c0,
+                                                              lane);
         else
             chunk_wide<COMP, QPT, false, DMA>(t, lds_raw, ri, cur, n, verdict, owner, c0, lane);
     }
     if (c0 < n) {
         load_chunk<QPT, true>(q, n, c0, lane, x);
         if (PACKED)
-            chunk_packed<COMP, LEVELS, QPT, true, DMA>(t, lds_raw, ri, x, n, verdict, owner, c0, lane);
+            chunk_packed<COMP, LEVELS, QPT, true, DMA, LREC>(t, lds_raw, ri, x, n, verdict, owner, c0, lane);
         else
             chunk_wide<COMP, QPT, true, DMA>(t, lds_raw, ri, x, n, verdict, owner, c0, lane);
     }
 }
 
-template <bool COMP, bool PACKED, int LEVELS, int QPT, bool DMA>
+template <bool COMP, bool PACKED, int LEVELS, int QPT, bool DMA, bool LREC>
 static hipError_t launch_v(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
                            uint8_t* verdict, int32_t* owner, hipStream_t s) {
-    const void* fn = reinterpret_cast<const void*>(&k_validate<COMP, PACKED, LEVELS, QPT, DMA>);
-    const size_t lds = t.lds_bytes;
+    const void* fn = reinterpret_cast<const void*>(&k_validate<COMP, PACKED, LEVELS, QPT, DMA, LREC>);
+    const size_t lds = t.lds_bytes + (LREC ? (size_t)t.nb * 16 : 0);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)(lds > 0 ? lds : 16));
     if (e != hipSuccess) return e;
@@ -302,26 +299,42 @@ static hipError_t launch_v(const DevTable& t, const DevInfo& d, const void* q, u
     const uint64_t want = (chunks + (VBLOCK / 64) - 1) / (VBLOCK / 64);
     uint64_t grid = (uint64_t)d.num_cu * per_cu;
     if (want < grid) grid = want;
-    hipLaunchKernelGGL((k_validate<COMP, PACKED, LEVELS, QPT, DMA>), dim3((uint32_t)grid), dim3(VBLOCK),
-                       lds, s, t, reinterpret_cast<const ulonglong2*>(q), n, verdict, owner);
+    hipLaunchKernelGGL((k_validate<COMP, PACKED, LEVELS, QPT, DMA, LREC>), dim3((uint32_t)grid),
+                       dim3(VBLOCK), lds, s, t, reinterpret_cast<const ulonglong2*>(q), n, verdict, owner);
     return hipGetLastError();
 }
+
+template <bool COMP, bool DMA, bool LREC>
+static hipError_t launch_packed(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
+                                uint8_t* verdict, int32_t* owner, hipStream_t s) {
+    constexpr int QP = 6;  // queries per lane, packed records
+    switch (t.lift) {
+        case 2: return launch_v<COMP, true, 2, QP, DMA, LREC>(t, d, q, n, verdict, owner, s);
+        case 4: return launch_v<COMP, true, 4, QP, DMA, LREC>(t, d, q, n, verdict, owner, s);
+        case 6: return launch_v<COMP, true, 6, QP, DMA, LREC>(t, d, q, n, verdict, owner, s);
+        default: return launch_v<COMP, true, 8, QP, DMA, LREC>(t, d, q, n, verdict, owner, s);
+    }
+}
+
+// Records in LDS: a record read from L1 or L2 costs the CU's vector memory path one line per query (a
+// line of 128 bytes at 64 bytes a clock, and a place among the lines it can have outstanding, which the
+// query stream needs as well), a read from LDS neither. 2^26 queries, records in L2 / in LDS: 4,096
+// ranges 354 / 268 us, 8,192 380 / 270, 12,000 395 / 270. Up to 512 buckets the records stay in L1 (256 /
+// 264 with 64 ranges; from 2^24 queries on they are left there, below that LDS is the faster: 2^22 queries
+// 16.6 / 14.6), and below 2^20 queries staging them takes longer than it saves.
+constexpr uint64_t LREC_MIN_N = 1ull << 20, L1_MIN_N = 1ull << 24;
+constexpr uint32_t L1_BUCKETS = 512;
 
 template <bool COMP, bool DMA>
 static hipError_t launch_c(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
                            uint8_t* verdict, int32_t* owner, hipStream_t s) {
     constexpr int QW = 6;  // queries per lane, general records
-    constexpr int QP = 6;  // queries per lane, packed records
-    if (t.narrow && t.rlog2 == 0) {
-        switch (t.lift) {
-            case 2: return launch_v<COMP, true, 2, QP, DMA>(t, d, q, n, verdict, owner, s);
-            case 4: return launch_v<COMP, true, 4, QP, DMA>(t, d, q, n, verdict, owner, s);
-            case 6: return launch_v<COMP, true, 6, QP, DMA>(t, d, q, n, verdict, owner, s);
-            case 8: return launch_v<COMP, true, 8, QP, DMA>(t, d, q, n, verdict, owner, s);
-            default: break;
-        }
+    if (t.narrow && t.rlog2 == 0) {  // then lift is 2, 4, 6 or 8
+        if (t.lds_rec && n >= LREC_MIN_N && (t.nb > L1_BUCKETS || n < L1_MIN_N))
+            return launch_packed<COMP, DMA, true>(t, d, q, n, verdict, owner, s);
+        return launch_packed<COMP, DMA, false>(t, d, q, n, verdict, owner, s);
     }
-    return launch_v<COMP, false, 0, QW, DMA>(t, d, q, n, verdict, owner, s);
+    return launch_v<COMP, false, 0, QW, DMA, false>(t, d, q, n, verdict, owner, s);
 }
 
 hipError_t launch_validate(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,

@@ -136,15 +136,18 @@ struct agile_rt {
 };
 
 // Image layout for nb buckets, the same on the device and in the staging buffer, so that an upload is
-// one copy: split64 | rec | split32 | backed | radix | nrec (each 64-byte aligned; nrec follows the
-// radix entries in use).
+// one copy: split64 | rec | backed | index | nrec | split32 (the first four 64-byte aligned, the others
+// right behind; the last two only where they are needed).
 static size_t up64(size_t x) { return (x + 63) & ~(size_t)63; }
 static size_t rec_offset(size_t nb) { return up64(nb * 8); }
-static size_t split32_offset(size_t nb) { return rec_offset(nb) + nb * sizeof(PairRec); }
-static size_t backed_offset(size_t nb) { return up64(split32_offset(nb) + nb * 4); }
-static size_t radix_offset(size_t nb) { return up64(backed_offset(nb) + nb); }
-static size_t nrec_offset(size_t nb, size_t nr) { return up64(radix_offset(nb) + (nr + 1) * 4); }
-static size_t image_bytes(size_t cap_nb) { return nrec_offset(cap_nb, MAX_RADIX) + cap_nb * 16; }
+static size_t backed_offset(size_t nb) { return rec_offset(nb) + nb * sizeof(PairRec); }
+static size_t index_offset(size_t nb) { return up64(backed_offset(nb) + nb); }
+// the index is at most as large as the LDS, splitters, sentinels (at most twice the splitters, or 256)
+// and radix entries (at most two per splitter)
+static size_t image_bytes(size_t cap_nb, size_t lds) {
+    return index_offset(cap_nb) + std::min(lds, (3 * cap_nb + 256) * 8 + (2 * cap_nb + 4) * 4) + 64 +
+           cap_nb * 20;
+}
 
 static uint32_t bitlen(uint64_t x) {
     uint32_t b = 0;
@@ -228,7 +231,8 @@ static void search_geometry(DevTable& t, const uint64_t* s64, uint32_t* radix, s
         t.lift = 0;
         t.pad = 1;
         radix[0] = radix[1] = 0;
-        t.lds_bytes = 16 + 8;
+        t.radix_off = 16;
+        t.lds_bytes = 32;
         return;
     }
     const uint64_t gmin = s64[0];
@@ -253,7 +257,7 @@ static void search_geometry(DevTable& t, const uint64_t* s64, uint32_t* radix, s
             const uint32_t lift = rlevels <= 8 ? std::max(lift_levels(rlevels), min_lift)
                                                : lift_levels(rlevels);
             const size_t top_bytes = ((((size_t)ntop + (1ull << lift)) * ks + 15) / 16) * 16;
-            const size_t need = top_bytes + (size_t)(nr + 1) * 4;
+            const size_t need = top_bytes + (((size_t)(nr + 1) * 4 + 15) / 16) * 16;
             if (need > budget) continue;
             t.rlog2 = rlog2;
             t.ntop = ntop;
@@ -263,6 +267,7 @@ static void search_geometry(DevTable& t, const uint64_t* s64, uint32_t* radix, s
             t.rlevels = rlevels;
             t.lift = lift;
             t.pad = 1u << lift;
+            t.radix_off = (uint32_t)top_bytes;
             t.lds_bytes = (uint32_t)need;
             return;
         }
@@ -289,9 +294,8 @@ static int upload(agile_rt* rt, hipStream_t s) {
     uint8_t* h = static_cast<uint8_t*>(im.stage);
     uint64_t* s64 = reinterpret_cast<uint64_t*>(h);
     PairRec* rec = reinterpret_cast<PairRec*>(h + rec_offset(nb));
-    uint32_t* s32 = reinterpret_cast<uint32_t*>(h + split32_offset(nb));
     uint8_t* bk = h + backed_offset(nb);
-    uint32_t* radix = reinterpret_cast<uint32_t*>(h + radix_offset(nb));
+    std::vector<uint32_t> radix(MAX_RADIX + 1);
     const auto& E = rt->entries;
     for (uint32_t b = 0; b < nb; ++b) {
         const Entry& e0 = E[2 * b];
@@ -315,9 +319,9 @@ static int upload(agile_rt* rt, hipStream_t s) {
     DevTable t{};
     t.split64 = reinterpret_cast<const uint64_t*>(im.dev);
     t.rec = reinterpret_cast<const PairRec*>(im.dev + rec_offset(nb));
-    t.split32 = reinterpret_cast<const uint32_t*>(im.dev + split32_offset(nb));
     t.backed = im.dev + backed_offset(nb);
-    t.radix = reinterpret_cast<const uint32_t*>(im.dev + radix_offset(nb));
+    const size_t o_index = index_offset(nb);
+    t.index = reinterpret_cast<const uint4*>(im.dev + o_index);
     t.nb = nb;
     t.compressed = 0;
     if (nb > 0) {
@@ -330,15 +334,35 @@ static int upload(agile_rt* rt, hipStream_t s) {
         bool ok = (span >> sh) <= 0xFFFFFFFEull;
         for (uint32_t b = 0; ok && b < nb; ++b) ok = ((s64[b] - gmin) & mask) == 0;
         if (ok) {
-            for (uint32_t b = 0; b < nb; ++b) s32[b] = (uint32_t)((s64[b] - gmin) >> sh);
             t.compressed = 1;
             t.shift = sh;
         }
     }
-    search_geometry(t, s64, radix, std::min(rt->lds_budget, rt->info.lds_per_block), rt->min_lift);
-    const size_t o_nrec = nrec_offset(nb, t.nr);
+    const size_t budget = std::min(rt->lds_budget, rt->info.lds_per_block);
+    size_t o_nrec = 0;
+    const auto lay_out = [&](size_t lds) {
+        search_geometry(t, s64, radix.data(), lds, rt->min_lift);
+        o_nrec = o_index + t.lds_bytes;
+        t.narrow = 0;
+        if (!rt->wide_only) build_narrow(t, s64, rec, reinterpret_cast<uint32_t*>(h + o_nrec));
+    };
+    // first an index that leaves packed records room in the LDS (with fewer radix entries, if need be)
+    const size_t recs = (size_t)nb * 16;
+    if (!rt->wide_only && recs + 1024 <= budget) {
+        lay_out(budget - recs);
+        t.lds_rec = t.narrow;
+    }
+    if (!t.lds_rec) lay_out(budget);
     t.nrec = reinterpret_cast<const uint4*>(im.dev + o_nrec);
-    if (!rt->wide_only) build_narrow(t, s64, rec, reinterpret_cast<uint32_t*>(h + o_nrec));
+    // the index as the LDS holds it
+    uint8_t* ix = h + o_index;
+    const auto key32 = [&](uint64_t b) { return (uint32_t)((s64[b] - t.gmin) >> t.shift); };
+    for (uint32_t k = 0; k < t.ntop + t.pad; ++k) {
+        const uint64_t b = (uint64_t)k << t.rlog2;
+        if (t.compressed) reinterpret_cast<uint32_t*>(ix)[k] = k < t.ntop ? key32(b) : 0xFFFFFFFFu;
+        else reinterpret_cast<uint64_t*>(ix)[k] = k < t.ntop ? s64[b] : U64MAX;
+    }
+    std::memcpy(ix + t.radix_off, radix.data(), ((size_t)t.nr + 1) * 4);
     // the last readers of image x
     for (hipEvent_t e : im.retired)
         if (hipStreamWaitEvent(s, e, 0) != hipSuccess) return AGILE_EDEVICE;
@@ -353,7 +377,15 @@ static int upload(agile_rt* rt, hipStream_t s) {
         if (hipEventRecord(ev, o) != hipSuccess) return AGILE_EDEVICE;
     }
     rt->streams_used.clear();
-    const size_t bytes = t.narrow ? o_nrec + (size_t)nb * 16 : radix_offset(nb) + ((size_t)t.nr + 1) * 4;
+    // every 32-bit key: the index holds them all, or they follow
+    size_t bytes = o_nrec + (t.narrow ? (size_t)nb * 16 : 0);
+    t.split32 = reinterpret_cast<const uint32_t*>(im.dev + o_index);
+    if (t.compressed && t.rlog2) {
+        uint32_t* s32 = reinterpret_cast<uint32_t*>(h + bytes);
+        for (uint32_t b = 0; b < nb; ++b) s32[b] = key32(b);
+        t.split32 = reinterpret_cast<const uint32_t*>(im.dev + bytes);
+        bytes += (size_t)nb * 4;
+    }
     if (hipMemcpyAsync(im.dev, h, bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipEventRecord(im.ready, s) != hipSuccess)
         return AGILE_EDEVICE;
@@ -468,7 +500,7 @@ int agile_rt_create(agile_rt** out, uint32_t capacity, int device) {
         const int v = std::atoi(e);
         if (v == 2 || v == 4 || v == 6 || v == 8) rt->min_lift = (uint32_t)v;
     }
-    rt->stage_bytes = image_bytes(rt->cap_nb);
+    rt->stage_bytes = image_bytes(rt->cap_nb, rt->info.lds_per_block);
     const size_t img_bytes = ((rt->stage_bytes + 255) / 256) * 256;
     const size_t dev_bytes = 2 * img_bytes + sizeof(DevLog);
     if (hipMalloc(&rt->dmem, dev_bytes) != hipSuccess) {

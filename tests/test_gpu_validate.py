@@ -183,3 +183,35 @@ def test_insert_remove_interleaved_with_validation():
         q = _boundary_queries(tw.ot, rng)
         assert_same(tw, q, f"step {step}")
     tw.close()
+
+
+@pytest.mark.parametrize("n_ranges,far,lift", [(64, False, None), (1000, False, "8"),
+                                               (1100, True, None), (8192, False, None),
+                                               (8192, False, "6"), (9000, True, None),
+                                               (13000, False, None), (15100, False, None)])
+def test_bulk_queries_with_records_in_lds(n_ranges, far, lift, monkeypatch):
+    """From 2^20 queries on, tables whose packed records fit the LDS behind the index are checked from
+    there: small and large tables on either side of that, with 32-bit and 64-bit splitter keys (a far
+    range makes the span too wide), pointer and DMA queries, a ragged count."""
+    need_gpu()
+    if lift:
+        monkeypatch.setenv("AGILE_MIN_LIFT", lift)
+    tb = make_table(n_ranges, n_ranges // 8, n_ranges)
+    tw = Twin(n_ranges + 1)
+    tw.insert_table(tb)
+    if far:
+        tw.insert((1 << 47) + 3, 4099, 0)
+    n = (1 << 20) + 77
+    q = make_queries(tb, n, n_ranges).numpy().view(np.uint64)
+    q[:6] = [[0, 1], [U64_MAX, U64_MAX], [(1 << 47) + 3, 4099], [(1 << 47) + 4, 4099],
+             [(1 << 47) + 2, 1], [int(tb.base[0]) - 1, 2]]
+    assert_same(tw, q, f"{n_ranges} ranges")
+    from synth.workloads import make_dma_queries
+    q = make_dma_queries(tb, n, n_ranges).numpy().view(np.uint64)
+    qd = torch.from_numpy(q.view(np.int64).copy()).cuda()
+    v = torch.full((n,), 255, dtype=torch.uint8, device="cuda")
+    o = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    tw.g.agile_validate_dma(tw.h, qd, n, v, o)
+    ev, eo = tw.ot.dma_verdict_many(q[:, 0], q[:, 1])
+    assert np.array_equal(v.cpu().numpy(), ev) and np.array_equal(o.cpu().numpy(), eo)
+    tw.close()
