@@ -294,7 +294,9 @@ static hipError_t launch_v(const DevTable& t, const DevInfo& d, const void* q, u
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, VBLOCK, lds);
     if (e != hipSuccess) return e;
-    if (per_cu < 1) per_cu = 1;
+    // with the records in LDS one workgroup a CU streams large batches faster than two (2^26 queries 242 /
+    // 251 us, DMA 225 / 262), two the smaller ones (2^22: 14.2 / 15.4)
+    if (per_cu < 1 || (LREC && n > (1ull << 24))) per_cu = 1;
     const uint64_t chunks = (n + 64u * QPT - 1) / (64u * QPT);
     const uint64_t want = (chunks + (VBLOCK / 64) - 1) / (VBLOCK / 64);
     uint64_t grid = (uint64_t)d.num_cu * per_cu;
@@ -304,10 +306,9 @@ static hipError_t launch_v(const DevTable& t, const DevInfo& d, const void* q, u
     return hipGetLastError();
 }
 
-template <bool COMP, bool DMA, bool LREC>
+template <bool COMP, bool DMA, bool LREC, int QP>
 static hipError_t launch_packed(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
                                 uint8_t* verdict, int32_t* owner, hipStream_t s) {
-    constexpr int QP = 6;  // queries per lane, packed records
     switch (t.lift) {
         case 2: return launch_v<COMP, true, 2, QP, DMA, LREC>(t, d, q, n, verdict, owner, s);
         case 4: return launch_v<COMP, true, 4, QP, DMA, LREC>(t, d, q, n, verdict, owner, s);
@@ -318,23 +319,27 @@ static hipError_t launch_packed(const DevTable& t, const DevInfo& d, const void*
 
 // Records in LDS: a record read from L1 or L2 costs the CU's vector memory path one line per query (a
 // line of 128 bytes at 64 bytes a clock, and a place among the lines it can have outstanding, which the
-// query stream needs as well), a read from LDS neither. 2^26 queries, records in L2 / in LDS: 4,096
-// ranges 354 / 268 us, 8,192 380 / 270, 12,000 395 / 270. Up to 512 buckets the records stay in L1 (256 /
-// 264 with 64 ranges; from 2^24 queries on they are left there, below that LDS is the faster: 2^22 queries
-// 16.6 / 14.6), and below 2^20 queries staging them takes longer than it saves.
-constexpr uint64_t LREC_MIN_N = 1ull << 20, L1_MIN_N = 1ull << 24;
-constexpr uint32_t L1_BUCKETS = 512;
+// query stream needs as well), a read from LDS neither. 2^26 queries, records in L2 / in LDS: 64 ranges 256 /
+// 241 us, 4,096 354 / 242, 8,192 380 / 242, 12,000 395 / 243 (HBM alone 210). From 786,432 queries on, where
+// staging them costs less than it saves (8,192 ranges, 700,001 queries 6.2 / 6.2, 1,000,003 6.7 / 6.1).
+constexpr uint64_t LREC_MIN_N = 3ull << 18;
+// Queries per lane: up to this many queries in a launch two, so that the chip's waves share them (200,000
+// queries on 4,096 ranges 3.6 us, with six 6.1); beyond it eight, so that many record reads are in flight
+// (2^26 on 65,536 ranges 424 us, with six 428, four 442, two 473). With the records in LDS two are best
+// throughout (three 250, one 330 us against 242).
+constexpr uint64_t FEW_N = 1ull << 20;
 
 template <bool COMP, bool DMA>
 static hipError_t launch_c(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
                            uint8_t* verdict, int32_t* owner, hipStream_t s) {
-    constexpr int QW = 6;  // queries per lane, general records
     if (t.narrow && t.rlog2 == 0) {  // then lift is 2, 4, 6 or 8
-        if (t.lds_rec && n >= LREC_MIN_N && (t.nb > L1_BUCKETS || n < L1_MIN_N))
-            return launch_packed<COMP, DMA, true>(t, d, q, n, verdict, owner, s);
-        return launch_packed<COMP, DMA, false>(t, d, q, n, verdict, owner, s);
+        if (t.lds_rec && n >= LREC_MIN_N)
+            return launch_packed<COMP, DMA, true, 2>(t, d, q, n, verdict, owner, s);
+        if (n <= FEW_N) return launch_packed<COMP, DMA, false, 2>(t, d, q, n, verdict, owner, s);
+        return launch_packed<COMP, DMA, false, 8>(t, d, q, n, verdict, owner, s);
     }
-    return launch_v<COMP, false, 0, QW, DMA, false>(t, d, q, n, verdict, owner, s);
+    if (n <= FEW_N) return launch_v<COMP, false, 0, 2, DMA, false>(t, d, q, n, verdict, owner, s);
+    return launch_v<COMP, false, 0, 6, DMA, false>(t, d, q, n, verdict, owner, s);
 }
 
 hipError_t launch_validate(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,

@@ -190,8 +190,8 @@ def test_insert_remove_interleaved_with_validation():
                                                (8192, False, "6"), (9000, True, None),
                                                (13000, False, None), (15100, False, None)])
 def test_bulk_queries_with_records_in_lds(n_ranges, far, lift, monkeypatch):
-    """From 2^20 queries on, tables whose packed records fit the LDS behind the index are checked from
-    there: small and large tables on either side of that, with 32-bit and 64-bit splitter keys (a far
+    """From 786,432 queries on, tables whose packed records fit the LDS behind the index are checked from
+    there, with as many workgroups as fit or, for more than 2^24 queries, one per CU: small and large tables on either side of that, with 32-bit and 64-bit splitter keys (a far
     range makes the span too wide), pointer and DMA queries, a ragged count."""
     need_gpu()
     if lift:
