@@ -76,6 +76,24 @@ struct DevTable {
     uint32_t pad2;
 };
 
+// Byte index of a large table (validation of large batches, see chunk_bytes). Ranges are numbered in
+// address order, with ids id0, id0 + 1, ...; their bases lie on multiples of 2^u above the first, and 256
+// such units make a bin (up to the last range's end). In LDS:
+//   low[i] (u8): range i's base inside its bin, in units
+//   code[i] (u8): bit 7: not a USER range; bits 0-6: its size rounded down to the float whose bits are
+//     (code << csh) + cbias
+//   bin[r + 2] (u16): the last range of the bins up to r; bin[0] = bin[1] = 0
+struct ByteIndex {
+    const uint4* image;  // as it lies in LDS
+    uint64_t bins_end;   // nbins << (u + 8)
+    uint32_t bytes;      // of the image, a multiple of 16 (0: the table has none)
+    uint32_t code_off, bin_off;
+    uint32_t u, nbins;
+    uint32_t levels;  // bits of the most ranges in a bin
+    uint32_t csh, cbias;
+    int32_t id0;
+};
+
 // Device copy of the public fault log (same field order as agile_fault) + per-launch scratch.
 struct DevLog {
     unsigned long long count;

@@ -1,10 +1,10 @@
 // Batched pointer validation (the API-time classification rule of AgileOS Sections IV-E and
 // V-C, applied to many (addr, len) queries at once).
 //
-// Each workgroup (16 waves, one per CU: the LDS holds the whole search index) stages the
-// table's splitters (every 2^rlog2-th bucket base; 32-bit keys when the table allows exact
-// compression), a run of largest-value sentinels and a radix index over the splitters into LDS
-// once. Every lane then classifies its queries: the radix entry of the address offset gives the
+// Each workgroup (16 waves) stages the table's splitters (every 2^rlog2-th bucket base; 32-bit keys
+// when the table allows exact compression), a run of largest-value sentinels and a radix index over
+// the splitters into LDS once, with the packed records behind them where they fit and the batch is
+// large. Every lane then classifies its queries: the radix entry of the address offset gives the
 // start of a short run of candidate splitters, binary lifting over that run finds the last
 // splitter <= addr (reading past the run is harmless: later splitters and the sentinels compare
 // greater, so the predicate stays monotone and needs no bound checks), and one bucket record
@@ -15,7 +15,8 @@
 // its base with its full size, is reported INEXACT.
 //
 // Two record formats: packed 16-byte records (one load per query; offsets relative to the
-// bucket base, used whenever the table's offsets fit) and general 32-byte records. Queries
+// bucket base, used whenever the table's offsets fit) and general 32-byte records. Large batches on
+// tables whose records do not fit the LDS have an index of their own (chunk_bytes). Queries
 // stream in with coalesced 16-byte loads, the next chunk's queries are in flight while the
 // current chunk is searched, and verdict bytes and owner ids are stored coalesced.
 #include <cstdlib>
@@ -342,9 +343,151 @@ static hipError_t launch_c(const DevTable& t, const DevInfo& d, const void* q, u
     return launch_v<COMP, false, 0, 6, DMA, false>(t, d, q, n, verdict, owner, s);
 }
 
-hipError_t launch_validate(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
-                           uint8_t* verdict, int32_t* owner, bool dma, hipStream_t s) {
+// ---------------------------------------------------------------- byte index (large tables)
+// Tables whose records do not fit into LDS, where two bytes per range do (65,536 ranges: 150 KiB with the
+// bins). The bin of an address and binary lifting over its ranges' low bytes give the range exactly, and
+// its code two bounds of its size, between which most queries fall out the same. Only the lanes left open
+// (a tenth of mixed pointer queries, 59% of DMA checks) read the range's end, so that the vector memory path is left to the
+// streams. The vector units come next; hence 32-bit differences (ranges are shorter than 2^30 and start
+// less than 2^31 apart) and no branch. 2^26 queries on 65,536 ranges 424 -> 264 us, DMA checks 429 -> 373
+// (HBM alone 210; 302 / 282 / 276 with 2, 3 or 6 queries per lane, 327 with 64-bit differences and branches).
+typedef __attribute__((address_space(3))) const uint8_t lds_u8;
+typedef __attribute__((address_space(3))) const uint16_t lds_u16;
+
+template <int QPT, bool DMA, bool TAIL>
+__device__ __forceinline__ void chunk_bytes(const DevTable& t, const ByteIndex& x, uint32_t cbias,
+                                            const ulonglong2 (&q)[QPT], uint64_t n,
+                                            uint8_t* __restrict__ verdict, int32_t* __restrict__ owner,
+                                            uint64_t c0, uint32_t lane) {
+    // this kernel has no other LDS: offsets into the image are addresses
+    lds_u8* low = (lds_u8*)0u;
+    lds_u8* code = (lds_u8*)x.code_off;
+    lds_u16* bin = (lds_u16*)x.bin_off;
+    const uint32_t B = x.u + 8;
+    uint32_t i[QPT], ql[QPT], i0[QPT], i1[QPT], before[QPT], dl[QPT];
+    bool beyond[QPT], first_bin[QPT];
+#pragma unroll
+    for (int j = 0; j < QPT; ++j) {
+        const uint64_t d = q[j].x - t.gmin;
+        beyond[j] = d >= x.bins_end;
+        dl[j] = (uint32_t)d;
+        const uint32_t rd = __builtin_amdgcn_alignbit((uint32_t)(d >> 32), dl[j], B);
+        const uint32_t r = rd < x.nbins - 1 ? rd : x.nbins - 1;
+        ql[j] = __builtin_amdgcn_ubfe(dl[j], x.u, 8);
+        first_bin[j] = r == 0;
+        before[j] = bin[r];
+        i[j] = i0[j] = bin[r + 1];
+        i1[j] = bin[r + 2];
+    }
+    for (uint32_t step = (1u << x.levels) >> 1; step; step >>= 1) {
+        uint32_t to[QPT], v[QPT];
+#pragma unroll
+        for (int j = 0; j < QPT; ++j) {
+            to[j] = i[j] + step < i1[j] ? i[j] + step : i1[j];
+            v[j] = low[to[j]];
+        }
+#pragma unroll
+        for (int j = 0; j < QPT; ++j) i[j] = v[j] <= ql[j] ? to[j] : i[j];
+    }
+    uint32_t lo[QPT], c[QPT];
+#pragma unroll
+    for (int j = 0; j < QPT; ++j) {
+        lo[j] = low[i[j]];
+        c[j] = code[i[j]];
+    }
+    const __amdgpu_buffer_rsrc_t recs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)t.rec, 0, (int)(t.nb * sizeof(PairRec)), 0x00020000);
+    bool first[QPT];
+    uint32_t len[QPT], end[QPT], from[QPT];
+#pragma unroll
+    for (int j = 0; j < QPT; ++j) {
+        // range i starts in an earlier bin: the one before, unless that has none (or is none: bin 0)
+        const bool carry = (i[j] == i0[j]) & !(DMA & first_bin[j]);
+        const bool known = !carry | (i[j] > before[j]);
+        const uint32_t rel = (((carry ? 256u : 0u) - lo[j]) << x.u) + (dl[j] & ((1u << B) - 1));
+        const uint32_t bits = ((c[j] & 127u) << x.csh) + cbias;
+        const uint32_t sure = (uint32_t)__uint_as_float(bits);                 // <= size
+        const uint32_t next = (uint32_t)__uint_as_float(bits + (1u << x.csh));  // > size
+        // what is left of the range from the address on: at least rmin, less than rmax
+        const int32_t rmin = (int32_t)(sure - rel), rmax = (int32_t)(next - rel);
+        len[j] = (uint32_t)(q[j].y >> 32) ? ~0u : (uint32_t)q[j].y;
+        first[j] = known & (rel == 0);
+        const bool fits = (len[j] <= (uint32_t)rmin) & !(DMA & first[j] & (len[j] == sure));
+        const bool in = (rmin > 0) & (fits | (len[j] > (uint32_t)rmax) | (c[j] > 127u));
+        const bool open = !beyond[j] & !(known & (in | (rmax <= 0)));
+        // a lane that is not open asks for an address past the buffer, which reads as zero, and goes on
+        // with rmin (beyond the bins: with -1)
+        const uint32_t at = (i[j] << 4) + ((~i[j] & 1u) << 3);
+        end[j] = __builtin_amdgcn_raw_buffer_load_b32(recs, open ? at : 0x80000000u, 0, 0);
+        const uint32_t closed = beyond[j] ? 1u : rel - sure;
+        from[j] = open ? (uint32_t)q[j].x : closed;
+    }
+#pragma unroll
+    for (int j = 0; j < QPT; ++j) {
+        const int32_t room = (int32_t)(end[j] - from[j]);
+        const bool whole = first[j] & (len[j] == (uint32_t)room);
+        uint32_t v = DMA & !whole ? V_INEXACT : V_ALLOW;
+        v = len[j] > (uint32_t)room ? V_STRADDLE : v;
+        v = c[j] > 127u ? V_PROTECTED : v;
+        v = room <= 0 ? V_UNMAPPED : v;
+        const int32_t id = x.id0 + (int32_t)i[j], o = room <= 0 ? -1 : id;
+        const uint64_t at = c0 + (uint64_t)j * 64u + lane;
+        if (!TAIL || at < n) {
+            __builtin_nontemporal_store((uint8_t)v, verdict + at);
+            __builtin_nontemporal_store(o, owner + at);
+        }
+    }
+}
+
+template <int QPT, bool DMA>
+__global__ __launch_bounds__(VBLOCK) void k_validate_bytes(DevTable t, ByteIndex x,
+                                                            const ulonglong2* __restrict__ q, uint64_t n,
+                                                            uint8_t* __restrict__ verdict,
+                                                            int32_t* __restrict__ owner) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    stage_index(reinterpret_cast<uint4*>(lds_raw), x.image, x.bytes / 16);
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t cbias;  // in a vector register: an instruction takes one scalar, here the shift
+    asm("v_mov_b32 %0, %1" : "=v"(cbias) : "s"(x.cbias));
+    constexpr uint64_t CHUNK = 64u * QPT;
+    const uint64_t nfull = n / CHUNK * CHUNK, stride = (((uint64_t)gridDim.x * VBLOCK) >> 6) * CHUNK;
+    uint64_t c0 = (((uint64_t)blockIdx.x * VBLOCK + threadIdx.x) >> 6) * CHUNK;
+    ulonglong2 y[QPT], z[QPT];
+    if (c0 < nfull) load_chunk<QPT, false>(q, n, c0, lane, y);
+    while (c0 < nfull) {
+        if (c0 + stride < nfull) load_chunk<QPT, false>(q, n, c0 + stride, lane, z);
+        chunk_bytes<QPT, DMA, false>(t, x, cbias, y, n, verdict, owner, c0, lane);
+        c0 += stride;
+        if (c0 >= nfull) break;
+        if (c0 + stride < nfull) load_chunk<QPT, false>(q, n, c0 + stride, lane, y);
+        chunk_bytes<QPT, DMA, false>(t, x, cbias, z, n, verdict, owner, c0, lane);
+        c0 += stride;
+    }
+    if (c0 < n) {
+        load_chunk<QPT, true>(q, n, c0, lane, y);
+        chunk_bytes<QPT, DMA, true>(t, x, cbias, y, n, verdict, owner, c0, lane);
+    }
+}
+
+template <bool DMA>
+static hipError_t launch_bytes(const DevTable& t, const ByteIndex& x, const DevInfo& d, const void* q,
+                               uint64_t n, uint8_t* verdict, int32_t* owner, hipStream_t s) {
+    constexpr int QPT = 4;
+    const void* fn = reinterpret_cast<const void*>(&k_validate_bytes<QPT, DMA>);
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)x.bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_validate_bytes<QPT, DMA>), dim3((uint32_t)d.num_cu), dim3(VBLOCK), x.bytes, s, t, x,
+                       reinterpret_cast<const ulonglong2*>(q), n, verdict, owner);
+    return hipGetLastError();
+}
+
+hipError_t launch_validate(const DevTable& t, const ByteIndex& x, const DevInfo& d, const void* q,
+                           uint64_t n, uint8_t* verdict, int32_t* owner, bool dma, hipStream_t s) {
     if (n == 0) return hipSuccess;
+    if (x.bytes && n >= BYTES_MIN_N) {
+        if (dma) return launch_bytes<true>(t, x, d, q, n, verdict, owner, s);
+        return launch_bytes<false>(t, x, d, q, n, verdict, owner, s);
+    }
     if (dma) {
         if (t.compressed) return launch_c<true, true>(t, d, q, n, verdict, owner, s);
         return launch_c<false, true>(t, d, q, n, verdict, owner, s);

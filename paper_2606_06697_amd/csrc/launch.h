@@ -16,9 +16,15 @@ struct DevInfo {
 // Maximum number of radix entries (plus one) the validation index may use.
 constexpr uint32_t MAX_RADIX = (1u << 14) + 1;
 
+// Least queries of a launch that uses the byte index, if the table has one. Smaller launches are over
+// before the index (twice as long to stage) pays: 65,536 ranges, packed records in L2 against this, 2^19
+// queries 6.2 / 7.1 us, 2^20 8.7 / 7.6, 2^21 15.6 / 10.9; DMA checks 6.3 / 7.3, 9.0 / 8.1, 15.6 / 12.4.
+// Tables whose records fit the LDS are better off there: 8,192 ranges, 2^26 queries 242 against 269 us.
+constexpr uint64_t BYTES_MIN_N = 1ull << 20;
+
 // dma: answer the DMA registration check (only a whole USER range is ALLOW, else INEXACT).
-hipError_t launch_validate(const DevTable& t, const DevInfo& d, const void* q, uint64_t n,
-                           uint8_t* verdict, int32_t* owner, bool dma, hipStream_t s);
+hipError_t launch_validate(const DevTable& t, const ByteIndex& x, const DevInfo& d, const void* q,
+                           uint64_t n, uint8_t* verdict, int32_t* owner, bool dma, hipStream_t s);
 
 // The denials of a copy or triad, which follow from its allowed prefixes and are worked out by the
 // caller (count == 0: none, or not logged); the launch writes them to the log.

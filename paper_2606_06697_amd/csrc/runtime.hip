@@ -125,6 +125,9 @@ struct agile_rt {
     int cur = 0;
     DevLog* d_log = nullptr;
     DevTable tab{};
+    ByteIndex bytes{};       // of the current image, built by a launch that it pays for (byte_index)
+    size_t bytes_at = 0;     // where it goes in the image (0: the table has none, or it is there)
+    uint64_t bytes_seen = 0;  // queries of the launches that could have used it
     size_t stage_bytes = 0;
     agile_fault* hlog = nullptr;
     unsigned long long* htrap = nullptr;  // log count before / after a TRAP-policy call
@@ -136,8 +139,9 @@ struct agile_rt {
 };
 
 // Image layout for nb buckets, the same on the device and in the staging buffer, so that an upload is
-// one copy: split64 | rec | backed | index | nrec | split32 (the first four 64-byte aligned, the others
-// right behind; the last two only where they are needed).
+// one copy: split64 | rec | backed | index | nrec | split32 | byte index (the first four 64-byte aligned, the
+// others right behind; the last three only where they are needed).
+constexpr size_t BYTES_MIN_RANGES = 8192;  // smaller tables have no byte index
 static size_t up64(size_t x) { return (x + 63) & ~(size_t)63; }
 static size_t rec_offset(size_t nb) { return up64(nb * 8); }
 static size_t backed_offset(size_t nb) { return rec_offset(nb) + nb * sizeof(PairRec); }
@@ -145,8 +149,8 @@ static size_t index_offset(size_t nb) { return up64(backed_offset(nb) + nb); }
 // the index is at most as large as the LDS, splitters, sentinels (at most twice the splitters, or 256)
 // and radix entries (at most two per splitter)
 static size_t image_bytes(size_t cap_nb, size_t lds) {
-    return index_offset(cap_nb) + std::min(lds, (3 * cap_nb + 256) * 8 + (2 * cap_nb + 4) * 4) + 64 +
-           cap_nb * 20;
+    return index_offset(cap_nb) + std::min(lds, (3 * cap_nb + 256) * 8 + (2 * cap_nb + 4) * 4) + 128 +
+           cap_nb * 20 + (2 * cap_nb >= BYTES_MIN_RANGES ? lds : 0);
 }
 
 static uint32_t bitlen(uint64_t x) {
@@ -274,6 +278,70 @@ static void search_geometry(DevTable& t, const uint64_t* s64, uint32_t* radix, s
     }
 }
 
+// The byte index of a table (see ByteIndex) at `h`, device address `dev`, of at most `budget` bytes.
+// None (bytes == 0) for tables that it cannot describe: more than 2^16 ranges, ids that do not follow the
+// addresses, ranges of 2^30 bytes or more or that start 2^31 apart, and bases so fine or so far apart that
+// the bins do not fit or that more than a sixteenth of them have no base (an address whose range starts more
+// than a bin before it has to read the range's end).
+static ByteIndex build_bytes(const std::vector<Entry>& E, uint8_t* h, const uint8_t* dev, size_t budget) {
+    ByteIndex x{};
+    const size_t n = E.size(), n16 = (n + 15) & ~(size_t)15;
+    if (n < BYTES_MIN_RANGES || n > (1u << 16) || 2 * n16 > budget) return x;
+    const uint64_t gmin = E[0].base;
+    uint64_t bits = 0, smin = ~0ull, smax = 0, apart = 0;
+    for (size_t i = 0; i < n; ++i) {
+        if (E[i].id != E[0].id + (int32_t)i) return x;
+        const uint64_t s = E[i].end - E[i].base;
+        smin = std::min(smin, s);
+        smax = std::max(smax, s);
+        if (i) apart = std::max(apart, E[i].base - E[i - 1].base);
+        bits |= E[i].base - gmin;
+    }
+    if (smax >> 30 || apart >> 31) return x;
+    const uint32_t u = std::min<uint32_t>(ctz64(bits), 22), B = u + 8;
+    const uint64_t nbins = ((E[n - 1].end - 1 - gmin) >> B) + 1;
+    if (nbins + 2 > (budget - 2 * n16) / 2) return x;
+    const size_t bytes = (2 * n16 + (nbins + 2) * 2 + 15) & ~(size_t)15;
+    if (bytes > budget) return x;
+    // sizes of emin..emin + exps - 1 bits; k bits below the first one are kept
+    const uint32_t emin = bitlen(smin), exps = bitlen(smax) - emin + 1;
+    uint32_t k = 0;
+    while ((exps << (k + 1)) <= 128 && k + 1 < emin) ++k;
+    uint8_t *low = h, *code = h + n16;
+    uint16_t* bin = reinterpret_cast<uint16_t*>(h + 2 * n16);
+    bin[0] = bin[1] = 0;
+    uint64_t r = 0, most = 0, empty = 0;
+    size_t first = 0;  // first range of bin r
+    for (size_t i = 0; i < n; ++i) {
+        const uint64_t d = E[i].base - gmin;
+        if (d >> B != r) {
+            most = std::max<uint64_t>(most, i - first);
+            first = i;
+            empty += (d >> B) - r - 1;
+            while (r < d >> B) bin[r++ + 2] = (uint16_t)(i - 1);
+        }
+        low[i] = (uint8_t)(d >> u);
+        const uint32_t s = (uint32_t)(E[i].end - E[i].base), e = 32 - (uint32_t)__builtin_clz(s);
+        code[i] = (uint8_t)((E[i].kind != AGILE_KIND_USER ? 128u : 0u) | ((e - emin) << k) |
+                            ((s >> (e - 1 - k)) & ((1u << k) - 1)));
+    }
+    empty += nbins - 1 - r;
+    while (r < nbins) bin[r++ + 2] = (uint16_t)(n - 1);
+    if (empty > nbins / 16) return x;
+    x.image = reinterpret_cast<const uint4*>(dev);
+    x.bins_end = nbins << B;
+    x.code_off = (uint32_t)n16;
+    x.bin_off = (uint32_t)(2 * n16);
+    x.u = u;
+    x.nbins = (uint32_t)nbins;
+    x.levels = bitlen(std::max<uint64_t>(most, n - first));
+    x.csh = 23 - k;
+    x.cbias = (emin - 1 + 127) << 23;
+    x.id0 = E[0].id;
+    x.bytes = (uint32_t)bytes;
+    return x;
+}
+
 static void note_stream(agile_rt* rt, hipStream_t s) {
     for (hipStream_t x : rt->streams_used)
         if (x == s) return;
@@ -394,6 +462,9 @@ static int upload(agile_rt* rt, hipStream_t s) {
     im.ready_stream = s;
     rt->cur = x;
     rt->tab = t;
+    rt->bytes = ByteIndex{};
+    rt->bytes_at = !t.lds_rec && !rt->wide_only && n >= BYTES_MIN_RANGES ? up64(bytes) : 0;
+    rt->bytes_seen = 0;
     rt->dirty = false;
     return AGILE_OK;
 }
@@ -413,6 +484,36 @@ static int prepare(agile_rt* rt, hipStream_t s) {
         }
     }
     note_stream(rt, s);
+    return AGILE_OK;
+}
+
+// Before a validation of n queries on s (after prepare): builds the current image's byte index and copies
+// it up, once the launches since the table changed have checked 2^10 queries per range. Built with every
+// upload it would add 3.5 ns of host time per range (65,536 ranges: 510 -> 740 us), and a launch gains
+// about as much from it by then. Not while s is captured: the copy would become part of the graph.
+static int byte_index(agile_rt* rt, uint64_t n, hipStream_t s) {
+    if (!rt->bytes_at || n < BYTES_MIN_N) return AGILE_OK;
+    rt->bytes_seen += std::min<uint64_t>(n, 1ull << 40);
+    if (rt->bytes_seen < (uint64_t)rt->entries.size() << 10) return AGILE_OK;
+    hipStreamCaptureStatus cs;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return AGILE_OK;
+    }
+    if (cs != hipStreamCaptureStatusNone) return AGILE_OK;
+    Image& im = rt->img[rt->cur];
+    const size_t o = rt->bytes_at;
+    rt->bytes_at = 0;
+    uint8_t* h = static_cast<uint8_t*>(im.stage) + o;
+    const ByteIndex x = build_bytes(rt->entries, h, im.dev + o,
+                                    std::min(rt->lds_budget, rt->info.lds_per_block));
+    if (!x.bytes) return AGILE_OK;
+    if (hipMemcpyAsync(im.dev + o, h, x.bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipEventRecord(im.ready, s) != hipSuccess)
+        return AGILE_EDEVICE;
+    im.ready_done = false;
+    im.ready_stream = s;
+    rt->bytes = x;
     return AGILE_OK;
 }
 
@@ -685,7 +786,9 @@ static int validate_common(agile_rt* rt, const agile_ptr* d_q, uint64_t n, uint8
     hipStream_t s = static_cast<hipStream_t>(stream);
     int rc = prepare(rt, s);
     if (rc != AGILE_OK) return rc;
-    if (launch_validate(rt->tab, rt->info, d_q, n, d_verdict, d_owner, dma, s) != hipSuccess)
+    rc = byte_index(rt, n, s);
+    if (rc != AGILE_OK) return rc;
+    if (launch_validate(rt->tab, rt->bytes, rt->info, d_q, n, d_verdict, d_owner, dma, s) != hipSuccess)
         return AGILE_EDEVICE;
     return AGILE_OK;
 }

@@ -191,8 +191,9 @@ def test_insert_remove_interleaved_with_validation():
                                                (13000, False, None), (15100, False, None)])
 def test_bulk_queries_with_records_in_lds(n_ranges, far, lift, monkeypatch):
     """From 786,432 queries on, tables whose packed records fit the LDS behind the index are checked from
-    there, with as many workgroups as fit or, for more than 2^24 queries, one per CU: small and large tables on either side of that, with 32-bit and 64-bit splitter keys (a far
-    range makes the span too wide), pointer and DMA queries, a ragged count."""
+    there, with as many workgroups as fit or, for more than 2^24 queries, one per CU: small and large
+    tables on either side of that, with 32-bit and 64-bit splitter keys (a far range makes the span too
+    wide), pointer and DMA queries, a ragged count."""
     need_gpu()
     if lift:
         monkeypatch.setenv("AGILE_MIN_LIFT", lift)
@@ -208,6 +209,88 @@ def test_bulk_queries_with_records_in_lds(n_ranges, far, lift, monkeypatch):
     assert_same(tw, q, f"{n_ranges} ranges")
     from synth.workloads import make_dma_queries
     q = make_dma_queries(tb, n, n_ranges).numpy().view(np.uint64)
+    qd = torch.from_numpy(q.view(np.int64).copy()).cuda()
+    v = torch.full((n,), 255, dtype=torch.uint8, device="cuda")
+    o = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    tw.g.agile_validate_dma(tw.h, qd, n, v, o)
+    ev, eo = tw.ot.dma_verdict_many(q[:, 0], q[:, 1])
+    assert np.array_equal(v.cpu().numpy(), ev) and np.array_equal(o.cpu().numpy(), eo)
+    tw.close()
+
+
+def _edge_queries(base, size, seed):
+    """Queries around both ends of sampled ranges, whole ranges, and lengths and addresses at the limits."""
+    rng = np.random.default_rng(seed)
+    k = rng.integers(0, base.size, 4000)
+    k[:2] = 0, base.size - 1
+    b, s = base[k], size[k]
+    one = np.ones_like(b)
+    sets = [(b, s), (b, s + one), (b, s - one), (b + s - one, one), (b + s, one), (b - one, one),
+            (b - one, one + one), (b + s - one, one + one), (b, one * np.uint64((1 << 32) + 1)),
+            (b, one * np.uint64(U64_MAX)), (b + one, s - one),
+            (b + rng.integers(0, 1 << 62, b.size).astype(np.uint64) % s, rng.integers(0, 1 << 62, b.size).astype(np.uint64) % s),
+            (rng.integers(0, 1 << 63, b.size).astype(np.uint64), one)]
+    q = np.concatenate([np.stack(x, 1) for x in sets])
+    return np.concatenate([q, np.array([[0, 1], [U64_MAX, U64_MAX], [U64_MAX, 1]], dtype=np.uint64)])
+
+
+def _byte_table(form):
+    """Tables above 15,100 ranges that the byte index describes, or just does not."""
+    if form in ("mixed", "most", "churned"):
+        return make_table({"mixed": 20000, "most": 1 << 16, "churned": 20000}[form], 2500, 3)
+    rng = np.random.default_rng(5)
+    n = 20001
+    size, gap = {
+        "256 in a bin": (np.full(n, 4096), np.full(n, 4096)),
+        "no alignment": (rng.integers(1, 65, n), rng.integers(0, 16, n)),
+        "largest": (rng.integers(1, 1 << 30, n), rng.integers(0, 1 << 24, n)),
+        "too large": (np.where(np.arange(n) == 77, 1 << 30, 4096), np.zeros(n, np.int64)),
+        "empty bins": (np.full(n, 4096), np.where(np.arange(n) % 8000 == 7, 40 << 20, 4096 * 40)),
+        "too many empty bins": (np.full(n, 4096), np.where(np.arange(n) % 2000 == 7, 40 << 20, 4096 * 40)),
+        "far apart": (np.full(n, 4096), np.where(np.arange(n) == 7, 1 << 32, 0)),
+    }[form]
+    align = {"no alignment": 1, "largest": 1 << 22}.get(form, 4096)
+    step = (size + gap + align - 1) // align * align
+    base = (1 << 41) + np.concatenate([[0], np.cumsum(step)[:-1]])
+    kind = rng.choice([0, 0, 0, 1, 2], n)
+    from synth import Table
+    return Table(torch.from_numpy(base), torch.from_numpy(size.astype(np.int64)),
+                 torch.from_numpy(kind.astype(np.uint8)))
+
+
+@pytest.mark.parametrize("form", ["mixed", "most", "churned", "256 in a bin", "no alignment", "largest",
+                                  "too large", "empty bins", "too many empty bins", "far apart"])
+def test_bulk_queries_on_large_tables(form):
+    """From 2^20 queries on, a large table is searched through two bytes per range, if those describe it and
+    2^10 queries per range have been checked since it changed (the first calls here go the general way):
+    bins with many ranges and with none, sizes of one step and of thirty powers of two, bases on any
+    alignment, ids out of order, ranges too large or too far apart; pointer and DMA queries, a ragged
+    count, and fewer queries on the same table."""
+    need_gpu()
+    from synth.workloads import make_dma_queries
+    tb = _byte_table(form)
+    base, size = (x.numpy().astype(np.uint64) for x in (tb.base, tb.size))
+    tw = Twin(base.size)
+    ids = tw.insert_table(tb)
+    if form == "churned":
+        for k in (100, 200):
+            tw.remove(int(ids[k]))
+        for k in (100, 200):
+            tw.insert(int(base[k]), int(size[k]), int(tb.kind[k]))
+    n = (1 << 20) + 77
+    edge = _edge_queries(base, size, 9)
+    q = make_queries(tb, n, 4).numpy().view(np.uint64)
+    q[:edge.shape[0]] = edge
+    q[-1] = edge[1]
+    qd = torch.from_numpy(q.view(np.int64).copy()).cuda()
+    v = torch.full((n,), 255, dtype=torch.uint8, device="cuda")
+    o = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    for _ in range((base.size << 10) // n):
+        tw.g.agile_validate_ptrs(tw.h, qd, n, v, o)
+    assert_same(tw, q, form)
+    assert_same(tw, edge, form)
+    q = make_dma_queries(tb, n, 4).numpy().view(np.uint64)
+    q[:edge.shape[0]] = edge
     qd = torch.from_numpy(q.view(np.int64).copy()).cuda()
     v = torch.full((n,), 255, dtype=torch.uint8, device="cuda")
     o = torch.full((n,), -7, dtype=torch.int32, device="cuda")
