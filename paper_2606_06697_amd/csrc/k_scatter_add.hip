@@ -30,6 +30,8 @@
 //   131,072 x 64         128 us     46 us   (chunks)
 //   1,048,576 x 32       204 us    132 us   (sorted)
 //   1,048,576 x 256      375 us    335 us   (sorted; the reduce alone 297 -> 265)
+#include <type_traits>
+
 #include "launch.h"
 
 namespace agile {
@@ -498,7 +500,7 @@ template <int W, int EPL, bool NT = false>
 __device__ __forceinline__ RowVec<W, EPL> load_row(const uint8_t* src, uint64_t rb, uint32_t row,
                                                    uint64_t col0) {
     using F = typename FloatOf<W>::F;
-    typedef F fv __attribute__((ext_vector_type(EPL)));
+    typedef F fv __attribute__((ext_vector_type(EPL), aligned(W)));
     RowVec<W, EPL> r;
     const F* sp = reinterpret_cast<const F*>(src + (uint64_t)row * rb) + col0;
     const fv* vp = reinterpret_cast<const fv*>(sp);
@@ -509,22 +511,29 @@ __device__ __forceinline__ RowVec<W, EPL> load_row(const uint8_t* src, uint64_t 
 }
 
 // End of a run: an owned destination row gets (its value loaded when the run started + the
-// run's sum) stored back; a shared one gets atomic adds.
+// run's sum) stored back; a shared one gets atomic adds. The first `skip` columns are another lane's.
 template <int W, int EPL>
 __device__ __forceinline__ void srt_flush(uint8_t* dst, uint64_t rb, int64_t row, uint64_t col0,
-                                          bool owned, const RowVec<W, EPL>& old,
+                                          uint32_t skip, bool owned, const RowVec<W, EPL>& old,
                                           const typename FloatOf<W>::F (&acc)[EPL]) {
     using F = typename FloatOf<W>::F;
-    typedef F fv __attribute__((ext_vector_type(EPL)));
+    typedef F fv __attribute__((ext_vector_type(EPL), aligned(W)));
     F* d = reinterpret_cast<F*>(dst + (uint64_t)row * rb) + col0;
     if (owned) {
         fv v;
 #pragma unroll
         for (int q = 0; q < EPL; ++q) v[q] = old.v[q] + acc[q];
-        *reinterpret_cast<fv*>(d) = v;
+        if (EPL == 1 || skip == 0) {
+            *reinterpret_cast<fv*>(d) = v;
+        } else {
+#pragma unroll
+            for (int q = 1; q < EPL; ++q)
+                if ((uint32_t)q >= skip) d[q] = v[q];
+        }
     } else {
 #pragma unroll
-        for (int q = 0; q < EPL; ++q) unsafeAtomicAdd(d + q, acc[q]);
+        for (int q = 0; q < EPL; ++q)
+            if (EPL == 1 || (uint32_t)q >= skip) unsafeAtomicAdd(d + q, acc[q]);
     }
 }
 
@@ -574,8 +583,10 @@ __global__ __launch_bounds__(256, ROW_WAVE ? 4 : 3) void k_srt_reduce(uint8_t* d
         const bool from_prev = head_on && grp > 0, to_next = tail_on && grp + 1 < ng;
         if (lir == 0) whole[grp] = head_on && k0 == klast;
         for (uint64_t cb = 0; cb < D; cb += (uint64_t)EPL << gl) {
-            const uint64_t col0 = cb + (uint64_t)lir * EPL;
-            const bool on = some && col0 < D;
+            // a row that ends inside a vector: its last lane's vector ends with the row
+            const uint64_t c0 = cb + (uint64_t)lir * EPL, col0 = EPL == 1 || c0 + EPL <= D ? c0 : D - EPL;
+            const uint32_t skip = (uint32_t)(c0 - col0);
+            const bool on = some && c0 < D;
             F acc[EPL], head[EPL];  // head: the end of a run that earlier tiles began
 #pragma unroll
             for (int q = 0; q < EPL; ++q) acc[q] = (F)-0.0;
@@ -635,7 +646,7 @@ __global__ __launch_bounds__(256, ROW_WAVE ? 4 : 3) void k_srt_reduce(uint8_t* d
 #pragma unroll
                                     for (int q = 0; q < EPL; ++q) head[q] = acc[q];
                                 } else if (on) {
-                                    srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0,
+                                    srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0, skip,
                                                       !(first && head_on), dcur, acc);
                                 }
 #pragma unroll
@@ -665,7 +676,7 @@ __global__ __launch_bounds__(256, ROW_WAVE ? 4 : 3) void k_srt_reduce(uint8_t* d
 #pragma unroll
                     for (int q = 0; q < EPL; ++q) head[q] = acc[q];
                 } else {
-                    srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0,
+                    srt_flush<W, EPL>(dst, rb, base + (int64_t)cur, col0, skip,
                                       !((first && head_on) || last_on), dcur, acc);
                 }
             }
@@ -687,7 +698,7 @@ __global__ __launch_bounds__(256, ROW_WAVE ? 4 : 3) void k_srt_reduce(uint8_t* d
                     for (int q = 0; q < EPL; ++q) run[q] += part[q][(p << gl) + lir];
 #pragma unroll
                 for (int q = 0; q < EPL; ++q) run[q] += head[q];
-                srt_flush<W, EPL>(dst, rb, base + (int64_t)k0, col0, owned, old, run);
+                srt_flush<W, EPL>(dst, rb, base + (int64_t)k0, col0, skip, owned, old, run);
             }
             __syncthreads();
         }
@@ -771,10 +782,18 @@ static hipError_t scatter_add_sorted(const AddCall& c, uint32_t npasses, void* s
         hipLaunchKernelGGL(k_srt_scan_rows, dim3(p == 0 ? 257 : 256), dim3(SRT_BLOCK), 0, c.s, b, ntiles);
         hipLaunchKernelGGL(k_srt_scatter, dim3(ntiles), dim3(SRT_TB), 0, c.s, b, c.n, p);
     }
-    if ((((uint64_t)c.src | (uint64_t)c.dst | c.rb) & 15) == 0)
-        reduce_sorted<G, W, 16 / W>(c.dst, c.rb, c.src, c.n, c.rg, npasses, b, c.d, c.s, zero_dst);
-    else
-        reduce_sorted<G, W, 1>(c.dst, c.rb, c.src, c.n, c.rg, npasses, b, c.d, c.s, zero_dst);
+    const uint64_t D = c.rb / W;
+    const auto reduce = [&](auto epl) {
+        reduce_sorted<G, W, decltype(epl)::value>(c.dst, c.rb, c.src, c.n, c.rg, npasses, b, c.d, c.s, zero_dst);
+    };
+    // Elements per lane: so many that 33-64 lanes cover a row, if any number does (a wave per row, keys
+    // and guard in scalar registers; with the whole vectors that alignment allowed before, or single
+    // elements, 2^19 rows of 64 floats 135 us against 116, of 65 164 / 131, of 128 174 / 142, 48 doubles
+    // 157 / 127); below that vectors from half a wave's worth on (17 floats 127 / 106), above it whole ones
+    // (129 floats 212 / 165, 65 doubles 190 / 156).
+    if (D <= 16 || (D > 32 && D <= 64)) reduce(std::integral_constant<int, 1>{});
+    else if (W == 8 || (D > 64 && D <= 128)) reduce(std::integral_constant<int, 2>{});
+    else reduce(std::integral_constant<int, 16 / W>{});
     if constexpr (G) {
         const uint64_t sb = (c.n + 255) / 256, cap = (uint64_t)c.d.num_cu * 4;
         const uint32_t grid = (uint32_t)(sb < cap ? sb : cap);

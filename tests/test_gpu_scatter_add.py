@@ -281,3 +281,13 @@ def test_sorted_scatter_add_runs(w, D, rows, n, monkeypatch):
         _add_and_compare(ar, tw, off, w, w * D, _pattern(rng, kind, n, rows), accumulate,
                          f"sorted w={w} D={D} n={n} {kind} accumulate={accumulate}")
     tw.close()
+
+
+@pytest.mark.parametrize("w,D,rows,n", [(4, 5, 3000, 262145), (4, 7, 3000, 262145), (4, 34, 3000, 262145),
+                                        (4, 63, 3000, 262145), (4, 66, 3000, 262145), (4, 127, 3000, 262145),
+                                        (4, 255, 3000, 98700), (4, 257, 3000, 97923),
+                                        (8, 3, 3000, 262145), (8, 64, 3000, 262145), (8, 129, 3000, 97542)])
+def test_sorted_scatter_add_rows_that_end_inside_a_vector(w, D, rows, n, monkeypatch):
+    """A row whose bytes are no multiple of 16 ends with a vector that overlaps the one before: the shared
+    columns are added once, in one pass over the row and in several."""
+    test_sorted_scatter_add_runs(w, D, rows, n, monkeypatch)
