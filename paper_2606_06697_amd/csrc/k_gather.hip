@@ -27,13 +27,18 @@ struct Word<8> {
     using T = uint64_t;
 };
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(1)));  // a vector at any address
 template <>
 struct Word<16> {
-    using T = u32x4;
+    using T = u32x4_any;
 };
 
 // Lane layout shared by both kernels: a row is covered by G = 2^glog2 lanes (one CW-byte chunk
-// each per pass), a wave covers 64/G rows, and each lane keeps R rows in flight. WIDE kernels
+// each per pass), a wave covers 64/G rows, and each lane keeps R rows in flight. Rows of 16 bytes and
+// more move in 16-byte chunks from any address; one that ends inside a chunk ends with a chunk that
+// overlaps the one before, which is written with the same bytes (gathers of 1/4 GiB, against a chunk
+// per element: 17 floats a row 325 -> 178 us, 33 297 -> 144, 65 217 -> 125, 255 160 -> 97, 5 390 -> 347;
+// scatters of 2^19 rows of 17 floats 54 -> 35, 65 135 -> 86). WIDE kernels
 // give a whole wave to each row (G = 64), so a row's index is wave-uniform and its guard test
 // runs on scalar registers.
 struct RowLanes {
@@ -78,7 +83,7 @@ __global__ __launch_bounds__(GBLOCK) void k_gather(DevLog* log, uint8_t* out, co
     using E = typename Word<W>::T;
     constexpr uint32_t EPC = CW / W;  // elements per chunk
     const uint64_t D = rb / W;
-    const uint64_t nch = rb / CW;
+    const uint64_t nch = (rb + CW - 1) / CW;
     const uint64_t Ki = rg.ki, Ko = rg.kc, nfast = rg.nfast;
     const RowGuard g = rg.g;
     const RowLanes L(WIDE ? 6u : glog2);
@@ -88,6 +93,7 @@ __global__ __launch_bounds__(GBLOCK) void k_gather(DevLog* log, uint8_t* out, co
         load_rows<GUARD, WIDE, R>(L, r0, nfast, idx, iv);
         for (uint64_t c0 = 0; c0 < nch; c0 += L.G) {
             const uint64_t ch = c0 + L.lir;
+            const uint64_t off = ch * CW < rb - CW ? ch * CW : rb - CW;
             V v[R];
             uint32_t slow = 0;  // rows of this lane whose chunk takes the exact path
 #pragma unroll
@@ -95,14 +101,14 @@ __global__ __launch_bounds__(GBLOCK) void k_gather(DevLog* log, uint8_t* out, co
                 const uint64_t i = r0 + u * L.rpw + L.riw;
                 const bool on = i < n && ch < nch;
                 const bool fast = on && (!GUARD || (i < nfast && g.rlo <= iv[u] && iv[u] <= g.rhi));
-                if (fast) v[u] = *reinterpret_cast<const V*>(T + (uint64_t)iv[u] * rb + ch * CW);
+                if (fast) v[u] = *reinterpret_cast<const V*>(T + (uint64_t)iv[u] * rb + off);
                 if (on && !fast) slow |= 1u << u;
             }
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 const uint64_t i = r0 + u * L.rpw + L.riw;
                 if (i < n && ch < nch && !((slow >> u) & 1u))
-                    __builtin_nontemporal_store(v[u], reinterpret_cast<V*>(out + i * rb + ch * CW));
+                    __builtin_nontemporal_store(v[u], reinterpret_cast<V*>(out + i * rb + off));
             }
             if (!GUARD || slow == 0) continue;
 #pragma unroll 1
@@ -116,8 +122,7 @@ __global__ __launch_bounds__(GBLOCK) void k_gather(DevLog* log, uint8_t* out, co
                 const uint8_t* trow = T + (uint64_t)x * rb;
                 uint8_t* orow = out + i * rb;
 #pragma unroll 1
-                for (uint32_t k = 0; k < EPC; ++k) {
-                    const uint64_t col = ch * EPC + k;
+                for (uint64_t col = ch * EPC; col < D && col < (ch + 1) * EPC; ++col) {
                     const uint64_t e = i * D + col;
                     E val = 0;
                     if (full || elem_ok(g, x, rb, col, W)) {
@@ -144,7 +149,7 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, u
     using E = typename Word<W>::T;
     constexpr uint32_t EPC = CW / W;
     const uint64_t D = rb / W;
-    const uint64_t nch = rb / CW;
+    const uint64_t nch = (rb + CW - 1) / CW;
     const uint64_t Ki = rg.ki, Ks = rg.kc, nfast = rg.nfast;
     const RowGuard g = rg.g;
     const RowLanes L(WIDE ? 6u : glog2);
@@ -154,6 +159,7 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, u
         load_rows<GUARD, WIDE, R>(L, r0, nfast, idx, iv);
         for (uint64_t c0 = 0; c0 < nch; c0 += L.G) {
             const uint64_t ch = c0 + L.lir;
+            const uint64_t off = ch * CW < rb - CW ? ch * CW : rb - CW;
             V v[R];
             uint32_t slow = 0;
 #pragma unroll
@@ -161,14 +167,14 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, u
                 const uint64_t i = r0 + u * L.rpw + L.riw;
                 const bool on = i < n && ch < nch;
                 const bool fast = on && (!GUARD || (i < nfast && g.rlo <= iv[u] && iv[u] <= g.rhi));
-                if (fast) v[u] = *reinterpret_cast<const V*>(src + i * rb + ch * CW);
+                if (fast) v[u] = *reinterpret_cast<const V*>(src + i * rb + off);
                 if (on && !fast) slow |= 1u << u;
             }
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 const uint64_t i = r0 + u * L.rpw + L.riw;
                 if (i < n && ch < nch && !((slow >> u) & 1u))
-                    *reinterpret_cast<V*>(dst + (uint64_t)iv[u] * rb + ch * CW) = v[u];
+                    *reinterpret_cast<V*>(dst + (uint64_t)iv[u] * rb + off) = v[u];
             }
             if (!GUARD || slow == 0) continue;
 #pragma unroll 1
@@ -182,8 +188,7 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, u
                 uint8_t* drow = dst + (uint64_t)x * rb;
                 const uint8_t* srow = src + i * rb;
 #pragma unroll 1
-                for (uint32_t k = 0; k < EPC; ++k) {
-                    const uint64_t col = ch * EPC + k;
+                for (uint64_t col = ch * EPC; col < D && col < (ch + 1) * EPC; ++col) {
                     const uint64_t e = i * D + col;
                     E val = 0;
                     if (e < Ks) val = *reinterpret_cast<const E*>(srow + col * W);
@@ -275,14 +280,26 @@ static uint32_t lanes_log2(uint64_t nch) {
     return l;
 }
 
-// Rows in flight per lane: more for narrow rows, where each load is a lone random access, and
-// for rows that take a whole wave, where the row's index and guard live in scalar registers.
-constexpr int R_NARROW = 8, R_WIDE = 4, R_ROWWAVE = 8;
-
-// Grid: 4 workgroups per CU, the measured best of 1-16 for rows of a wave or more. Narrow rows
-// (the random-access case) go in one pass instead, with as many workgroups as the rows need:
-// 1.437 ms against 1.458 ms for 2^26 four-byte rows. The same change made the embedding's
-// whole-wave rows slower (0.240 ms against 0.216 ms), so those keep the cap.
+// Rows in flight per lane (R), by what a launch waits for. All on MI355X, us a call.
+// - Few rows (the limits below): latency, so one or two rows and more workgroups; the kernel is also
+//   shorter. 1,000 rows of 1 / 17 / 64 / 256 floats gathered 8.2 / 7.7 / 7.5 / 9.6 with R = 8 / 4 / 4 / 8,
+//   now 6.8 / 6.9 / 6.5 / 7.3; 30,000 of 5 floats 8.5 -> 7.4, 100,000 of 256 38.8 -> 36.0.
+// - Rows of at most 16 bytes, gathered: each load is a lone random access; from an allocation larger than
+//   the L2s one pass of short-lived workgroups with one or two rows a lane beats eight (2^25 four-byte rows
+//   of 2^28, 0.1% denied, 723 -> 682; 2^22 of 2^24 99 -> 91), from smaller ones eight are better beyond
+//   2^20 rows (2^24 rows of 256 / 2^20: 173 / 194 against 202 / 217; of 2^22 284 / 297).
+//   Scattered, beyond the limit: eight (2^20 rows of 8 / 12 / 16 bytes 29 / 35 / 32, with one or two
+//   rows 33 / 40 / 37).
+// - Rows below half a KiB: four (1/4 GiB of 17 / 33 / 64 floats 178 / 144 / 98; two rows 190 / 157 / 107).
+// - Rows that take a whole wave, their index and guard in scalar registers: four (255 floats 97 -> 94, 129
+//   doubles 124 -> 114 against eight). Two are best for uniform rows (92, 103), but 2^20 Zipf rows of 256
+//   floats take 226 instead of 212, so only launches of up to 512 rows per CU take two (2^17 Zipf rows of
+//   511 floats 89 -> 82).
+//
+// Grid: 4 workgroups per CU, the measured best of 1-16 for rows of a wave or more. Gathers of narrow rows
+// go in one pass instead, with as many workgroups as the rows need: 1.437 ms against 1.458 ms for 2^26
+// four-byte rows. The same change made the embedding's whole-wave rows slower (0.240 ms against 0.216 ms),
+// so those keep the cap.
 static uint32_t rows_grid(uint64_t n, uint32_t glog2, int R, const DevInfo& d,
                           bool one_pass = false) {
     const uint64_t rows_per_block = (uint64_t)(GBLOCK / 64) * (64u >> glog2) * R;
@@ -323,24 +340,32 @@ static hipError_t row_launch(const RowCall& c, K kernel, uint32_t grid, const L&
 
 template <bool G, int CW, int W>
 static hipError_t gather_cw(const RowCall& c, void* out, const void* tab) {
-    const uint32_t gl = lanes_log2(c.rb / CW);
+    const uint32_t gl = lanes_log2((c.rb + CW - 1) / CW);
     const auto launch = [&](auto k, uint32_t grid, const auto& fin) {
         hipLaunchKernelGGL(k, dim3(grid), dim3(GBLOCK), 0, c.s, c.log, (uint8_t*)out, (const uint8_t*)tab,
                            c.rb, c.idx, c.n, c.rg, c.logon, gl, fin);
     };
-    if (gl == 6)
-        return row_launch<G>(c, k_gather<G, CW, W, R_ROWWAVE, true>, rows_grid(c.n, gl, R_ROWWAVE, c.d),
-                             launch);
-    if (c.rb <= 16)
-        return row_launch<G>(c, k_gather<G, CW, W, R_NARROW, false>,
-                             rows_grid(c.n, gl, R_NARROW, c.d, true), launch);
-    return row_launch<G>(c, k_gather<G, CW, W, R_WIDE, false>, rows_grid(c.n, gl, R_WIDE, c.d), launch);
+    if (gl == 6) {
+        if (c.n <= (uint64_t)c.d.num_cu * 512)
+            return row_launch<G>(c, k_gather<G, CW, W, 2, true>, rows_grid(c.n, gl, 2, c.d), launch);
+        return row_launch<G>(c, k_gather<G, CW, W, 4, true>, rows_grid(c.n, gl, 4, c.d), launch);
+    }
+    if (c.rb <= 16) {
+        constexpr int R = CW == 16 ? 1 : 2;
+        const bool far = G && c.rg.g.bound && c.rg.g.rlo <= c.rg.g.rhi &&
+                         (uint64_t)c.rg.g.rhi - (uint64_t)c.rg.g.rlo >= (32u << 20) / c.rb;
+        if (far || c.n <= (uint64_t)c.d.num_cu * 4096)
+            return row_launch<G>(c, k_gather<G, CW, W, R, false>, rows_grid(c.n, gl, R, c.d, true), launch);
+        return row_launch<G>(c, k_gather<G, CW, W, 8, false>, rows_grid(c.n, gl, 8, c.d, true), launch);
+    }
+    if (c.n <= (uint64_t)c.d.num_cu * 16 * (64u >> gl))
+        return row_launch<G>(c, k_gather<G, CW, W, 1, false>, rows_grid(c.n, gl, 1, c.d, true), launch);
+    return row_launch<G>(c, k_gather<G, CW, W, 4, false>, rows_grid(c.n, gl, 4, c.d), launch);
 }
 
 template <bool G, int W>
 static hipError_t gather_w(const RowCall& c, void* out, const void* tab) {
-    if (c.rb % 16 == 0 && (((uint64_t)out | (uint64_t)tab) & 15) == 0)
-        return gather_cw<G, 16, W>(c, out, tab);
+    if (c.rb >= 16) return gather_cw<G, 16, W>(c, out, tab);
     return gather_cw<G, W, W>(c, out, tab);
 }
 
@@ -358,24 +383,30 @@ hipError_t launch_gather(bool guard, const GuardTab& t, DevLog* log, const Bind*
 
 template <bool G, int CW, int W>
 static hipError_t scatter_cw(const RowCall& c, void* dst, const void* src) {
-    const uint32_t gl = lanes_log2(c.rb / CW);
+    const uint32_t gl = lanes_log2((c.rb + CW - 1) / CW);
     const auto launch = [&](auto k, uint32_t grid, const auto& fin) {
         hipLaunchKernelGGL(k, dim3(grid), dim3(GBLOCK), 0, c.s, c.log, (uint8_t*)dst, c.rb, c.idx,
                            (const uint8_t*)src, c.n, c.rg, c.logon, gl, fin);
     };
-    if (gl == 6)
-        return row_launch<G>(c, k_scatter<G, CW, W, R_ROWWAVE, true>, rows_grid(c.n, gl, R_ROWWAVE, c.d),
-                             launch);
-    if (c.rb <= 16)
-        return row_launch<G>(c, k_scatter<G, CW, W, R_NARROW, false>, rows_grid(c.n, gl, R_NARROW, c.d),
-                             launch);
-    return row_launch<G>(c, k_scatter<G, CW, W, R_WIDE, false>, rows_grid(c.n, gl, R_WIDE, c.d), launch);
+    if (gl == 6) {
+        if (c.n <= (uint64_t)c.d.num_cu * 512)
+            return row_launch<G>(c, k_scatter<G, CW, W, 2, true>, rows_grid(c.n, gl, 2, c.d), launch);
+        return row_launch<G>(c, k_scatter<G, CW, W, 4, true>, rows_grid(c.n, gl, 4, c.d), launch);
+    }
+    if (c.rb <= 16) {
+        constexpr int R = CW == 16 ? 1 : 2;
+        if (c.n <= (uint64_t)c.d.num_cu * 1024)
+            return row_launch<G>(c, k_scatter<G, CW, W, R, false>, rows_grid(c.n, gl, R, c.d), launch);
+        return row_launch<G>(c, k_scatter<G, CW, W, 8, false>, rows_grid(c.n, gl, 8, c.d), launch);
+    }
+    if (c.n <= (uint64_t)c.d.num_cu * 16 * (64u >> gl))
+        return row_launch<G>(c, k_scatter<G, CW, W, 1, false>, rows_grid(c.n, gl, 1, c.d, true), launch);
+    return row_launch<G>(c, k_scatter<G, CW, W, 4, false>, rows_grid(c.n, gl, 4, c.d), launch);
 }
 
 template <bool G, int W>
 static hipError_t scatter_w(const RowCall& c, void* dst, const void* src) {
-    if (c.rb % 16 == 0 && (((uint64_t)dst | (uint64_t)src) & 15) == 0)
-        return scatter_cw<G, 16, W>(c, dst, src);
+    if (c.rb >= 16) return scatter_cw<G, 16, W>(c, dst, src);
     return scatter_cw<G, W, W>(c, dst, src);
 }
 

@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import Arena, Twin, log_matches, need_gpu
+from gpu_util import Arena, Twin, guard_mod, log_matches, need_gpu
 from oracle import guarded as G
 
 pytestmark = pytest.mark.gpu
@@ -424,3 +424,53 @@ def test_copy_and_triad_at_every_place_in_a_vector(src_off, dst_off):
                     ar.check(what)
                     log_matches(tw, ol, what)
                     tw.close()
+
+
+@pytest.mark.parametrize("w,D", [(4, 5), (4, 6), (4, 7), (4, 34), (4, 129), (4, 255), (4, 257),
+                                 (8, 3), (8, 65), (8, 129)])
+@pytest.mark.parametrize("op", ["gather", "scatter", "scatter-add"])
+def test_rows_that_end_inside_a_vector(op, w, D):
+    """Rows of 16 bytes and more move in 16-byte vectors from any address; one whose bytes are no multiple
+    of 16 ends with a vector that overlaps the one before, and its denials count once."""
+    if op == "gather":
+        test_gather_random_cases(w, D)
+    else:
+        test_scatter_random_cases(w, D, int(op == "scatter-add"))
+
+
+@pytest.mark.parametrize("w,D,n", [(4, 1, 1 << 18), (4, 1, (1 << 18) + 1), (4, 3, (1 << 18) + 1),
+                                   (4, 4, 1 << 18), (4, 4, (1 << 18) + 1), (4, 17, 1 << 15),
+                                   (4, 17, (1 << 15) + 1), (8, 5, (1 << 16) + 1), (4, 130, 1 << 17),
+                                   (4, 130, (1 << 17) + 1), (8, 65, (1 << 17) + 1), (4, 2, (1 << 20) + 1),
+                                   (4, 4, (1 << 20) + 1)])
+def test_rows_around_the_limits_of_a_launch(w, D, n):
+    """As many rows in flight per lane as fit the number of rows and their width: both sides of every
+    limit (for 256 CUs; tables of 16 and 32 MiB), gathered and scattered, with every hundredth index
+    outside the table."""
+    need_gpu()
+    rows, dt = (1 << 21 if n >> 20 else 1 << 18) + 99, torch.float32 if w == 4 else torch.float64
+    gen = torch.Generator(device="cuda").manual_seed(n + D)
+    buf = torch.randn((rows + 8) * D, generator=gen, device="cuda", dtype=dt)
+    table = buf[:rows * D].view(rows, D)
+    idx = torch.randperm(rows, generator=gen, device="cuda")[:n].contiguous()
+    idx[torch.rand(n, generator=gen, device="cuda") < 0.01] = rows + 3
+    ok = (idx < rows).unsqueeze(1)
+    src = torch.randn(n, D, generator=gen, device="cuda", dtype=dt)
+    out = torch.full((n, D), 7.0, device="cuda", dtype=dt)
+    g = guard_mod()
+    rt = g.RangeTable(64)
+    for x in (table, idx, src, out):
+        rt.insert_tensor(x)
+    rt.insert(buf.data_ptr() + rows * D * w, 8 * D * w, g.KIND_PROTECTED)
+    dtype = g.DTYPE_F32 if w == 4 else g.DTYPE_F64
+    g.agile_guarded_gather(rt.handle, out, table, D * w, idx, n, dtype)
+    want = torch.where(ok, table[idx.clamp(max=rows - 1)], torch.zeros((), device="cuda", dtype=dt))
+    assert torch.equal(out, want)
+    bad = int((~ok).sum())
+    assert rt.fault_log()[1]["count"] == bad * D
+    want = table.clone()
+    want[idx[ok.squeeze(1)]] = src[ok.squeeze(1)]
+    g.agile_guarded_scatter(rt.handle, table, D * w, idx, src, n, dtype)
+    assert torch.equal(table, want) and torch.count_nonzero(buf[rows * D:]) > 0
+    assert rt.fault_log()[1]["count"] == 2 * bad * D
+    rt.close()
