@@ -31,8 +31,11 @@ namespace agile {
 constexpr uint32_t SLOT_MAX = 1u << 24;
 constexpr uint32_t GEN_MASK = (1u << 24) - 1;
 constexpr uint32_t OWNER_FREE = 0xFFFFFFFFu, OWNER_RETIRED = 0xFFFFFFFEu;
-constexpr int TBLOCK = 256;
+constexpr int TBLOCK = 256, LBLOCK = 1024;
 constexpr int TPAIRS = 2;  // pairs of tokens per thread
+// Least tokens of a launch that holds the slot records in LDS: 2^20 tokens take 7.4 us a call either way,
+// 2^21 on 256 / 4,096 / 16,384 / 40,960 slots 8.0 / 8.2 / 8.1 / 8.9 with them there, 8.8 / 9.0 / 13.6 / 15.9 without.
+constexpr uint64_t LREC_MIN_N = 1ull << 21;
 
 static __host__ __device__ inline uint64_t splitmix64(uint64_t x) {
     uint64_t z = x + 0x9E3779B97F4A7C15ull;
@@ -86,19 +89,33 @@ typedef uint16_t u16_any __attribute__((aligned(1)));
 // the slot records out of L2. Bound by the record reads, a 128-byte line from L2 for each of them
 // whatever its width (without them 48 us for 2^24 tokens, the streams' time); 4-byte records halve the
 // lines that miss L2 or L1. 2^24 tokens over 2^20 slots: 131 us (141 with 8-byte records and four single
-// tokens a thread), over 2^18 129 (132), 2^14 97 (115), 2^12 64 (69); four pairs a thread 133.
-template <bool PACKED>
-__global__ __launch_bounds__(TBLOCK) void k_tokens_check(
+// tokens a thread), over 2^18 129 (132); four pairs a thread 133.
+//
+// LREC: the packed records in LDS, staged by every workgroup, for large batches on tables that fit there
+// (up to 40,960 slots). The record reads leave the vector memory path, and the streams bound it: 2^24
+// tokens over 2^8 / 2^12 / 2^14 / 40,960 slots 50 / 50 / 51 / 52 us, from L1 and L2 64 / 64 / 99 / 118; with
+// one or four pairs a thread 53-56 / 53-56 (and up to 16 / 17 instead of 13-15 for 2^22).
+template <bool PACKED, bool LREC>
+__global__ __launch_bounds__(LREC ? LBLOCK : TBLOCK) void k_tokens_check(
     const void* __restrict__ recs, uint32_t cap, RecLayout lay, uint64_t key,
     const uint64_t* __restrict__ tok, const uint32_t* __restrict__ cli,
     const uint8_t* __restrict__ kinds, uint64_t n, uint8_t* __restrict__ verdict,
     int32_t* __restrict__ slot_out) {
+    extern __shared__ __align__(16) uint32_t lds_rec[];
+    constexpr int TB = LREC ? LBLOCK : TBLOCK;
+    if (LREC) {
+#pragma unroll 1
+        for (uint32_t k = threadIdx.x; k < (cap + 3) / 4; k += TB)
+            reinterpret_cast<uint4*>(lds_rec)[k] = static_cast<const uint4*>(recs)[k];
+        __syncthreads();
+    }
     const auto record = [&](uint32_t s) {
+        if (LREC) return unpack_rec(lds_rec[s], lay.ob);
         if (PACKED) return unpack_rec(static_cast<const uint32_t*>(recs)[s], lay.ob);
         return static_cast<const uint2*>(recs)[s];
     };
-    const uint64_t np = n / 2, nth = (uint64_t)gridDim.x * TBLOCK;
-    const uint64_t tid = (uint64_t)blockIdx.x * TBLOCK + threadIdx.x;
+    const uint64_t np = n / 2, nth = (uint64_t)gridDim.x * TB;
+    const uint64_t tid = (uint64_t)blockIdx.x * TB + threadIdx.x;
     for (uint64_t p0 = tid; p0 < np; p0 += nth * TPAIRS) {
         u64x2 t[TPAIRS];
         u32x2 c[TPAIRS];
@@ -167,6 +184,7 @@ using agile::token_tag;
 struct agile_tokens {
     int device = 0;
     uint32_t cap = 0;
+    uint32_t num_cu = 0, lds = 0;     // compute units, most LDS of a workgroup
     uint64_t key = 0;
     std::vector<uint2> rec;           // authoritative slot records
     std::set<uint32_t> free_slots;    // released, reusable
@@ -217,8 +235,14 @@ int agile_tokens_create(agile_tokens** out, uint32_t capacity, uint64_t key, int
     if (device < 0 || device >= ndev) return AGILE_EINVAL;
     DeviceGuard dg(device);
     if (!dg.ok) return AGILE_EDEVICE;
+    int num_cu = 0, lds = 0;
+    if (hipDeviceGetAttribute(&num_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+        hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) != hipSuccess)
+        return AGILE_EDEVICE;
     agile_tokens* ts = new (std::nothrow) agile_tokens();
     if (!ts) return AGILE_ENOMEM;
+    ts->num_cu = (uint32_t)num_cu;
+    ts->lds = (uint32_t)lds;
     ts->device = device;
     ts->cap = capacity;
     ts->key = key;
@@ -351,14 +375,21 @@ int agile_tokens_check(agile_tokens* ts, const uint64_t* d_tokens, const uint32_
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int rc = tokens_prepare(ts, s);
     if (rc != AGILE_OK) return rc;
-    const uint64_t per_block = (uint64_t)TBLOCK * TPAIRS;
+    const bool lrec = ts->lay.ob && ts->cap >= 4 && ts->cap <= ts->lds / 4 && n >= agile::LREC_MIN_N;
+    const uint64_t tb = lrec ? agile::LBLOCK : TBLOCK, per_block = tb * TPAIRS;
+    const size_t lds = lrec ? ((size_t)ts->cap + 3) / 4 * 16 : 0;
     uint64_t grid = (n / 2 + per_block - 1) / per_block;
-    // one pass (2^26 tokens took 4% longer with 8 workgroups per CU looping)
-    const uint64_t cap = 1ull << 23;
+    // one pass (2^26 tokens took 4% longer with 8 workgroups per CU looping); with the records in LDS one
+    // workgroup per CU (2^24 tokens on 256 / 16,384 slots 50 / 50 us, with two 54 / 56)
+    const uint64_t cap = lrec ? ts->num_cu : 1ull << 23;
     if (grid > cap) grid = cap;
     if (grid < 1) grid = 1;
-    auto k = ts->lay.ob ? agile::k_tokens_check<true> : agile::k_tokens_check<false>;
-    hipLaunchKernelGGL(k, dim3((uint32_t)grid), dim3(TBLOCK), 0, s, ts->d_rec, ts->cap, ts->lay, ts->key,
-                       d_tokens, d_clients, d_kinds, n, d_verdict, d_slot);
+    auto k = lrec ? agile::k_tokens_check<true, true>
+                  : ts->lay.ob ? agile::k_tokens_check<true, false> : agile::k_tokens_check<false, false>;
+    if (lrec && hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return AGILE_EDEVICE;
+    hipLaunchKernelGGL(k, dim3((uint32_t)grid), dim3((uint32_t)tb), lds, s, ts->d_rec, ts->cap, ts->lay,
+                       ts->key, d_tokens, d_clients, d_kinds, n, d_verdict, d_slot);
     return hipGetLastError() == hipSuccess ? AGILE_OK : AGILE_EDEVICE;
 }

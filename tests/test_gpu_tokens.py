@@ -204,3 +204,39 @@ def test_records_that_outgrow_their_layout(clients):
     minted[tok] = (own, 3)
     check()
     ts.close()
+
+
+@pytest.mark.parametrize("slots", [3, 4, 5, 4097, 40957, 40960, 40961])
+@pytest.mark.parametrize("n", [(1 << 21) - 1, 1 << 21, (1 << 21) + 3])
+def test_large_batches_on_tables_around_the_lds(slots, n):
+    """From 2^21 tokens on the packed records of up to 40,960 slots lie in LDS: both sides of both limits,
+    odd counts, slots past the table, records that are no whole number of vectors."""
+    need_gpu()
+    g = guard_mod()
+    rng = np.random.default_rng(slots)
+    key = int(rng.integers(1, 1 << 62))
+    ts, ot = g.TokenTable(slots, key), T.TokenTable(slots, key)
+    owner, kind = rng.integers(0, 64, slots), rng.integers(0, 4, slots)
+    tok = []
+    for o, k in zip(owner.tolist(), kind.tolist()):
+        tok.append(ts.mint(o, k))
+        assert tok[-1] == ot.mint(o, k)
+    for s in rng.choice(slots, slots // 4, replace=False).tolist():
+        ts.release(tok[s], int(owner[s]))
+        ot.release(tok[s], int(owner[s]))
+    m = 4 * slots + 8  # distinct questions, repeated over the batch
+    t = np.array(tok, np.uint64)[rng.integers(0, slots, m)]
+    c, k = owner[rng.integers(0, slots, m)], kind[rng.integers(0, slots, m)]
+    same = rng.random(m) < 0.6
+    at = (t >> np.uint64(40)).astype(np.int64)
+    c[same], k[same] = owner[at][same], kind[at][same]
+    t[rng.random(m) < 0.1] ^= np.uint64(1 << 45)
+    t[:2] = T.make_token(key, slots, 0), T.make_token(key, (1 << 24) - 1, 0)
+    want = [ot.check(int(x), int(y), int(z)) for x, y, z in zip(t, c, k)]
+    pick = np.concatenate([np.arange(min(m, n)), rng.integers(0, m, n - min(m, n))])
+    v, s = ts.check(torch.from_numpy(t.view(np.int64)[pick]).cuda(),
+                    torch.from_numpy(c.astype(np.int32)[pick]).cuda(),
+                    torch.from_numpy(k.astype(np.uint8)[pick]).cuda())
+    assert np.array_equal(v.cpu().numpy(), np.array([w[0] for w in want], np.uint8)[pick])
+    assert np.array_equal(s.cpu().numpy(), np.array([w[1] for w in want], np.int32)[pick])
+    ts.close()
