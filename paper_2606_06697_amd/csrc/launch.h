@@ -186,8 +186,8 @@ struct BatchArgs {
 };
 
 // Tile sizes of one launch, a request's tiles, and how many workgroups work on `tiles` of them.
-void batch_tile_sizes(uint64_t copy_bytes, uint64_t gather_rows, uint64_t& tile_copy,
-                      uint64_t& tile_rows);
+void batch_tile_sizes(uint64_t copy_bytes, uint64_t gather_rows, uint64_t largest_gather,
+                      uint64_t& tile_copy, uint64_t& tile_rows);
 uint64_t batch_tiles(const BatchReq& q, uint64_t tile_copy, uint64_t tile_rows);
 uint64_t batch_limit_tiles(const BatchReq& q);
 uint32_t batch_pieces(uint64_t tiles);

@@ -1179,7 +1179,7 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
     if (nptrs && (!d_ptrs || !d_ptr_verdict || !d_ptr_owner || ((uint64_t)d_ptrs & 15)))
         return AGILE_EINVAL;
     const uint32_t ncl = (uint32_t)cs->tables.size();
-    uint64_t total_copy = 0, total_rows = 0;
+    uint64_t total_copy = 0, total_rows = 0, most_rows = 0;
     for (uint32_t r = 0; r < nreq; ++r) {
         const agile_request& q = reqs[r];
         if (q.client >= ncl || q.ptr_off > nptrs || q.nptr > nptrs - q.ptr_off) return AGILE_EINVAL;
@@ -1191,9 +1191,10 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
             return AGILE_EINVAL;
         total_copy = q.copy_bytes > U64MAX - total_copy ? U64MAX : total_copy + q.copy_bytes;
         total_rows = q.gather_n > U64MAX - total_rows ? U64MAX : total_rows + q.gather_n;
+        most_rows = std::max<uint64_t>(most_rows, q.gather_n);
     }
     uint64_t tile_copy, tile_rows;
-    batch_tile_sizes(total_copy, total_rows, tile_copy, tile_rows);
+    batch_tile_sizes(total_copy, total_rows, most_rows, tile_copy, tile_rows);
     uint64_t ntiles = 0, limit = 0;
     for (uint32_t r = 0; r < nreq; ++r) {
         ntiles += batch_tiles(reinterpret_cast<const BatchReq&>(reqs[r]), tile_copy, tile_rows);

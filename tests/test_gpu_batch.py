@@ -254,3 +254,39 @@ def test_batch_pointers_with_keys_of_either_width(n_ranges, align):
     assert np.array_equal(pv, ev) and np.array_equal(po, eo)
     assert res[0]["arg"] == int(np.flatnonzero(ev)[0]) and res[0]["done"] == 1
     g.agile_clients_destroy(cs)
+
+
+@pytest.mark.parametrize("n", [133119, 133120, 266239, 266240, 300001])
+def test_batch_gathers_around_the_growth_of_their_tiles(n):
+    """Gather tiles double while the largest gather has more than 64: both sides of each step, beside
+    gathers that end inside a tile, every hundredth index hostile, against torch and the denials' count."""
+    need_gpu()
+    g = guard_mod()
+    rows, gen = 5000, torch.Generator(device="cuda").manual_seed(n)
+    buf = torch.randn(rows + 64, generator=gen, device="cuda")
+    sizes = [n, 1, 2047, 2049, 8193, 65537]
+    idx = torch.randint(0, rows, (sum(sizes),), generator=gen, device="cuda")
+    idx[torch.rand(sum(sizes), generator=gen, device="cuda") < 0.01] = rows + 5
+    out = torch.full((sum(sizes),), 7.0, device="cuda")
+    rt = g.RangeTable(16)
+    for x in (buf[:rows], idx, out):
+        rt.insert_tensor(x)
+    reqs, at = np.zeros(len(sizes), dtype=g.REQUEST_DTYPE), 0
+    for r, k in enumerate(sizes):
+        reqs[r]["gather_out"], reqs[r]["gather_table"] = out.data_ptr() + 4 * at, buf.data_ptr()
+        reqs[r]["gather_idx"], reqs[r]["gather_n"] = idx.data_ptr() + 8 * at, k
+        reqs[r]["gather_row_bytes"] = 4
+        at += k
+    cs = g.agile_clients_create([rt])
+    for few in (False, True):
+        out.fill_(7.0)
+        q = reqs[:1] if few else reqs
+        _, _, res = run_batch(g, cs, q, torch.zeros((1, 2), dtype=torch.int64, device="cuda"), 0)
+        assert (res["done"] == 1).all()
+        m = n if few else sum(sizes)
+        ok = idx[:m] < rows
+        want = torch.where(ok, buf[idx[:m].clamp(max=rows - 1)], torch.zeros((), device="cuda"))
+        assert torch.equal(out[:m], want) and bool((out[m:] == 7.0).all())
+        denied = [int((~p).sum()) for p in ok.split(sizes[:1] if few else sizes)]
+        assert [int(x) for x in res["count"]] == denied
+    g.agile_clients_destroy(cs)
