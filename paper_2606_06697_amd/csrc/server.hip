@@ -2,7 +2,7 @@
 // the device context and executes its clients' mediated requests; Sections IV-C and IV-E: every
 // pointer argument is checked against the calling client's own table before the real work).
 //
-// Host code only; every request runs in the persistent batch kernel through agile_batch_run.
+// Host code only; every request runs in the batched launch through agile_batch_run.
 // The loop polls, in order:
 //  1. retire: launches whose completion event has fired give their requests' latencies and
 //     results (written by the batch kernel straight into pinned host memory) and return their

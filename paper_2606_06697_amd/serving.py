@@ -16,7 +16,7 @@ The native loop (C++, host side) serves the trace open-loop: arrived requests wa
 request is admitted when its output fits in its client's output ring and in the global HBM
 budget for in-flight outputs and a launch slot (stream) is free; every poll retires finished
 launches (their event completed: latencies are recorded, output space is returned) and launches
-the admitted requests as one persistent batch on a free stream, so new work overlaps the
+the admitted requests as one batched launch on a free stream, so new work overlaps the
 batches already on the device. Revocation (Section IV-D, lifetime and revocation): at a given
 time every range of a client's table is removed while other batches are still on the device,
 and its requests from then on are refused; launches made before keep the table they were made
