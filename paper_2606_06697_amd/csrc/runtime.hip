@@ -1190,8 +1190,10 @@ int agile_batch_run(agile_clients* cs, const agile_request* reqs, uint32_t nreq,
                            q.gather_n > ((1ull << 62) - 1) / (q.gather_row_bytes / 4)))
             return AGILE_EINVAL;
         total_copy = q.copy_bytes > U64MAX - total_copy ? U64MAX : total_copy + q.copy_bytes;
-        total_rows = q.gather_n > U64MAX - total_rows ? U64MAX : total_rows + q.gather_n;
-        most_rows = std::max<uint64_t>(most_rows, q.gather_n);
+        const uint32_t sh = batch_row_shift(reinterpret_cast<const BatchReq&>(q));
+        const uint64_t rows = q.gather_n > (U64MAX >> sh) ? U64MAX : q.gather_n << sh;
+        total_rows = rows > U64MAX - total_rows ? U64MAX : total_rows + rows;
+        most_rows = std::max<uint64_t>(most_rows, rows);
     }
     uint64_t tile_copy, tile_rows;
     batch_tile_sizes(total_copy, total_rows, most_rows, tile_copy, tile_rows);

@@ -290,3 +290,47 @@ def test_batch_gathers_around_the_growth_of_their_tiles(n):
         denied = [int((~p).sum()) for p in ok.split(sizes[:1] if few else sizes)]
         assert [int(x) for x in res["count"]] == denied
     g.agile_clients_destroy(cs)
+
+
+@pytest.mark.parametrize("rb", [12, 16, 20, 60, 64, 68, 1020, 1024, 1028])
+def test_batch_gathers_of_wide_rows(rb):
+    """Rows of 16 bytes and more move in vectors, the last one overlapping: every width of a lane group and
+    several passes of a wave, tiles' remainders, hostile indices, an index buffer and an output that end
+    before the rows do, against the oracle byte for byte and in their fault records."""
+    need_gpu()
+    g = guard_mod()
+    D, rows, sizes = rb // 4, 37, [1, 63, 513, 2049]
+    gen = torch.Generator().manual_seed(rb)
+    span = [k * rb + 64 for k in sizes]
+    host = torch.randint(0, 256, (rows * rb + 64 + 2 * sum(span),), dtype=torch.uint8, generator=gen)
+    dev = host.cuda()
+    hidx = torch.randint(0, rows, (sum(sizes) * 2,), generator=gen)
+    hidx[torch.rand(hidx.shape, generator=gen) < 0.05] = rows + 3
+    hidx[torch.rand(hidx.shape, generator=gen) < 0.02] = -(1 << 62)
+    didx = hidx.cuda()
+    mem, ot, rt = Memory(), OracleTable(), g.RangeTable(64)
+    mem.add(dev.data_ptr(), host.numpy())
+    mem.add(didx.data_ptr(), hidx.numpy().view(np.uint8))
+    base = dev.data_ptr()
+    ranges, at, ia = [(base, rows * rb)], base + rows * rb + 64, didx.data_ptr()
+    reqs = np.zeros(2 * len(sizes), dtype=g.REQUEST_DTYPE)
+    for r in range(2 * len(sizes)):
+        n, cut = sizes[r // 2], r % 2           # every other request: buffers that end early
+        ranges.append((at, max(4, n * rb - cut * (2 * rb - 4))))
+        ranges.append((ia, 8 * max(1, n - cut)))
+        reqs[r]["gather_out"], reqs[r]["gather_table"], reqs[r]["gather_idx"] = at, base, ia
+        reqs[r]["gather_n"], reqs[r]["gather_row_bytes"] = n, rb
+        at += n * rb + 64 - (n * rb + 64) % 4
+        ia += 8 * n
+    for b, s in ranges:
+        rt.insert(b, s, 0)
+        ot.insert(b, s, 0)
+    cs = g.agile_clients_create([rt])
+    _, _, res = run_batch(g, cs, reqs, torch.zeros((1, 2), dtype=torch.int64, device="cuda"), 0)
+    assert (res["done"] == 1).all()
+    for r, q in enumerate(reqs):
+        log = G.FaultLog()
+        G.gather_vec(ot, mem, log, r, int(q["gather_out"]), base, rb, int(q["gather_idx"]), int(q["gather_n"]), 4)
+        check_fault(res[r], log, r, r)
+    assert np.array_equal(dev.cpu().numpy(), mem.buffer(dev.data_ptr()))
+    g.agile_clients_destroy(cs)
