@@ -205,7 +205,11 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, u
     if (GUARD && logon) end_faults(acc, log, fin);
 }
 
+// One wave: a place of the launches' denials per lane.
 __global__ void k_log_reset(DevLog* log) {
+    log->place[threadIdx.x].minkey = ~0ull;
+    log->place[threadIdx.x].count = 0;
+    if (threadIdx.x) return;
     log->count = 0;
     log->first_seq = ~0ull;
     log->first_elem = 0;
@@ -216,13 +220,11 @@ __global__ void k_log_reset(DevLog* log) {
     log->first_verdict = 0;
     log->first_owner = -1;
     log->reserved = 0;
-    log->s_minkey = ~0ull;
-    log->s_count = 0;
     for (uint32_t k = 0; k <= TICKETS; ++k) log->ticket[k * TICKET_STRIDE] = 0;
 }
 
 hipError_t launch_log_reset(DevLog* log, hipStream_t s) {
-    hipLaunchKernelGGL(k_log_reset, dim3(1), dim3(1), 0, s, log);
+    hipLaunchKernelGGL(k_log_reset, dim3(1), dim3(FOLD_PLACES), 0, s, log);
     return hipGetLastError();
 }
 

@@ -1,0 +1,62 @@
+"""Denied accesses are no more expensive than allowed ones by much: a client that aims its indices
+outside its allocations must not slow down the launch that it shares the chip with. Each case times a
+call with denials against the same call without any, on the same box and in turn, with a bound well
+above what a launch needs for the exact path and well below what waiting for one memory place costs,
+and checks the log's count and first record over all the calls."""
+import pytest
+import torch
+
+from gpu_util import guard_mod, need_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _times(calls, rounds=7):
+    """Least milliseconds of each of `calls`, taken in turn."""
+    best = [float("inf")] * len(calls)
+    for r in range(rounds + 1):
+        for k, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(3):
+                call()
+            b.record()
+            b.synchronize()
+            if r:
+                best[k] = min(best[k], a.elapsed_time(b) / 3)
+    return best
+
+
+def _indices(n, rows, part, gen):
+    """Uniform rows, and the same with `part` of them `rows + 3`: past the table."""
+    good = torch.randint(0, rows, (n,), generator=gen, device="cuda")
+    bad = torch.rand(n, generator=gen, device="cuda") < part
+    bad[n // 3] = True
+    return good, torch.where(bad, rows + 3, good), int(bad.sum()), int(bad.nonzero()[0])
+
+
+@pytest.mark.parametrize("n,D,rows,part", [(1 << 24, 1, 1 << 26, 0.01), (1 << 24, 1, 1 << 26, 1.0),
+                                           (1 << 20, 3, 1 << 24, 0.3), (1 << 24, 1, 1 << 20, 0.3)])
+def test_denied_rows_of_a_gather_fold_without_waiting_for_each_other(n, D, rows, part):
+    need_gpu()
+    g = guard_mod()
+    gen = torch.Generator(device="cuda").manual_seed(n + D)
+    table = torch.rand(rows, D, generator=gen, device="cuda")
+    out = torch.empty(n, D, device="cuda")
+    good, mixed, nbad, first = _indices(n, rows, part, gen)
+    rt = g.RangeTable(16)
+    for t in (table, out, good, mixed):
+        rt.insert_tensor(t)
+    runs = [0]
+
+    def denied():
+        runs[0] += 1
+        g.agile_guarded_gather(rt.handle, out, table, 4 * D, mixed, n)
+
+    t_ok, t_bad = _times([lambda: g.agile_guarded_gather(rt.handle, out, table, 4 * D, good, n), denied])
+    denied()
+    assert torch.equal(out, torch.where((mixed < rows)[:, None], table[mixed.clamp(max=rows - 1)], 0.0))
+    rc, f = rt.fault_log(clear=True)
+    assert f["count"] == runs[0] * nbad * D and f["first_elem"] == first * D and f["first_operand"] == 1
+    assert t_bad < 2.0 * t_ok, (t_ok, t_bad)
+    rt.close()
