@@ -163,14 +163,14 @@ __device__ inline void copy_tile(uint8_t* dst, const uint8_t* src, uint64_t o0, 
     }
 }
 
-// Row i of a guarded gather whose index is iv.
+// Columns c0, c0 + step, ... of row i of a guarded gather whose index is iv.
 __device__ inline void gather_row(const BatchReq& q, const RowGuard& g, uint64_t D, uint64_t Ko,
-                                  uint64_t i, int64_t iv, FaultAcc& acc) {
+                                  uint64_t i, int64_t iv, uint32_t c0, uint32_t step, FaultAcc& acc) {
     const uint64_t rb = q.gather_row_bytes;
     const bool full = g.rlo <= iv && iv <= g.rhi;
     const uint8_t* trow = reinterpret_cast<const uint8_t*>(q.gather_table) + (uint64_t)iv * rb;
     uint32_t* out = reinterpret_cast<uint32_t*>(q.gather_out);
-    for (uint64_t col = 0; col < D; ++col) {
+    for (uint64_t col = c0; col < D; col += step) {
         const uint64_t e = i * D + col;
         uint32_t val = 0;
         if (full || elem_ok(g, iv, rb, col, 4)) val = *reinterpret_cast<const uint32_t*>(trow + col * 4);
@@ -183,7 +183,9 @@ __device__ inline void gather_row(const BatchReq& q, const RowGuard& g, uint64_t
 // Rows of at least 16 bytes: 2^gl lanes a row, each 16-byte vectors of it from any address; a row that ends
 // inside a vector ends with one that overlaps the one before. Against one thread per row, a word at a time
 // (launches, us): 50,000 rows of 64 / 256 / 1,024 words 107 / 369 / 2,104 -> 22 / 60 / 78, 64 requests of
-// 5,000 rows of 16 / 128 words 105 / 855 -> 23 / 76, one of 2,000 rows of 256 words 343 -> 22.
+// 5,000 rows of 16 / 128 words 105 / 855 -> 23 / 76, one of 2,000 rows of 256 words 343 -> 22. The lanes of a
+// row also share its exact path: 50,000 rows of 64 / 256 words, all denied, 51 / 152 us (by one lane a row 510 /
+// 7,945).
 __device__ inline void gather_tile_wide(const BatchReq& q, const RowsGuard& rg, uint64_t i0, uint64_t i1,
                                         FaultAcc& acc) {
     constexpr int R = 4;  // rows in flight per lane
@@ -219,13 +221,12 @@ __device__ inline void gather_tile_wide(const BatchReq& q, const RowsGuard& rg, 
                     __builtin_amdgcn_raw_buffer_store_b128(
                         v[u], ro, (uint32_t)((r0 + (uint64_t)u * rpp - i0) * rb + off), 0, 2 | 16);
         }
-        if (lir) continue;
 #pragma unroll 1
         for (int u = 0; u < R; ++u) {
             const uint64_t i = r0 + (uint64_t)u * rpp;
             if (fast[u] || i >= i1) continue;
-            if (i >= rg.ki) acc.note((i * D) << 2);
-            gather_row(q, g, D, rg.kc, i, iv[u], acc);
+            if (lir == 0 && i >= rg.ki) acc.note((i * D) << 2);
+            gather_row(q, g, D, rg.kc, i, iv[u], lir, 1u << gl, acc);
         }
     }
 }
@@ -262,7 +263,7 @@ __device__ inline void gather_tile(const BatchReq& q, const RowsGuard& rg, uint6
                 store_out(out + i, v[u]);
             } else if (i < i1) {
                 if (i >= rg.ki) acc.note((i * D) << 2);
-                gather_row(q, g, D, rg.kc, i, iv[u], acc);
+                gather_row(q, g, D, rg.kc, i, iv[u], 0, 1, acc);
             }
         }
     }
@@ -371,6 +372,7 @@ __device__ inline void finish_request(const BatchArgs& A, uint32_t r) {
 // 512 mixed requests take 299 us instead of 287; bound to 64 they take 375.
 __global__ __launch_bounds__(BBLOCK, 6) void k_batch(BatchArgs A) {
     __shared__ uint32_t s_minfail;
+    __shared__ unsigned long long s_denied, s_mindenied;  // a gather piece's denials, least key
     __shared__ __align__(16) unsigned char s_keys[LDS_KEYS];
     const uint32_t tid = threadIdx.x;
     const uint64_t tile = A.tile0 + blockIdx.x / SUB;
@@ -404,6 +406,13 @@ __global__ __launch_bounds__(BBLOCK, 6) void k_batch(BatchArgs A) {
                       o0 + COPY_PASS < t1 ? o0 + COPY_PASS : t1, A.guards[r].copy_ks,
                       A.guards[r].copy_kd);
     } else if (q.gather_n) {
+        // the request's one count is touched once per workgroup: 2^20 rows of a word, 1% denied, 56 us (125
+        // with two atomics per wave)
+        if (tid == 0) {
+            s_denied = 0;
+            s_mindenied = ~0ull;
+        }
+        __syncthreads();
         const uint64_t tile_rows = A.tile_rows >> batch_row_shift(q), rows = tile_rows / SUB;
         const uint64_t i0 = (local - vt - ct) * tile_rows + sub * rows;
         const uint64_t i1 = i0 + rows < q.gather_n ? i0 + rows : q.gather_n;
@@ -412,8 +421,13 @@ __global__ __launch_bounds__(BBLOCK, 6) void k_batch(BatchArgs A) {
         const unsigned long long c = wave_sum_u64(acc.cnt);
         const unsigned long long m = wave_min_u64(acc.mk);
         if ((tid & 63u) == 0 && c) {
-            atomicAdd(&A.scratch[r].gcount, c);
-            atomicMin(&A.scratch[r].gminkey, m);
+            atomicAdd(&s_denied, c);
+            atomicMin(&s_mindenied, m);
+        }
+        __syncthreads();
+        if (tid == 0 && s_denied) {
+            atomicAdd(&A.scratch[r].gcount, s_denied);
+            atomicMin(&A.scratch[r].gminkey, s_mindenied);
         }
     }
     // every wave waits for its own write-through stores and atomics, then the piece is counted

@@ -3,6 +3,7 @@ outside its allocations must not slow down the launch that it shares the chip wi
 call with denials against the same call without any, on the same box and in turn, with a bound well
 above what a launch needs for the exact path and well below what waiting for one memory place costs,
 and checks the log's count and first record over all the calls."""
+import numpy as np
 import pytest
 import torch
 
@@ -59,4 +60,40 @@ def test_denied_rows_of_a_gather_fold_without_waiting_for_each_other(n, D, rows,
     rc, f = rt.fault_log(clear=True)
     assert f["count"] == runs[0] * nbad * D and f["first_elem"] == first * D and f["first_operand"] == 1
     assert t_bad < 2.0 * t_ok, (t_ok, t_bad)
+    rt.close()
+
+
+@pytest.mark.parametrize("n,D,rows,part,bound", [(50_000, 256, 1 << 16, 0.3, 4.0), (50_000, 64, 1 << 18, 1.0, 6.0),
+                                                 (1 << 20, 1, 1 << 24, 0.01, 2.6)])
+def test_denied_rows_of_a_batched_gather_are_shared_by_their_lanes(n, D, rows, part, bound):
+    """A row outside the table is zeroed by as many lanes as would have copied it, and its denials reach the
+    request's record once per workgroup."""
+    need_gpu()
+    g = guard_mod()
+    gen = torch.Generator(device="cuda").manual_seed(n + D)
+    table = torch.rand(rows, D, generator=gen, device="cuda")
+    out = torch.empty(n, D, device="cuda")
+    good, mixed, nbad, first = _indices(n, rows, part, gen)
+    rt = g.RangeTable(16)
+    for t in (table, out, good, mixed):
+        rt.insert_tensor(t)
+    cs = g.agile_clients_create([rt])
+    ptrs = torch.zeros(1, 2, dtype=torch.int64, device="cuda")
+    verdict = torch.zeros(1, dtype=torch.uint8, device="cuda")
+    owner = torch.zeros(1, dtype=torch.int32, device="cuda")
+    result = torch.zeros(72, dtype=torch.uint8, device="cuda")
+
+    def call(idx):
+        q = np.zeros(1, dtype=g.REQUEST_DTYPE)
+        q[0]["gather_out"], q[0]["gather_table"] = out.data_ptr(), table.data_ptr()
+        q[0]["gather_idx"], q[0]["gather_n"], q[0]["gather_row_bytes"] = idx.data_ptr(), n, 4 * D
+        return lambda: g.agile_batch_run(cs, q, ptrs, 0, verdict, owner, result)
+
+    t_ok, t_bad = _times([call(good), call(mixed)])
+    call(mixed)()
+    assert torch.equal(out, torch.where((mixed < rows)[:, None], table[mixed.clamp(max=rows - 1)], 0.0))
+    r = g.batch_results(result, 1)[0]
+    assert r["done"] == 1 and r["count"] == nbad * D and r["first_elem"] == first * D
+    assert t_bad < bound * t_ok, (t_ok, t_bad)
+    g.agile_clients_destroy(cs)
     rt.close()
