@@ -97,3 +97,30 @@ def test_denied_rows_of_a_batched_gather_are_shared_by_their_lanes(n, D, rows, p
     assert t_bad < bound * t_ok, (t_ok, t_bad)
     g.agile_clients_destroy(cs)
     rt.close()
+
+
+@pytest.mark.parametrize("n,D,part", [(33_000, 16, 1.0), (262_144, 1, 0.3)])
+def test_denied_rows_of_a_scatter_add_take_a_group_of_lanes_each(n, D, part):
+    """Rows aimed outside the destination, in calls that add chunk by chunk: as many at a time as
+    allowed rows, not one per wave. Values of a power of two: every sum is exact."""
+    need_gpu()
+    g = guard_mod()
+    rows = 1 << 16
+    gen = torch.Generator(device="cuda").manual_seed(n + D)
+    good, mixed, nbad, first = _indices(n, rows, part, gen)
+    dst, src = torch.zeros(rows, D, device="cuda"), torch.full((n, D), 0.25, device="cuda")
+    rt = g.RangeTable(16)
+    for t in (dst, src, good, mixed):
+        rt.insert_tensor(t)
+    calls = [lambda i=i: g.agile_guarded_scatter(rt.handle, dst, 4 * D, i, src, n, 0, g.SCATTER_ADD)
+             for i in (good, mixed)]
+    t_ok, t_bad = _times(calls)
+    rt.fault_log(clear=True)
+    dst.zero_()
+    calls[1]()
+    want = torch.bincount(mixed[mixed < rows], minlength=rows).float() * 0.25
+    assert torch.equal(dst, want[:, None].expand(rows, D))
+    rc, f = rt.fault_log(clear=True)
+    assert f["count"] == nbad * D and f["first_elem"] == first * D and f["first_operand"] == 2
+    assert t_bad < 2.0 * t_ok, (t_ok, t_bad)
+    rt.close()
