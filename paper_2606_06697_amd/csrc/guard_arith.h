@@ -61,6 +61,12 @@ AGILE_HD inline bool elem_ok(const RowGuard& g, int64_t iv, uint64_t rb, uint64_
     return off >= -(__int128)g.dlo && off + (__int128)W <= (__int128)g.dhi;
 }
 
+// Whether row x has no byte inside the binding. The rows just before rlo and just after rhi may reach into
+// it; the next ones cannot.
+AGILE_HD inline bool row_outside(const RowGuard& g, int64_t x) {
+    return !g.bound || (x < g.rlo && x + 1 < g.rlo) || (x > g.rhi && x - 1 > g.rhi);
+}
+
 // Guard of a row kernel (gather, scatter, scatter-add), fixed for a launch: the readable prefix
 // of the index array, the allowed element prefix of the contiguous operand (out or src), the
 // number of leading rows that pass both (index readable and contiguous row wholly allowed),

@@ -244,7 +244,11 @@ struct FaultAcc {
     unsigned long long cnt = 0;
     unsigned long long mk = ~0ull;
     __device__ __forceinline__ void note(unsigned long long key) {
-        ++cnt;
+        note_run(key, 1);
+    }
+    // n denials, the first of them with the smallest key
+    __device__ __forceinline__ void note_run(unsigned long long key, uint64_t n) {
+        cnt += n;
         mk = key < mk ? key : mk;
     }
 };

@@ -59,7 +59,10 @@ struct RowLanes {
 // matching stores, and only then runs the exact per-element path for the rest, so the guard
 // adds no wait between the R independent loads. The fast test of row i is i < nfast (its index
 // is readable and its contiguous-operand row is wholly allowed: both are prefixes) and
-// rlo <= idx[i] <= rhi (its row-addressed row is wholly inside the binding).
+// rlo <= idx[i] <= rhi (its row-addressed row is wholly inside the binding). A row that has no byte in
+// the binding needs no look at its elements either: a chunk of it is one store of zeros, or none, and
+// one count (gathers of 131,072 rows of 256 floats with 1% / 30% / 100% denied 48 / 91 / 115 us element by
+// element, now 38 / 38 / 38, and 36 without denials; scatters 48 / 90 / 108, now 38 / 37 / 29).
 template <bool GUARD, bool WIDE, int R>
 __device__ __forceinline__ void load_rows(const RowLanes& L, uint64_t r0, uint64_t nfast,
                                           const int64_t* idx, int64_t (&iv)[R]) {
@@ -118,6 +121,12 @@ __global__ __launch_bounds__(GBLOCK) void k_gather(DevLog* log, uint8_t* out, co
                 const bool iok = i < Ki;
                 if (!iok && ch == 0) acc.note((i * D) << 2);  // one 8-byte index load per row
                 const int64_t x = iok ? idx[i] : 0;
+                const uint64_t e0 = i * D + ch * EPC, ne = D - ch * EPC < EPC ? D - ch * EPC : EPC;
+                if (row_outside(g, x) && e0 + ne <= Ko) {
+                    *reinterpret_cast<V*>(out + i * rb + off) = V{};
+                    acc.note_run((e0 << 2) | 1u, ne);
+                    continue;
+                }
                 const bool full = g.rlo <= x && x <= g.rhi;
                 const uint8_t* trow = T + (uint64_t)x * rb;
                 uint8_t* orow = out + i * rb;
@@ -184,6 +193,11 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, u
                 const bool iok = i < Ki;
                 if (!iok && ch == 0) acc.note((i * D) << 2);
                 const int64_t x = iok ? idx[i] : 0;
+                const uint64_t e0 = i * D + ch * EPC, ne = D - ch * EPC < EPC ? D - ch * EPC : EPC;
+                if (row_outside(g, x) && e0 + ne <= Ks) {
+                    acc.note_run((e0 << 2) | 2u, ne);
+                    continue;
+                }
                 const bool full = g.rlo <= x && x <= g.rhi;
                 uint8_t* drow = dst + (uint64_t)x * rb;
                 const uint8_t* srow = src + i * rb;

@@ -124,3 +124,36 @@ def test_denied_rows_of_a_scatter_add_take_a_group_of_lanes_each(n, D, part):
     assert f["count"] == nbad * D and f["first_elem"] == first * D and f["first_operand"] == 2
     assert t_bad < 2.0 * t_ok, (t_ok, t_bad)
     rt.close()
+
+
+@pytest.mark.parametrize("op", ["gather", "scatter"])
+@pytest.mark.parametrize("n,D,rows,part", [(131_072, 256, 1 << 16, 0.1), (131_072, 256, 1 << 16, 1.0),
+                                           (300_000, 256, 1 << 16, 0.1)])
+def test_rows_outside_their_allocation_need_no_look_at_each_element(n, D, rows, part, op):
+    need_gpu()
+    g = guard_mod()
+    gen = torch.Generator(device="cuda").manual_seed(n + D)
+    table = torch.rand(rows, D, generator=gen, device="cuda")
+    flat = torch.rand(n, D, generator=gen, device="cuda")
+    good, mixed, nbad, first = _indices(n, rows, part, gen)
+    rt = g.RangeTable(16)
+    for t in (table, flat, good, mixed):
+        rt.insert_tensor(t)
+    if op == "gather":
+        calls = [lambda i=i: g.agile_guarded_gather(rt.handle, flat, table, 4 * D, i, n) for i in (good, mixed)]
+    else:
+        calls = [lambda i=i: g.agile_guarded_scatter(rt.handle, table, 4 * D, i, flat, n) for i in (good, mixed)]
+    t_ok, t_bad = _times(calls)
+    rt.fault_log(clear=True)
+    before = table.clone()
+    calls[1]()
+    if op == "gather":
+        assert torch.equal(flat, torch.where((mixed < rows)[:, None], table[mixed.clamp(max=rows - 1)], 0.0))
+    else:  # rows that no index names keep their values
+        untouched = torch.bincount(mixed[mixed < rows], minlength=rows) == 0
+        assert torch.equal(table[untouched], before[untouched])
+    rc, f = rt.fault_log(clear=True)
+    assert f["count"] == nbad * D and f["first_elem"] == first * D
+    assert f["first_operand"] == (1 if op == "gather" else 2)
+    assert t_bad < 1.4 * t_ok, (t_ok, t_bad)
+    rt.close()
