@@ -29,6 +29,7 @@
 #include "agile_aperture.h"
 #include "agile_guard.h"
 #include "device_guard.h"
+#include "launch_grid.h"
 #include "va_ranges.h"
 
 using agile::DeviceGuard;
@@ -66,7 +67,7 @@ struct ApBounds {
 
 // A block covers ABLOCK * AQPT consecutive queries per pass, lane-contiguous for each of its
 // AQPT loads; the loads of a pass are issued before any query is classified. The grid covers
-// the queries in one pass (the loop only matters beyond 2^40 queries).
+// the queries in one pass (the loop only matters from 2^33 queries on).
 template <bool REGION>
 __global__ __launch_bounds__(ABLOCK) void k_validate_aperture(ApBounds B, const u64x2* __restrict__ q,
                                                               uint64_t n, uint8_t* __restrict__ verdict,
@@ -387,16 +388,14 @@ int agile_validate_aperture(const agile_aperture* ap, const agile_ptr* d_q, uint
     if (!dg.ok) return AGILE_EDEVICE;
     const ApBounds B{ap->b[0], ap->b[1], ap->b[2], ap->b[3]};
     // one pass per block: a grid-stride loop over a CU-sized grid measured 1.3x slower here
-    const uint64_t per = (uint64_t)ABLOCK * AQPT;
-    uint64_t grid = (n + per - 1) / per;
-    if (grid > (1ull << 30)) grid = 1ull << 30;
+    const uint32_t grid = workgroups(n, (uint64_t)ABLOCK * AQPT, ABLOCK);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const u64x2* q = reinterpret_cast<const u64x2*>(d_q);
     if (d_region)
-        hipLaunchKernelGGL(k_validate_aperture<true>, dim3((uint32_t)grid), dim3(ABLOCK), 0, s, B,
+        hipLaunchKernelGGL(k_validate_aperture<true>, dim3(grid), dim3(ABLOCK), 0, s, B,
                            q, n, d_verdict, d_region);
     else
-        hipLaunchKernelGGL(k_validate_aperture<false>, dim3((uint32_t)grid), dim3(ABLOCK), 0, s, B,
+        hipLaunchKernelGGL(k_validate_aperture<false>, dim3(grid), dim3(ABLOCK), 0, s, B,
                            q, n, d_verdict, d_region);
     return hipGetLastError() == hipSuccess ? AGILE_OK : AGILE_EDEVICE;
 }

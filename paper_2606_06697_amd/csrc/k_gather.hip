@@ -315,14 +315,12 @@ static uint32_t lanes_log2(uint64_t nch) {
 // Grid: 4 workgroups per CU, the measured best of 1-16 for rows of a wave or more. Gathers of narrow rows
 // go in one pass instead, with as many workgroups as the rows need: 1.437 ms against 1.458 ms for 2^26
 // four-byte rows. The same change made the embedding's whole-wave rows slower (0.240 ms against 0.216 ms),
-// so those keep the cap.
+// so those keep the cap. One pass only as far as a grid holds it (2^31 twelve-byte or 2^33 four-byte rows of
+// a large allocation): beyond that a wave takes further rows.
 static uint32_t rows_grid(uint64_t n, uint32_t glog2, int R, const DevInfo& d,
                           bool one_pass = false) {
     const uint64_t rows_per_block = (uint64_t)(GBLOCK / 64) * (64u >> glog2) * R;
-    uint64_t want = (n + rows_per_block - 1) / rows_per_block;
-    const uint64_t cap = one_pass ? (1ull << 30) : (uint64_t)d.num_cu * 4;
-    if (want < 1) want = 1;
-    return (uint32_t)(want < cap ? want : cap);
+    return workgroups(n, rows_per_block, GBLOCK, one_pass ? ~0ull : (uint64_t)d.num_cu * 4);
 }
 
 struct RowCall {  // a row kernel's launch, and what its denials need

@@ -132,17 +132,11 @@ __global__ __launch_bounds__(SBLOCK) void k_triad(StreamFault f, DevLog* log, fl
 // split), and against 0.51-0.60 ms for the triad with blocks of 64-256 threads and 2-4 vectors.
 // One vector a thread, blocks of 128 / 256 threads: 256 MiB copy 83.9 / 83.7 us, from an odd address
 // 90.2 / 89.6; triad of 2^25 61.5 / 62.8.
-static uint32_t stream_grid(uint64_t nv, uint64_t block) {
-    uint64_t want = (nv + block - 1) / block;
-    const uint64_t cap = 1ull << 30;  // beyond 2^37 vectors the loop takes further passes
-    if (want < 1) want = 1;
-    return (uint32_t)(want < cap ? want : cap);
-}
-
+// As far as a grid holds it: from 2^32 vectors (64 GiB) on a thread takes further ones.
 hipError_t launch_copy(bool guard, const StreamFault& f, DevLog* log, const Bind* binds, void* dst,
                        const void* src, uint64_t n, unsigned long long seq, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    const dim3 grid(stream_grid(n / 16, CBLOCK)), block(CBLOCK);
+    const dim3 grid(workgroups(n / 16, CBLOCK, CBLOCK)), block(CBLOCK);
     if (guard)
         hipLaunchKernelGGL(k_copy<true>, grid, block, 0, s, f, log, (uint8_t*)dst, (const uint8_t*)src, n,
                            clip_prefix(binds[0], (uint64_t)src, n, 1),
@@ -157,7 +151,7 @@ hipError_t launch_triad(bool guard, const StreamFault& f, DevLog* log, const Bin
                         const float* b, const float* c, float sc, uint64_t n,
                         unsigned long long seq, hipStream_t s) {
     if (n == 0) return hipSuccess;
-    const dim3 grid(stream_grid(n / 4, SBLOCK)), block(SBLOCK);
+    const dim3 grid(workgroups(n / 4, SBLOCK, SBLOCK)), block(SBLOCK);
     if (guard)
         hipLaunchKernelGGL(k_triad<true>, grid, block, 0, s, f, log, a, b, c, sc, n,
                            clip_prefix(binds[2], (uint64_t)a, n, 4),

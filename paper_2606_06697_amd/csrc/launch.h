@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "guard_device.h"
+#include "launch_grid.h"
 
 namespace agile {
 
