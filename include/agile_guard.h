@@ -28,7 +28,8 @@
  *    read the previous table).
  *  - Threading: one handle must not be used from two host threads at once, and guarded
  *    calls on one handle that run concurrently on different streams race on its fault
- *    scratch; order them (one stream, or events).
+ *    scratch; order them (one stream, or events). What the log holds of calls that were not
+ *    ordered is unspecified; ordered calls after them are logged as always.
  *  - Guard denials are not errors: validation reports them as verdicts, guarded kernels
  *    suppress them (loads read zero bits, stores are dropped) and count them in the log.
  *  - Overlap: a guarded kernel's output must not alias its inputs except an elementwise

@@ -20,6 +20,7 @@
 #include <type_traits>
 
 #include "guard_arith.h"
+#include "ticket.h"
 
 namespace agile {
 
@@ -120,11 +121,8 @@ struct DevLog {
     // after another, and each wave with a denial adds to one: 2^24 four-byte rows of 2^26 gathered, 1% /
     // 30% / all of them denied, 1,208 / 1,632 / 1,590 us with a single place, 339 / 291 / 102 with 64.
     FaultPlace place[FOLD_PLACES];
-    // workgroups of the launch that are done, counted in TICKETS places a memory channel apart (one
-    // place takes about 20 ns a workgroup, one after another), and the places that are full
-    uint32_t ticket[(32 + 1) * 64];
+    uint64_t ticket[TICKET_WORDS];  // workgroups that are done (last_workgroup)
 };
-constexpr uint32_t TICKETS = 32, TICKET_STRIDE = 64;
 
 // A table of at most INLINE_RANGES ranges in a launch's own arguments (entries in address order), for
 // the reason of its first denial.
@@ -360,6 +358,15 @@ __device__ inline void finish_faults(const Look& look, DevLog* log, const FaultS
     }
 }
 
+struct TicketAtomics {
+    __device__ __forceinline__ void raise(uint64_t* w, uint64_t v) const {
+        (void)__hip_atomic_fetch_max(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ uint64_t add(uint64_t* w) const {
+        return __hip_atomic_fetch_add(w, (uint64_t)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+};
+
 // End of a guarded row kernel, called by every thread of every workgroup of the launch: folds the
 // denials, and in a fused launch the last workgroup to get here finishes them.
 __device__ inline void end_faults(const FaultAcc& acc, DevLog* log, const FinishArgs& fin) {
@@ -369,20 +376,8 @@ __device__ inline void end_faults(const FaultAcc& acc, DevLog* log, const Finish
     // every wave waits for its own atomics, then the workgroup is counted
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t last = 1;
-        const uint32_t nb = gridDim.x;
-        if (nb > 1) {
-            const uint32_t s = blockIdx.x % TICKETS, full = (nb - s + TICKETS - 1) / TICKETS;
-            uint32_t* mine = log->ticket + s * TICKET_STRIDE;
-            uint32_t* top = log->ticket + TICKETS * TICKET_STRIDE;
-            const uint32_t places = nb < TICKETS ? nb : TICKETS;
-            // atomicInc goes back to 0 after its bound: the counts are ready for the next launch
-            last = atomicInc(mine, full - 1) == full - 1;
-            if (last) last = atomicInc(top, places - 1) == places - 1;
-        }
-        s_last = last;
-    }
+    if (threadIdx.x == 0)
+        s_last = gridDim.x == 1 || last_workgroup(TicketAtomics{}, log->ticket, fin.seq, blockIdx.x, gridDim.x);
     __syncthreads();
     if (s_last && threadIdx.x < 64) finish_faults(InlineLook{fin.tab}, log, fin.site, fin.seq);
 }

@@ -219,8 +219,11 @@ __global__ __launch_bounds__(GBLOCK) void k_scatter(DevLog* log, uint8_t* dst, u
     if (GUARD && logon) end_faults(acc, log, fin);
 }
 
-// One wave: a place of the launches' denials per lane.
-__global__ void k_log_reset(DevLog* log) {
+// One wave: a place of the launches' denials per lane. The tickets are set up once, for a new log.
+__global__ void k_log_reset(DevLog* log, uint32_t fresh) {
+    if (fresh)
+        for (uint32_t k = threadIdx.x; k < TICKET_WORDS / TICKET_STRIDE; k += FOLD_PLACES)
+            log->ticket[k * TICKET_STRIDE] = 0;
     log->place[threadIdx.x].minkey = ~0ull;
     log->place[threadIdx.x].count = 0;
     if (threadIdx.x) return;
@@ -234,11 +237,10 @@ __global__ void k_log_reset(DevLog* log) {
     log->first_verdict = 0;
     log->first_owner = -1;
     log->reserved = 0;
-    for (uint32_t k = 0; k <= TICKETS; ++k) log->ticket[k * TICKET_STRIDE] = 0;
 }
 
-hipError_t launch_log_reset(DevLog* log, hipStream_t s) {
-    hipLaunchKernelGGL(k_log_reset, dim3(1), dim3(FOLD_PLACES), 0, s, log);
+hipError_t launch_log_reset(DevLog* log, hipStream_t s, bool fresh) {
+    hipLaunchKernelGGL(k_log_reset, dim3(1), dim3(FOLD_PLACES), 0, s, log, (uint32_t)fresh);
     return hipGetLastError();
 }
 
@@ -257,15 +259,16 @@ hipError_t launch_fault_finish(const GuardTab& t, DevLog* log, const FaultSite& 
     return hipGetLastError();
 }
 
-// The workgroups count themselves up to this grid: 64 rows of 4 bytes 7.9 us a call against 10.9 with a
-// finishing kernel, 2^21 rows (1,024 workgroups) 33.9 / 34.5, 2^23 (4,096) 126 / 127 without denials and
-// 161 / 157 with 0.1%, 2^25 (16,384) 517 / 509.
+// The workgroups count themselves up to this grid. With a finishing kernel / counted, gathers without denials
+// and with 0.1%: 1,000 rows of 64 floats 8.7 / 5.8 us and 9.1 / 7.0, 2^19 rows of 4 bytes (1,024 workgroups)
+// 9.5 / 7.4 and 11.4 / 10.2, 2^20 (2,048) 13.0 / 12.7 and 16.3 / 16.8, 2^22 (8,192) 76.2 / 75.5 and 80.8 / 80.8.
 constexpr uint64_t FUSE_GRID = 2048;
 
 FinishArgs finish_args(const GuardTab& t, const FaultSite& f, unsigned long long seq, uint64_t grid,
-                       bool wanted) {
+                       bool wanted, hipStream_t s) {
+    static_assert(FUSE_GRID < 1u << TICKET_COUNT_BITS, "a word counts a launch's workgroups");
     FinishArgs a;
-    a.fused = wanted && t.inl && grid <= FUSE_GRID;
+    a.fused = wanted && t.inl && grid <= FUSE_GRID && !is_captured(s);
     a.seq = seq;
     if (a.fused) {
         a.tab = *t.inl;
@@ -343,7 +346,7 @@ template <bool G, class K, class L>
 static hipError_t row_launch(const RowCall& c, K kernel, uint32_t grid, const L& launch) {
     const bool wanted = G && c.logon && c.finish;
     if constexpr (G) {
-        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted);
+        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted, c.s);
         launch(kernel, grid, fin);
         if (wanted && !fin.fused) return launch_fault_finish(c.t, c.log, c.site, c.seq, c.s);
     } else {

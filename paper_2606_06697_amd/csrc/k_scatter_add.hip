@@ -809,7 +809,7 @@ static hipError_t scatter_add_sorted(const AddCall& c, uint32_t npasses, void* s
         const uint64_t sb = (c.n + 255) / 256, cap = (uint64_t)c.d.num_cu * 4;
         const uint32_t grid = (uint32_t)(sb < cap ? sb : cap);
         const bool wanted = c.logon && c.finish;
-        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted);
+        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted, c.s);
         hipLaunchKernelGGL((k_srt_slow<W>), dim3(grid), dim3(256), 0, c.s, c.log, c.dst, c.rb, c.idx, c.src,
                            c.n, c.rg, b, npasses, c.logon, fin);
         if (wanted && !fin.fused) return launch_fault_finish(c.t, c.log, c.site, c.seq, c.s);
@@ -827,7 +827,7 @@ static hipError_t scatter_add_chunks(const AddCall& c, uint32_t gl) {
     };
     if constexpr (G) {
         const bool wanted = c.logon && c.finish;
-        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted);
+        const FinishArgs fin = finish_args(c.t, c.site, c.seq, grid, wanted, c.s);
         launch(fin);
         if (wanted && !fin.fused) return launch_fault_finish(c.t, c.log, c.site, c.seq, c.s);
     } else {

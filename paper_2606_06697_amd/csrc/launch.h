@@ -89,7 +89,8 @@ inline bool scatter_add_sorts(uint64_t n, uint64_t rb) {
     return n > (1u << 18) || (n >= (1u << 15) && n * rb > (96u << 20));
 }
 
-hipError_t launch_log_reset(DevLog* log, hipStream_t s);
+// fresh: a log that no launch has used yet.
+hipError_t launch_log_reset(DevLog* log, hipStream_t s, bool fresh = false);
 
 // Redirecting policies (sink to a quarantine, report): the pass after a guarded kernel.
 constexpr uint32_t REDIRECT_SINK = 1, REDIRECT_REPORT = 2, REDIRECT_REMAP = 3;
@@ -123,10 +124,19 @@ hipError_t launch_fault_finish(const GuardTab& t, DevLog* log, const FaultSite& 
                                unsigned long long seq, hipStream_t s);
 FaultSite rows_fault_site(uint32_t op, uint32_t w, uint32_t row_operand, uint64_t rb, uint64_t ki,
                           const void* idx, const void* cont, const void* rowp);
+// Whether work queued on s becomes part of a graph (true also where that cannot be told).
+inline bool is_captured(hipStream_t s) {
+    hipStreamCaptureStatus c;
+    if (hipStreamIsCapturing(s, &c) == hipSuccess) return c != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // The finishing arguments of a launch of `grid` workgroups: fused when the table is in the arguments
-// and the launch is small enough for its workgroups to count themselves.
+// and the launch is small enough for its workgroups to count themselves. Launches that are captured end
+// with the finishing kernel: replays of one launch share its number.
 FinishArgs finish_args(const GuardTab& t, const FaultSite& f, unsigned long long seq, uint64_t grid,
-                       bool wanted);
+                       bool wanted, hipStream_t s);
 
 // ---- batched multi-client launch (device images of the public request/result layouts) ----
 struct BatchReq {

@@ -495,12 +495,7 @@ static int byte_index(agile_rt* rt, uint64_t n, hipStream_t s) {
     if (!rt->bytes_at || n < BYTES_MIN_N) return AGILE_OK;
     rt->bytes_seen += std::min<uint64_t>(n, 1ull << 40);
     if (rt->bytes_seen < (uint64_t)rt->entries.size() << 10) return AGILE_OK;
-    hipStreamCaptureStatus cs;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return AGILE_OK;
-    }
-    if (cs != hipStreamCaptureStatusNone) return AGILE_OK;
+    if (is_captured(s)) return AGILE_OK;
     Image& im = rt->img[rt->cur];
     const size_t o = rt->bytes_at;
     rt->bytes_at = 0;
@@ -627,7 +622,7 @@ int agile_rt_create(agile_rt** out, uint32_t capacity, int device) {
         agile_rt_destroy(rt);
         return AGILE_ENOMEM;
     }
-    if (launch_log_reset(rt->d_log, nullptr) != hipSuccess ||
+    if (launch_log_reset(rt->d_log, nullptr, true) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
         agile_rt_destroy(rt);
         return AGILE_EDEVICE;
