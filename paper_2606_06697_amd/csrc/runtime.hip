@@ -44,6 +44,11 @@ struct Image {
     hipStream_t ready_stream = nullptr;
     bool uploaded = false;
     bool ready_done = false;         // the upload is known to have completed
+    // The same of the byte index, which is copied in behind it by a later launch. An event of its own: what
+    // reads the rest of the image has nothing to wait for.
+    hipEvent_t bytes_ready = nullptr;
+    hipStream_t bytes_stream = nullptr;
+    bool bytes_copied = false, bytes_done = false;
     // Recorded, when this image stopped being current, on every stream that had launched with
     // it: the next upload into it waits for these (that is, for its last readers) only.
     std::vector<hipEvent_t> retired;
@@ -357,6 +362,8 @@ static int upload(agile_rt* rt, hipStream_t s) {
     Image& im = rt->img[x];
     // the staging buffer may still feed this image's previous upload
     if (im.uploaded && hipEventSynchronize(im.ready) != hipSuccess) return AGILE_EDEVICE;
+    if (im.bytes_copied && hipEventSynchronize(im.bytes_ready) != hipSuccess) return AGILE_EDEVICE;
+    im.bytes_copied = false;
     const uint32_t n = (uint32_t)rt->entries.size();
     const uint32_t nb = (n + 1) / 2;
     uint8_t* h = static_cast<uint8_t*>(im.stage);
@@ -487,28 +494,43 @@ static int prepare(agile_rt* rt, hipStream_t s) {
     return AGILE_OK;
 }
 
-// Before a validation of n queries on s (after prepare): builds the current image's byte index and copies
-// it up, once the launches since the table changed have checked 2^10 queries per range. Built with every
+// The byte index for a validation of n queries on s (after prepare), or none. Builds the current image's and
+// copies it up once the launches since the table changed have checked 2^10 queries per range. Built with every
 // upload it would add 3.5 ns of host time per range (65,536 ranges: 510 -> 740 us), and a launch gains
-// about as much from it by then. Not while s is captured: the copy would become part of the graph.
-static int byte_index(agile_rt* rt, uint64_t n, hipStream_t s) {
-    if (!rt->bytes_at || n < BYTES_MIN_N) return AGILE_OK;
-    rt->bytes_seen += std::min<uint64_t>(n, 1ull << 40);
-    if (rt->bytes_seen < (uint64_t)rt->entries.size() << 10) return AGILE_OK;
-    if (is_captured(s)) return AGILE_OK;
+// about as much from it by then. Not while s is captured: the copy would become part of the graph. Nor can a
+// captured stream ask or wait for a copy that another one made: unless it is known to be done, it goes without.
+static int byte_index(agile_rt* rt, uint64_t n, hipStream_t s, ByteIndex* x) {
+    *x = ByteIndex{};
+    if (n < BYTES_MIN_N) return AGILE_OK;
     Image& im = rt->img[rt->cur];
+    if (rt->bytes.bytes) {
+        if (!im.bytes_done && im.bytes_stream != s) {
+            if (is_captured(s)) return AGILE_OK;
+            const hipError_t q = hipEventQuery(im.bytes_ready);
+            if (q == hipSuccess) {
+                im.bytes_done = true;
+            } else if (q != hipErrorNotReady || hipStreamWaitEvent(s, im.bytes_ready, 0) != hipSuccess) {
+                return AGILE_EDEVICE;
+            }
+        }
+        *x = rt->bytes;
+        return AGILE_OK;
+    }
+    if (!rt->bytes_at) return AGILE_OK;
+    rt->bytes_seen += std::min<uint64_t>(n, 1ull << 40);
+    if (rt->bytes_seen < (uint64_t)rt->entries.size() << 10 || is_captured(s)) return AGILE_OK;
     const size_t o = rt->bytes_at;
     rt->bytes_at = 0;
     uint8_t* h = static_cast<uint8_t*>(im.stage) + o;
-    const ByteIndex x = build_bytes(rt->entries, h, im.dev + o,
+    const ByteIndex b = build_bytes(rt->entries, h, im.dev + o,
                                     std::min(rt->lds_budget, rt->info.lds_per_block));
-    if (!x.bytes) return AGILE_OK;
-    if (hipMemcpyAsync(im.dev + o, h, x.bytes, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipEventRecord(im.ready, s) != hipSuccess)
-        return AGILE_EDEVICE;
-    im.ready_done = false;
-    im.ready_stream = s;
-    rt->bytes = x;
+    if (!b.bytes) return AGILE_OK;
+    if (hipMemcpyAsync(im.dev + o, h, b.bytes, hipMemcpyHostToDevice, s) != hipSuccess) return AGILE_EDEVICE;
+    im.bytes_copied = true;
+    im.bytes_done = false;
+    im.bytes_stream = s;
+    if (hipEventRecord(im.bytes_ready, s) != hipSuccess) return AGILE_EDEVICE;
+    *x = rt->bytes = b;
     return AGILE_OK;
 }
 
@@ -608,7 +630,8 @@ int agile_rt_create(agile_rt** out, uint32_t capacity, int device) {
         Image& im = rt->img[k];
         im.dev = d;
         if (hipHostMalloc(&im.stage, rt->stage_bytes, hipHostMallocDefault) != hipSuccess ||
-            hipEventCreateWithFlags(&im.ready, hipEventDisableTiming) != hipSuccess) {
+            hipEventCreateWithFlags(&im.ready, hipEventDisableTiming) != hipSuccess ||
+            hipEventCreateWithFlags(&im.bytes_ready, hipEventDisableTiming) != hipSuccess) {
             agile_rt_destroy(rt);
             return AGILE_ENOMEM;
         }
@@ -638,6 +661,7 @@ int agile_rt_destroy(agile_rt* rt) {
     if (hipDeviceSynchronize() != hipSuccess) rc = AGILE_EDEVICE;
     for (Image& im : rt->img) {
         if (im.ready) (void)hipEventDestroy(im.ready);
+        if (im.bytes_ready) (void)hipEventDestroy(im.bytes_ready);
         if (im.stage) (void)hipHostFree(im.stage);
         drop_events(im.retired);
     }
@@ -781,9 +805,10 @@ static int validate_common(agile_rt* rt, const agile_ptr* d_q, uint64_t n, uint8
     hipStream_t s = static_cast<hipStream_t>(stream);
     int rc = prepare(rt, s);
     if (rc != AGILE_OK) return rc;
-    rc = byte_index(rt, n, s);
+    ByteIndex x;
+    rc = byte_index(rt, n, s, &x);
     if (rc != AGILE_OK) return rc;
-    if (launch_validate(rt->tab, rt->bytes, rt->info, d_q, n, d_verdict, d_owner, dma, s) != hipSuccess)
+    if (launch_validate(rt->tab, x, rt->info, d_q, n, d_verdict, d_owner, dma, s) != hipSuccess)
         return AGILE_EDEVICE;
     return AGILE_OK;
 }

@@ -27,8 +27,8 @@ AGILE_TICKET_HD inline uint64_t* ticket_set(uint64_t* words, uint64_t launch) {
     return words + launch % TICKET_SETS * (TICKETS + 1) * TICKET_STRIDE;
 }
 
-// One thread per workgroup: whether its workgroup is the launch's last one. at.raise(w, v): *w = max(*w, v); at.add(w): *w += 1, the old value;
-// relaxed, a thread's go to one word in order.
+// One thread per workgroup: whether its workgroup is the launch's last one. at.raise(w, v): *w = max(*w, v);
+// at.add(w): *w += 1, the old value; relaxed, a thread's go to one word in order.
 template <class Atomics>
 AGILE_TICKET_HD inline bool last_workgroup(const Atomics& at, uint64_t* words, uint64_t launch, uint32_t block,
                                            uint32_t blocks) {
