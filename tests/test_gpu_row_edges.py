@@ -4,8 +4,9 @@ a whole number of rows from the allocation's ends, with outputs, sources and ind
 inside a row. Row widths below, at and above a 16-byte vector, a group of lanes and a wave."""
 import numpy as np
 import pytest
+import torch
 
-from gpu_util import Arena, Twin, log_matches, need_gpu
+from gpu_util import Arena, Twin, guard_mod, log_matches, need_gpu
 from oracle import guarded as G
 
 pytestmark = pytest.mark.gpu
@@ -60,3 +61,37 @@ def test_rows_around_the_ends_of_their_allocation(w, D):
             ar.check("scatter " + what)
             log_matches(tw, ol, "scatter " + what)
     tw.close()
+
+
+@pytest.mark.parametrize("add", [False, True])
+@pytest.mark.parametrize("w,D,n", [(4, 1, 5000), (4, 3, 300_000), (4, 5, 100_000), (4, 17, 5000), (4, 17, 200_000),
+                                   (4, 65, 40_000), (4, 255, 30_000), (8, 3, 100_000), (8, 33, 50_000),
+                                   (8, 129, 20_000)])
+def test_hostile_scatter_leaves_what_lies_around_its_table_alone(w, D, n, add):
+    """Distinct rows and rows just outside, in calls of every number of rows in flight: the bytes before and
+    behind the table are what they were, bit for bit."""
+    need_gpu()
+    g = guard_mod()
+    dt = torch.float32 if w == 4 else torch.float64
+    rows, pad = n + 100, 16
+    gen = torch.Generator(device="cuda").manual_seed(w + D + n)
+    buf = torch.randn((rows + 2 * pad) * D, generator=gen, device="cuda", dtype=dt)
+    table = buf[pad * D:(rows + pad) * D].view(rows, D)
+    src = torch.randn(n, D, generator=gen, device="cuda", dtype=dt)
+    idx = torch.randperm(rows, generator=gen, device="cuda")[:n].contiguous()
+    bad = torch.rand(n, generator=gen, device="cuda") < 0.05
+    idx[bad] = torch.where(torch.rand(int(bad.sum()), generator=gen, device="cuda") < 0.5, rows + 3, -2)
+    rt = g.RangeTable(8)
+    for t in (table, src, idx):
+        rt.insert_tensor(t)
+    before = buf.clone()
+    g.agile_guarded_scatter(rt.handle, table, D * w, idx, src, n, 0 if w == 4 else 1, int(add))
+    want = before[pad * D:(rows + pad) * D].view(rows, D).clone()
+    good = ~bad
+    want[idx[good]] = want[idx[good]] + src[good] if add else src[good]   # one addition a row: exact
+    assert torch.equal(table, want)
+    bits = torch.int32 if w == 4 else torch.int64
+    for part in (slice(0, pad * D), slice((rows + pad) * D, None)):
+        assert torch.equal(buf[part].view(bits), before[part].view(bits))
+    assert rt.fault_log()[1]["count"] == int(bad.sum()) * D
+    rt.close()
