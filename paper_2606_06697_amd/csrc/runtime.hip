@@ -10,6 +10,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <unordered_map>
@@ -134,6 +135,7 @@ struct agile_rt {
     size_t bytes_at = 0;     // where it goes in the image (0: the table has none, or it is there)
     uint64_t bytes_seen = 0;  // queries of the launches that could have used it
     size_t stage_bytes = 0;
+    std::unique_ptr<uint32_t[]> radix;    // an upload's radix entries, MAX_RADIX + 1 (nothing throws there)
     agile_fault* hlog = nullptr;
     unsigned long long* htrap = nullptr;  // log count before / after a TRAP-policy call
     uint8_t* q_ptr = nullptr;             // quarantine of the SINK policy (caller-owned)
@@ -370,7 +372,7 @@ static int upload(agile_rt* rt, hipStream_t s) {
     uint64_t* s64 = reinterpret_cast<uint64_t*>(h);
     PairRec* rec = reinterpret_cast<PairRec*>(h + rec_offset(nb));
     uint8_t* bk = h + backed_offset(nb);
-    std::vector<uint32_t> radix(MAX_RADIX + 1);
+    uint32_t* const radix = rt->radix.get();
     const auto& E = rt->entries;
     for (uint32_t b = 0; b < nb; ++b) {
         const Entry& e0 = E[2 * b];
@@ -416,7 +418,7 @@ static int upload(agile_rt* rt, hipStream_t s) {
     const size_t budget = std::min(rt->lds_budget, rt->info.lds_per_block);
     size_t o_nrec = 0;
     const auto lay_out = [&](size_t lds) {
-        search_geometry(t, s64, radix.data(), lds, rt->min_lift);
+        search_geometry(t, s64, radix, lds, rt->min_lift);
         o_nrec = o_index + t.lds_bytes;
         t.narrow = 0;
         if (!rt->wide_only) build_narrow(t, s64, rec, reinterpret_cast<uint32_t*>(h + o_nrec));
@@ -437,7 +439,7 @@ static int upload(agile_rt* rt, hipStream_t s) {
         if (t.compressed) reinterpret_cast<uint32_t*>(ix)[k] = k < t.ntop ? key32(b) : 0xFFFFFFFFu;
         else reinterpret_cast<uint64_t*>(ix)[k] = k < t.ntop ? s64[b] : U64MAX;
     }
-    std::memcpy(ix + t.radix_off, radix.data(), ((size_t)t.nr + 1) * 4);
+    std::memcpy(ix + t.radix_off, radix, ((size_t)t.nr + 1) * 4);
     // the last readers of image x
     for (hipEvent_t e : im.retired)
         if (hipStreamWaitEvent(s, e, 0) != hipSuccess) return AGILE_EDEVICE;
@@ -597,6 +599,11 @@ int agile_rt_create(agile_rt** out, uint32_t capacity, int device) {
     rt->device = device;
     rt->capacity = capacity;
     rt->cap_nb = (capacity + 1) / 2;
+    rt->radix.reset(new (std::nothrow) uint32_t[MAX_RADIX + 1]);
+    if (!rt->radix) {
+        delete rt;
+        return AGILE_ENOMEM;
+    }
     hipDeviceProp_t p;
     if (hipGetDeviceProperties(&p, device) != hipSuccess) {
         delete rt;
