@@ -390,7 +390,8 @@ def _kernel_sources_digest(kernel):
     import hashlib
     csrc = os.path.join(ROOT, "paper_2606_06697_amd", "csrc")
     files = {"validate": ["k_validate.hip"], "triad": ["k_stream.hip"],
-             "gather": ["k_gather.hip"]}[kernel] + ["guard_device.h", "guard_arith.h", "launch.h"]
+             "gather": ["k_gather.hip"]}[kernel] + ["guard_device.h", "guard_arith.h", "ticket.h", "launch.h",
+                                                "launch_grid.h"]
     h = hashlib.sha256()
     for f in files:
         with open(os.path.join(csrc, f), "rb") as fh:

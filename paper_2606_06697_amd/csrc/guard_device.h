@@ -125,7 +125,9 @@ struct DevLog {
 };
 
 // A table of at most INLINE_RANGES ranges in a launch's own arguments (entries in address order), for
-// the reason of its first denial.
+// the reason of its first denial: as many as a wave has lanes, and 1.3 of the 4 KiB that arguments may take.
+// After a change of the table a gather of 1,000 rows of 64 floats takes 7 us with 3 ranges, 16-22 with 103 and
+// 26-31 with 4,003: those are uploaded, and a kernel of its own records the denials.
 constexpr uint32_t INLINE_RANGES = 64;
 struct InlineTab {
     uint32_t n;

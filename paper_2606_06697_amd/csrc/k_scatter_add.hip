@@ -20,16 +20,17 @@
 //
 // Chunk path (smaller calls, or destination intervals too large for 32-bit keys): one kernel, whose
 // workgroups sort 64 to 1,024 consecutive indices each in LDS and add each row of the chunk once, with
-// one atomic per element; rows outside the interval are checked per element.
+// one atomic per element; rows outside the interval are checked per element. The order of the atomics
+// is not fixed: a row with indices in three or more chunks may differ in its last bits from call to call.
 //
 // Measured against an earlier chunk path of 2,048 indices a workgroup (one CU in use for every 2,048
 // rows) and a reduce with a wave per row of any width (Zipf indices, 4,096-2^20 destination rows):
 //   rows x columns       before     now
-//     5,000 x 64         318 us     17 us   (chunks)
-//    50,000 x 32          82 us     34 us   (chunks)
-//   131,072 x 64         128 us     46 us   (chunks)
-//   1,048,576 x 32       204 us    132 us   (sorted)
-//   1,048,576 x 256      375 us    335 us   (sorted; the reduce alone 297 -> 265)
+//     5,000 x 64         312 us     13 us   (chunks)
+//    50,000 x 32          85 us     26 us   (chunks)
+//   131,072 x 64         131 us     41 us   (chunks)
+//   1,048,576 x 32       190 us    125 us   (sorted)
+//   1,048,576 x 256      358 us    327 us   (sorted; the reduce alone 297 -> 265)
 #include <type_traits>
 
 #include "launch.h"

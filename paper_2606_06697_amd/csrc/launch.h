@@ -82,9 +82,10 @@ size_t scatter_add_scratch_bytes(uint64_t n);
 // Scatter-add calls that sort their destination keys (given scratch): of more than 2^18 rows, or of
 // at least 2^15 rows and 96 MiB. Sorting costs ten launches, about 50 us, and then reads each row once
 // and writes it once; the chunk path is one launch, but adds a row's sum once per chunk. Chunk against
-// sorted, Zipf indices: 65,536 x 256 floats 58 / 60 us, 131,072 x 64 46 / 80, 131,072 x 256 92 / 96 (all
-// different: 131 / 106), 262,144 x 64 71 / 93, 262,144 x 256 170 / 138. Beyond 2^18 rows (256 chunks)
-// the hottest row's sum would be added up in more steps, and less exactly, than the sorted path does.
+// sorted, Zipf indices (all different): 32,768 x 64 floats 27 / 60 us (27 / 62), 65,536 x 256 57 / 74 (77 / 84),
+// 131,072 x 64 41 / 67 (44 / 72), 131,072 x 256 90 / 90 (129 / 108), 262,144 x 64 64 / 76, 262,144 x 256 157 /
+// 124. Beyond 2^18 rows (256 chunks) the hottest row's sum would be added up in more steps, and less exactly,
+// than the sorted path does.
 inline bool scatter_add_sorts(uint64_t n, uint64_t rb) {
     return n > (1u << 18) || (n >= (1u << 15) && n * rb > (96u << 20));
 }

@@ -86,10 +86,12 @@ typedef uint16_t u16_any __attribute__((aligned(1)));
 // load each and its verdicts and slots one store each (the vector memory path takes instructions in
 // order, so fewer of them leave it to the record reads), and a thread's record reads, random ones of a
 // table that the L2s hold, are issued together. The streams are non-temporal, so that they do not push
-// the slot records out of L2. Bound by the record reads, a 128-byte line from L2 for each of them
-// whatever its width (without them 48 us for 2^24 tokens, the streams' time); 4-byte records halve the
-// lines that miss L2 or L1. 2^24 tokens over 2^20 slots: 131 us (141 with 8-byte records and four single
-// tokens a thread), over 2^18 129 (132); four pairs a thread 133.
+// the slot records out of L2. Bound by the vector memory path, on which record reads (a 128-byte line
+// each, whatever the record's width) and streams do not overlap: 2^24 tokens over 2^20 slots take 130 us, the
+// streams alone 48, the record reads alone 65, with the tokens' stream 88, with all streams in but none out
+// 112, with those out but none in 58. 17 us are more than the two add up to; the size of the table is not
+// the reason (2^18 slots, which fit L2 four times, 127). 141 with 8-byte records and four single tokens a
+// thread; four pairs a thread 133.
 //
 // LREC: the packed records in LDS, staged by every workgroup, for large batches on tables that fit there
 // (up to 40,960 slots). The record reads leave the vector memory path, and the streams bound it: 2^24
