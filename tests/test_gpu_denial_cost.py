@@ -1,6 +1,6 @@
 """Denied accesses are no more expensive than allowed ones by much: a client that aims its indices
 outside its allocations must not slow down the launch that it shares the chip with. Each case times a
-call with denials against the same call without any, on the same box and in turn, with a bound well
+call with denials against the same call without any, on the same GPU and in turn, with a bound well
 above what a launch needs for the exact path and well below what waiting for one memory place costs,
 and checks the log's count and first record over all the calls."""
 import numpy as np
